@@ -1,0 +1,191 @@
+"""Workloads of entmax attention through the public binding, for timing and for comparing two builds.
+
+`listed()` are the configurations the library is used in: the language-model attention layer (12 heads of 64,
+16 heads of 128) forward and backward at training lengths, the forward at evaluation lengths, the layer with its scale
+projections and distance bias, the dense-logit setting, a small fp32 problem, and decode steps against a long key cache.
+`draw(rng)` gives further problems of the same ranges.  A case is a dict:
+
+  kind      "train": forward keeping the support lists, then backward; "layer": the same between the scale projections
+            (forward before, backward after); "forward": forward alone; "decode": nq query rows against nk keys
+  B H nq nk d dtype alpha causal   the attention problem
+  scale     "none": logits / sqrt(d); "head": beta, gamma per head ~ U(0.5, 1.5), delta = 1; "dense": beta per head
+            ~ U(0.5, 1.5), gamma = -1/2, delta = 0 (rows keep most of their keys); "proj": beta, gamma per query from
+            the projections of the layer's tokens (kind "layer")
+  planted   fraction of the keys moved along a later query so that their logit is 4 (before rounding)
+  nape      every other head carries the linear distance bias
+  logn      0: n in (ln n)^gamma is nk, 1: the number of keys the row sees
+"""
+import math
+
+import torch
+
+from paper_2506_16640_amd import binding, synth
+
+E = 768  # hidden width of the layer whose projections give beta and gamma
+
+
+def _case(kind, B, H, nq, nk, d, alpha, scale, dtype="bf16", causal=True, planted=0.0, nape=False, logn=0, name=None):
+    c = dict(kind=kind, B=B, H=H, nq=nq, nk=nk, d=d, dtype=dtype, alpha=alpha, causal=causal, scale=scale, planted=planted,
+             nape=nape, logn=logn)
+    if name is not None:
+        c["name"] = name
+    return c
+
+
+def listed():
+    return [
+        # one small fp32 head: launch latency and host path, the size a unit test or a tiny model steps through
+        _case("train", 1, 1, 256, 256, 64, 1.5, "none", dtype="fp32", name="small_fp32_train"),
+        # evaluation of a 12-head model at its training length, many short sequences
+        _case("forward", 8, 12, 1024, 1024, 64, 1.5, "head", name="n1024_forward"),
+        # the training step of the language-model layer at n = 4096
+        _case("train", 4, 12, 4096, 4096, 64, 1.5, "head", planted=0.05, name="n4096_train"),
+        # the same layer with the longer supports of alpha = 1.25
+        _case("train", 4, 12, 4096, 4096, 64, 1.25, "head", planted=0.05, name="n4096_train_alpha1.25"),
+        # logits of constant range: rows keep most of their keys
+        _case("train", 4, 12, 4096, 4096, 64, 1.5, "dense", planted=0.05, name="n4096_train_dense"),
+        # wide heads, longer sequence
+        _case("train", 2, 16, 8192, 8192, 128, 1.5, "head", name="n8192_d128_train"),
+        # the layer as a whole at an odd length: projections, half of the heads with the distance bias, their backward
+        _case("layer", 3, 12, 1999, 1999, 64, 1.5, "proj", nape=True, logn=1, name="layer_n1999_nape"),
+        # sparsemax forward on wide heads at an odd length
+        _case("forward", 2, 16, 5003, 5003, 128, 2.0, "head", name="n5003_d128_alpha2_forward"),
+        # long-context evaluation
+        _case("forward", 1, 12, 32768, 32768, 64, 1.5, "head", planted=0.05, name="n32768_forward"),
+        # one new token against a long key cache
+        _case("decode", 4, 12, 1, 32768, 64, 1.5, "head", name="decode_1_of_32768"),
+        # a few new tokens per sequence against caches of an odd length, wide heads
+        _case("decode", 8, 16, 5, 6007, 128, 1.5, "head", name="decode_5_of_6007_d128"),
+        # a chunk of a prompt against the long cache
+        _case("decode", 4, 12, 64, 32768, 64, 1.5, "head", name="decode_64_of_32768"),
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    kind = rng.choice(["train", "train", "train", "layer", "forward", "forward", "decode", "decode"])
+    H, d = rng.choice([(12, 64), (12, 64), (8, 64), (16, 128)])
+    if kind == "decode":
+        nq = rng.choice([1, 1, 2, rng.randint(3, 8), rng.randint(9, 64)])
+        nk = _log_int(rng, max(512, 64 * nq), 32768)
+        B = rng.randint(1, max(1, min(8, 4 * 12 * 32768 * 64 // (H * nk * d))))
+        return _case(kind, B, H, nq, nk, d, rng.choice([1.5, 1.5, 1.25, 2.0]), "head", nape=rng.random() < 0.2)
+    # score products of a causal forward: at most those of 12 heads of 64 at n = 32768 (forward), of 48 at 4096 (train)
+    most = (12 * 32768 ** 2 if kind == "forward" else 48 * 4096 ** 2) * 64 // d
+    n = _log_int(rng, 200, 32768 if kind == "forward" else 7000)
+    n = min(n, int(math.sqrt(most / H)))
+    causal = not (kind == "forward" and n <= 4096 and rng.random() < 0.2)
+    B = rng.randint(1, max(1, min(8, most // (H * n * n))))
+    if not causal:
+        B = max(1, B // 2)
+    dtype = "fp32" if n <= 600 and rng.random() < 0.25 else "bf16"
+    # alpha = 2: the backward's weights jump where a key enters the support, so that two correct programs may differ in
+    # a whole row of dQ; the forward does not
+    alpha = rng.choice([1.5, 1.5, 1.25, 2.0, 1.7]) if kind == "forward" else rng.choice([1.5, 1.5, 1.25, 1.4])
+    scale = "proj" if kind == "layer" else rng.choice(["head", "head", "head", "head", "none", "dense"])
+    if scale != "head" or alpha < 1.5:  # long supports: keep the cost within the listed cases'
+        n, B = min(n, 4096 if d == 64 else 2048), min(B, 4)
+    return _case(kind, B, H, n, n, d, alpha, scale, dtype=dtype, causal=causal,
+                 planted=0.05 if causal and scale == "head" and rng.random() < 0.5 else 0.0, nape=causal and rng.random() < 0.25,
+                 logn=rng.choice([0, 0, 1]))
+
+
+def _plant(q, k, frac, gen):
+    """Moves ceil(frac n) keys of every head along one random later query so that their logit becomes 4."""
+    B, H, n, d = k.shape
+    m = int(math.ceil(frac * n))
+    js = torch.rand(B, H, n, generator=gen, device=k.device).argsort(dim=-1)[..., :m]
+    later = (torch.rand(B, H, m, generator=gen, device=k.device) * (n - js)).long()
+    at = lambda t, idx: torch.gather(t, 2, idx[..., None].expand(-1, -1, -1, d))  # noqa: E731
+    qi, kj = at(q, (js + later).clamp_(max=n - 1)), at(k, js)
+    coef = (4.0 * math.sqrt(d) - (qi * kj).sum(-1)) / (qi * qi).sum(-1)
+    k.scatter_(2, js[..., None].expand(-1, -1, -1, d), kj + coef[..., None] * qi)
+
+
+def prepare(case, seed):
+    dev = torch.device("cuda")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(int(seed))
+    B, H, nq, nk, d = (case[x] for x in ("B", "H", "nq", "nk", "d"))
+    tdt = torch.bfloat16 if case["dtype"] == "bf16" else torch.float32
+    normal = lambda *s: torch.randn(*s, generator=gen, device=dev)  # noqa: E731
+    q, k = normal(B, H, nq, d).to(tdt).float(), normal(B, H, nk, d)
+    if case["planted"] > 0.0:
+        _plant(q, k, case["planted"], gen)
+    s = {"q": q.to(tdt), "k": k.to(tdt), "v": normal(B, H, nk, d).to(tdt), "kind": case["kind"], "beta": None, "gamma": None}
+    del q, k
+    uniform = lambda: 0.5 + torch.rand(H, generator=gen, device=dev)  # noqa: E731
+    delta = 1.0
+    if case["scale"] == "head":
+        s["beta"], s["gamma"] = uniform(), uniform()
+    elif case["scale"] == "dense":
+        s["beta"], s["gamma"], delta = uniform(), torch.full((H,), -0.5, device=dev), 0.0
+    elif case["scale"] == "proj":
+        s["x"] = normal(B, nq, E).to(tdt)
+        s["wb"], s["wg"] = 0.05 * normal(H, E), 0.05 * normal(H, E)
+        s["beta"] = torch.empty(B, H, nq, device=dev)  # layout of what the projections return
+    s["kw"] = dict(alpha=case["alpha"], delta=delta, causal=case["causal"], logn_mode=case["logn"])
+    if case["nape"]:
+        s["kw"].update(alibi_slopes=torch.from_numpy(synth.nape_slopes(H)).to(dev), bias_mode=0)
+    prm = binding.make_params(s["q"], s["k"], case["alpha"], delta, case["causal"], s["beta"], case["logn"])
+    s["out"] = torch.empty_like(s["q"])
+    s["tau"] = torch.empty(B, H, nq, dtype=torch.float32, device=dev)
+    train = case["kind"] in ("train", "layer")
+    need = max(binding.workspace_bytes(prm, 0), binding.workspace_bytes(prm, 1) if train else 0, 256)
+    s["workspace"] = torch.empty(need, dtype=torch.uint8, device=dev)
+    if train:
+        s["do"] = normal(B, H, nq, d).to(tdt)
+        s["saved"] = binding.new_saved(prm, dev)
+    return s
+
+
+def run(s):
+    q, k, v, kw = s["q"], s["k"], s["v"], s["kw"]
+    if s["kind"] in ("forward", "decode"):
+        return binding.entmax_attn_fwd(q, k, v, beta=s["beta"], gamma=s["gamma"], out=s["out"], tau=s["tau"],
+                                       workspace=s["workspace"], **kw)
+    beta, gamma = s["beta"], s["gamma"]
+    if s["kind"] == "layer":
+        beta, gamma = binding.scale_proj_fwd(s["x"], s["wb"], s["wg"], 1.0)
+    o, tau = binding.entmax_attn_fwd(q, k, v, beta=beta, gamma=gamma, out=s["out"], tau=s["tau"], workspace=s["workspace"],
+                                     saved=s["saved"], **kw)
+    dq, dk, dv, dbeta, dgamma = binding.entmax_attn_bwd(q, k, v, o, s["do"], tau, beta=beta, gamma=gamma,
+                                                        workspace=s["workspace"], saved=s["saved"], **kw)
+    res = [o, tau, dq, dk, dv, dbeta, dgamma]
+    if s["kind"] == "layer":
+        res += [beta, gamma, *binding.scale_proj_bwd(s["x"], s["wb"], s["wg"], beta, gamma, dbeta, dgamma, 1.0)]
+    return [t for t in res if t is not None]
+
+
+def work(case):
+    B, H, nq, nk, d = (case[x] for x in ("B", "H", "nq", "nk", "d"))
+    eb = 2 if case["dtype"] == "bf16" else 4
+    rows, train = B * H * nq, case["kind"] in ("train", "layer")
+    pairs = float(B * H) * (nq * (nk - nq) + nq * (nq + 1) / 2.0 if case["causal"] else float(nq) * nk)
+    dense = case["scale"] == "dense"
+    # forward: Q in, O and tau out, K in; the values only where a probability is not zero (about two keys a row; at most
+    # every row of V once)
+    v_rows = B * H * nk if dense else min(B * H * nk, 2 * rows)
+    nbytes = eb * d * (2 * rows + B * H * nk + v_rows) + 4 * rows
+    flops = 2.0 * d * pairs * (2 if dense else 1)  # every visible score; P V where the rows keep most keys
+    if train:
+        # dO in, dQ, dK, dV out (Q, K, V are in already); of the products only a dense row's cannot be left out: S, dP,
+        # dV, dQ, dK
+        nbytes += eb * d * (2 * rows + 2 * B * H * nk)
+        flops += 10.0 * d * pairs if dense else 0.0
+    if case["kind"] == "layer":
+        nbytes += 2 * eb * B * nq * E + 8 * rows + 16 * H * E  # X in, dX out; beta and gamma; the projection vectors and their gradients
+        flops += 3 * 2.0 * B * nq * E * 2 * H
+    return {"bytes": nbytes, "flops": flops}
+
+
+def tolerance(case):
+    # Two ways through the library (support lists, and full tiles with P and dS rounded to bf16 between products) differ
+    # by up to 7.5e-3 in dQ over these ranges, 0.33 at the worst element; the same values in fp32 throughout lie 1e-3 to
+    # 4e-3 from either.  fp32: up to 5.1e-6 (sums of d beta, d gamma in another order), 8.1e-5 at the worst element.
+    if case["dtype"] == "bf16":
+        return {"rel": 1.5e-2, "max": 0.8}
+    return {"rel": 2e-5, "max": 4e-4}
