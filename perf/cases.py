@@ -189,3 +189,93 @@ def tolerance(case):
     if case["dtype"] == "bf16":
         return {"rel": 1.5e-2, "max": 0.8}
     return {"rel": 2e-5, "max": 4e-4}
+
+
+def _exact_rows(q, k, v, s, nape, alpha, causal, r0, do=None):
+    """fp64 rows r0 .. of one head: q, do [n, d], k, v [nk, d], s [n] the logit multiplier.  Returns o, tau and, with
+    do, dq, the contributions to dk and dv, and the gradient with respect to s."""
+    n, d = q.shape
+    nk, r = k.shape[0], 1.0 / (alpha - 1.0)
+    pos = torch.arange(r0, r0 + n, device=q.device)[:, None]
+    keys = torch.arange(nk, device=q.device)[None]
+    z = q @ k.T / math.sqrt(d)
+    if nape:
+        z -= nape * (pos - keys).clamp_(min=0)
+    y = (alpha - 1.0) * s[:, None] * z
+    if causal:
+        y.masked_fill_(keys > pos, -math.inf)
+    top = y.amax(dim=1, keepdim=True)
+    m = int((y > top - 1.0).sum(dim=1).max())
+    c = y if 4 * m > nk else y.topk(m, dim=1)[0]
+    tau = top - 1.0
+    for _ in range(200):  # f is convex and decreasing, f >= 0 at the start: the steps rise to the root
+        x = (c - tau).clamp_(min=0)
+        g = torch.where(x > 0, x ** (r - 1.0), 0.0).sum(dim=1, keepdim=True)
+        step = ((x ** r).sum(dim=1, keepdim=True) - 1.0) / (r * g)
+        tau = tau + step
+        if float(step.max()) < 1e-14:
+            break
+    x = (y - tau).clamp_(min=0)
+    p = x ** r
+    o = p @ v
+    if do is None:
+        return o, tau[:, 0]
+    g = torch.where(x > 0, x ** (r - 1.0), 0.0)
+    dp = do @ v.T
+    ds = g * (dp - (g * dp).sum(dim=1, keepdim=True) / g.sum(dim=1, keepdim=True))
+    w = ds * (s / math.sqrt(d))[:, None]
+    return o, tau[:, 0], w @ k, w.T @ q, p.T @ do, (ds * z).sum(dim=1)
+
+
+def exact(case, seed):
+    s = prepare(case, seed)
+    dbl = lambda t: t.double()  # noqa: E731
+    B, H, nq, nk, d = (case[x] for x in ("B", "H", "nq", "nk", "d"))
+    train, layer, delta = case["kind"] in ("train", "layer"), case["kind"] == "layer", s["kw"]["delta"]
+    off = nk - nq
+    n = torch.full((nq,), float(nk), dtype=torch.float64, device="cuda")
+    if case["logn"] and case["causal"]:
+        n = torch.arange(off + 1, nk + 1, dtype=torch.float64, device="cuda")
+    L = n.log()
+    if layer:
+        x = dbl(s["x"])
+        u, t = x @ dbl(s["wb"]).T, (x @ dbl(s["wg"]).T).tanh()
+        beta, gamma = (torch.nn.functional.softplus(u).transpose(1, 2), t.transpose(1, 2))
+    elif s["beta"] is not None:
+        beta, gamma = (dbl(a)[None, :, None].expand(B, H, nq) for a in (s["beta"], s["gamma"]))
+    else:
+        beta = gamma = None
+    Lg = L.new_zeros(B, H, nq) if beta is None else torch.where(n > 1, L ** gamma, 0.0)
+    scale = delta + (beta * Lg if beta is not None else Lg)
+    o, tau = torch.empty(B, H, nq, d, dtype=torch.float64, device="cuda"), torch.empty(B, H, nq, dtype=torch.float64, device="cuda")
+    if train:
+        dq, dscale = torch.empty_like(o), torch.empty_like(tau)
+        dk, dv = (torch.zeros(B, H, nk, d, dtype=torch.float64, device="cuda") for _ in range(2))
+    slopes = s["kw"].get("alibi_slopes")
+    rows = max(64, 2 ** 26 // nk)
+    for b in range(B):
+        for h in range(H):
+            kk, vv = dbl(s["k"][b, h]), dbl(s["v"][b, h])
+            for r0 in range(0, nq, rows):
+                e = slice(r0, min(nq, r0 + rows))
+                end = min(nk, e.stop + off) if case["causal"] else nk
+                res = _exact_rows(dbl(s["q"][b, h, e]), kk[:end], vv[:end], scale[b, h, e], 0.0 if slopes is None else float(slopes[h]),
+                                  case["alpha"], case["causal"], r0 + off, dbl(s["do"][b, h, e]) if train else None)
+                o[b, h, e], tau[b, h, e] = res[:2]
+                if train:
+                    dq[b, h, e], dscale[b, h, e] = res[2], res[5]
+                    dk[b, h, :end] += res[3]
+                    dv[b, h, :end] += res[4]
+    if not train:
+        return o, tau
+    out = [o, tau, dq, dk, dv]
+    if beta is None:
+        return out
+    db = dscale * Lg
+    dg = torch.where(n > 1, db * beta * L.log(), 0.0)
+    if not layer:
+        return out + [db.sum(dim=(0, 2)), dg.sum(dim=(0, 2))]
+    out += [db, dg, beta.contiguous(), gamma.contiguous()]
+    du, dt = (db * -torch.expm1(-beta)).transpose(1, 2), (dg * (1.0 - gamma * gamma)).transpose(1, 2)
+    flat = lambda a: a.reshape(B * nq, -1)  # noqa: E731
+    return out + [du @ dbl(s["wb"]) + dt @ dbl(s["wg"]), flat(du).T @ flat(x), flat(dt).T @ flat(x)]
