@@ -66,10 +66,21 @@ constexpr size_t cell_bytes_per_workgroup(int cap) { return (size_t)kThreads * c
 // when the keys are at least kDecodeLongRatio times as many.
 constexpr int kDecodeRows = 8;
 constexpr int kDecodeRowsLong = 64;
-constexpr int kDecodeMfmaRows = 16;  // from this many rows on the scores come from the matrix cores (measured: 9 rows
-                                     // 91 us with per-row dot products against 114 us, 16 rows 131 against 121)
+// From this many rows on the scores come from the matrix cores, in bf16 (5 rows, 201 MB of K: 41 us with per-row dot
+// products, 32 us so; one row is bound by K either way) and in fp32 (whose matrix rate is that of the dot products).
+constexpr int kDecodeMfmaRows = 2;
+constexpr int kDecodeMfmaRowsF32 = 16;
 constexpr int kDecodeLongRatio = 64;
 constexpr int kDecodeChunk = 512;  // keys per workgroup of the score kernel (64 to 128 KB of K); 256 to 2048 measured alike
+// The matrix-core score kernel: chunks a workgroup takes.  The more it takes, the sooner its rows know a large score
+// and the fewer of the others they write; but every CU should have three workgroups.
+constexpr int kDecodeMfmaChunks = 4;
+inline int decode_chunks_per_wg(long long heads, int nchunks) {
+  int n = kDecodeMfmaChunks;
+  while (n > 1 && heads * ((nchunks + n - 1) / n) < 768) n /= 2;
+  return n;
+}
+constexpr int kDecodeManyRows = 512;  // from this many query rows on the solve kernel runs with 256 threads a row
 inline bool decode_shape(int Nq, int Nk) {
   return Nq <= kDecodeRows || (Nq <= kDecodeRowsLong && (long long)Nk >= (long long)kDecodeLongRatio * Nq);
 }

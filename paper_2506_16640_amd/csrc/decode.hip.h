@@ -20,7 +20,6 @@ namespace entmax {
 
 // dynamic LDS of decode_scores_kernel: Q rows as in memory, the groups' maxima, a coefficient and a limit per row
 inline size_t decode_scores_lds(int Nq, int D, size_t esize) { return (size_t)Nq * (D * esize + (kThreads / 8) * 4 + 12); }
-constexpr int kDecodeSolveThreads = 1024;
 constexpr int kDecodeListCap = 4096;    // support candidates kept in LDS; longer ones are re-read from the score row
 
 struct DecodeArgs {
@@ -31,10 +30,33 @@ struct DecodeArgs {
   void* O;
   float* tau;     // [B*H*Nq]
   float* scores;  // [B*H*Nq][nks] workspace, entries j < row_limit(i) written; nks = Nk rounded up to 4
-  float* cmax;    // [B*H*Nq][nchunks] largest score of each chunk of `chunk` keys (-inf: none visible)
+  uint32_t* cmax; // [B*H*Nq][nchunks] largest score of each chunk of kDecodeChunk keys and which of its 32-key blocks'
+                  // scores were written, see pack_cmax()
   int nks, nchunks;
-  int chunk;      // keys per workgroup of decode_scores_kernel, a multiple of 256
+  int chunks_per_wg;  // decode_scores_mfma_kernel: chunks a workgroup takes (at most kDecodeMfmaChunks)
 };
+
+// A chunk's word: the largest visible score rounded down to 16 bits (a bf16 that is not larger) above one bit per
+// 32-key block of the chunk whose scores were written (kDecodeChunk / 32 = 16 blocks).
+static_assert(kDecodeChunk == 16 * 32, "one bit per 32-key block in the low half of the word");
+constexpr uint32_t kCmaxNone = 0xff800000u;  // -inf, nothing written
+__device__ __forceinline__ uint32_t pack_cmax(float m, uint32_t written) {
+  const uint32_t u = __float_as_uint(m);
+  const uint32_t down = (u & 0x80000000u) ? u + 0xffffu : u;  // towards -inf: a negative number's magnitude goes up
+  return (m == -kInf ? kCmaxNone : down & 0xffff0000u) | (written & 0xffffu);
+}
+// a value not above / not below the chunk's largest score
+__device__ __forceinline__ float cmax_floor(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
+__device__ __forceinline__ float cmax_ceil(uint32_t w) {
+  const float f = cmax_floor(w);
+  return fmaf(fabsf(f), 0x1p-7f, f) + 0x1p-126f;  // (one step of a bf16 is at most 2^-7 of its value)
+}
+// order-preserving map of floats to signed integers, and back
+__device__ __forceinline__ int ordered_bits(float x) {
+  const int i = __float_as_int(x);
+  return i >= 0 ? i : i ^ 0x7fffffff;
+}
+__device__ __forceinline__ float from_ordered_bits(int i) { return __int_as_float(i >= 0 ? i : i ^ 0x7fffffff); }
 
 // x + (x of the lane that the DPP control CTRL pairs this lane with): one VALU instruction, no LDS traffic.
 template <int CTRL>
@@ -72,12 +94,12 @@ __global__ __launch_bounds__(kThreads) void decode_scores_kernel(DecodeArgs A) {
   int* limit = reinterpret_cast<int*>(coef + g.Nq);                        // [Nq]
   float* ybias = reinterpret_cast<float*>(limit + g.Nq);                   // [Nq] distance bias per unit distance, times (alpha-1)
   const int tid = threadIdx.x, bh = blockIdx.y, b = bh / g.H, h = bh % g.H;
-  const int j0 = blockIdx.x * A.chunk;
+  const int j0 = blockIdx.x * kDecodeChunk;
   const T* Qh = reinterpret_cast<const T*>(A.Q) + (long long)b * g.q_sb + (long long)h * g.q_sh;
   const T* Kh = reinterpret_cast<const T*>(A.K) + (long long)b * g.kv_sb + (long long)h * g.kv_sh;
   // the first key rows are requested before anything else: their addresses need nothing from the queries
   const int grp = tid >> 3, sub = tid & 7;
-  const int jend = min(j0 + A.chunk, g.Nk);
+  const int jend = min(j0 + kDecodeChunk, g.Nk);
   RawRow<T, kSlice> nx[4];
   auto fetch = [&](RawRow<T, kSlice>* dst, int base) {
 #pragma unroll
@@ -146,102 +168,139 @@ __global__ __launch_bounds__(kThreads) void decode_scores_kernel(DecodeArgs A) {
     float mx = i < g.Nq ? group_max[i * kGroups + (tid & 31)] : -kInf;
 #pragma unroll
     for (int off = 16; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-    if ((tid & 31) == 0 && i < g.Nq) A.cmax[((long long)bh * g.Nq + i) * A.nchunks + blockIdx.x] = mx;
+    if ((tid & 31) == 0 && i < g.Nq) A.cmax[((long long)bh * g.Nq + i) * A.nchunks + blockIdx.x] = pack_cmax(mx, 0xffffu);
   }
 }
 
-// The same scores for 9 to 64 query rows, where the per-row dot products of the kernel above (about 5 us per
-// row at Nk = 32768 and 48 heads) outweigh the read of K: S = Q K_chunk^T on the matrix cores, one or two
-// 32-query blocks against 32-key blocks whose fragments come straight from global memory (every K row is read
-// once by one lane pair, 16 bytes at a time along the row).  In the accumulator layout the 32 lanes of a half
-// wave hold 32 consecutive keys of one query: the score rows are written in 128-byte runs.
-template <typename T, int D>
+// The same scores for several query rows on the matrix cores (bf16 from kDecodeMfmaRows rows on, fp32 from
+// kDecodeMfmaRowsF32): S^T = K_block Q^T with 32-key blocks whose fragments come straight from global memory (each
+// K row is read once, the next block's rows while this one is computed on) against NQB 32-query blocks.  A lane owns
+// a query row and 16 of the block's 32 keys, so a row's largest score of the block is 15 maxima and one exchange.
+// What bounds it is reading K once; the fp32 scores of 64 rows would be twice the bytes of K.  So a row's scores of a
+// block are written only if the largest of them is above the row's largest score so far less one, whatever wave of
+// the workgroup found that: a key at or below (largest score) - 1 has probability zero (App. A, lower end of the
+// bracket).  Which blocks of a chunk were written is noted beside the chunk's maximum (pack_cmax).
+// Measured: 48 heads, 64 rows, 32768 keys, D 64: 156 us with every score written, 57 us so (two blocks on their way instead of one: the same); 128 heads, 5 rows, 6007
+// keys, D 128: 41 us with per-row dot products (5 us a row at 201 MB of K), 32 us so, which is 6.1 TB/s on K.
+template <typename T, int D, int NQB>
 __global__ __launch_bounds__(kThreads) void decode_scores_mfma_kernel(DecodeArgs A) {
   constexpr int NC = D / 16;
-  __shared__ f32x4_t rowinfo[64];  // per query row: coefficient, bias per unit distance, limit, position (as bits)
-  __shared__ float wmax[kWaves][64];
+  constexpr int kBlocksPerChunk = kDecodeChunk / 32;
+  __shared__ int rowmax[NQB * 32];                                   // ordered_bits() of a row's largest score so far
+  __shared__ float wmax[kDecodeMfmaChunks][kWaves][NQB * 32];        // per chunk: what each wave saw and wrote
+  __shared__ uint32_t wmask[kDecodeMfmaChunks][kWaves][NQB * 32];
   const Geom& g = A.g;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 31, hh = lane >> 5;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, li = lane & 31, hh = lane >> 5;
   const int bh = blockIdx.y, b = bh / g.H, h = bh % g.H;
-  const int jc0 = blockIdx.x * A.chunk, jend = min(jc0 + A.chunk, g.Nk);
+  const int chunk0 = blockIdx.x * A.chunks_per_wg;
+  const int nblk = min(A.chunks_per_wg * kBlocksPerChunk, (g.Nk - chunk0 * kDecodeChunk + 31) >> 5);  // 32-key blocks of this workgroup
+  const int jc0 = chunk0 * kDecodeChunk;
   const T* Qh = reinterpret_cast<const T*>(A.Q) + (long long)b * g.q_sb + (long long)h * g.q_sh;
   const T* Kh = reinterpret_cast<const T*>(A.K) + (long long)b * g.kv_sb + (long long)h * g.kv_sh;
-  const int nqblk = (g.Nq + 31) >> 5;  // 1 or 2
-  if (tid < 64) {
-    const bool valid = tid < g.Nq;
-    const int lim = valid ? row_limit(g, tid) : 0;
-    const float cf = valid ? (g.alpha - 1.0f) * row_scale(g, b, h, tid, lim, nullptr, nullptr, nullptr) * (1.0f / sqrtf((float)D))
-                           : 0.f;
-    rowinfo[tid] = f32x4_t{cf, valid ? fabsf(cf) * bias_w<D>(g, h, cf, fabsf(cf)) : 0.f, __int_as_float(lim),
-                           __int_as_float(tid + (g.Nk - g.Nq))};
-  }
-  // query fragments (A operand: row = query, 8 features per lane half)
-  Frag<T> qf[2][NC];
+  Frag<T> kf[NC], kn[NC];
+  auto fetch = [&](Frag<T>* dst, int blk) {  // (rows past the end repeat the last one; their scores are masked)
+    const T* krow = Kh + (long long)min(jc0 + blk * 32 + li, g.Nk - 1) * g.kv_sn + 8 * hh;
 #pragma unroll
-  for (int qb = 0; qb < 2; ++qb) {
-    const int row = qb * 32 + li;
+    for (int cc = 0; cc < NC; ++cc) dst[cc] = Elem<T>::load(krow + 16 * cc);
+  };
+  if (wave < nblk) fetch(kn, wave);
+  Frag<T> qf[NQB][NC];
+  float cf[NQB], yb[NQB], top[NQB], cm[NQB];
+  int lim[NQB];
+  uint32_t mask[NQB];
+#pragma unroll
+  for (int qb = 0; qb < NQB; ++qb) {
+    const int i = qb * 32 + li;
+    const bool valid = i < g.Nq;
+    lim[qb] = valid ? row_limit(g, i) : 0;
+    cf[qb] = valid ? (g.alpha - 1.0f) * row_scale(g, b, h, i, lim[qb], nullptr, nullptr, nullptr) * (1.0f / sqrtf((float)D)) : 0.f;
+    yb[qb] = valid ? fabsf(cf[qb]) * bias_w<D>(g, h, cf[qb], fabsf(cf[qb])) : 0.f;
+    top[qb] = cm[qb] = -kInf;
+    mask[qb] = 0u;
 #pragma unroll
     for (int cc = 0; cc < NC; ++cc)
-      qf[qb][cc] = row < g.Nq ? Elem<T>::load(Qh + (long long)row * g.q_sn + 16 * cc + 8 * hh) : Elem<T>::zero();
+      qf[qb][cc] = valid ? Elem<T>::load(Qh + (long long)i * g.q_sn + 16 * cc + 8 * hh) : Elem<T>::zero();
   }
+  if (tid < NQB * 32) rowmax[tid] = ordered_bits(-kInf);
+  for (int e = tid; e < kDecodeMfmaChunks * kWaves * NQB * 32; e += kThreads) {
+    (&wmax[0][0][0])[e] = -kInf;
+    (&wmask[0][0][0])[e] = 0u;
+  }
+  // keys before this one take the short way: every row sees them (row 0 sees the fewest) and none carries a bias
+  const int plain_end = g.slopes != nullptr && g.slopes[h] != 0.f ? 0 : row_limit(g, 0);
   __syncthreads();
-  float rmax[2][16];
+  for (int blk = wave; blk < nblk; blk += kWaves) {
 #pragma unroll
-  for (int qb = 0; qb < 2; ++qb)
+    for (int cc = 0; cc < NC; ++cc) kf[cc] = kn[cc];
+    if (blk + kWaves < nblk) fetch(kn, blk + kWaves);
+    const int j0 = jc0 + blk * 32;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) rmax[qb][e] = -kInf;
-  const int per_wave = A.chunk / kWaves;  // a multiple of 32 (the chunk is a multiple of 256)
-  for (int j0 = jc0 + wave * per_wave; j0 < min(jc0 + (wave + 1) * per_wave, jend); j0 += 32) {
-    const int key = j0 + li;  // this lane's key (B operand column, accumulator column)
-    const bool kvalid = key < g.Nk;
-    const T* krow = Kh + (long long)min(key, g.Nk - 1) * g.kv_sn;
-    Frag<T> kf[NC];
-#pragma unroll
-    for (int cc = 0; cc < NC; ++cc) kf[cc] = Elem<T>::load(krow + 16 * cc + 8 * hh);
-#pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
-      if (qb >= nqblk) break;
+    for (int qb = 0; qb < NQB; ++qb) {
       f32x16_t acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int cc = 0; cc < NC; ++cc) acc = Elem<T>::mma(qf[qb][cc], kf[cc], acc);
-      // acc[4 q + r] of lane l: query qb*32 + 8 q + 4 (l/32) + r, key j0 + l%32
+      for (int cc = 0; cc < NC; ++cc) acc = Elem<T>::mma(kf[cc], qf[qb][cc], acc);
+      // acc[4 q + r] of lane l: key j0 + 8 q + 4 (l/32) + r, query qb*32 + l%32
+      if (j0 + 32 <= plain_end) {
+        // no bias, and every row sees the whole block: nothing to select per score
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int i = qb * 32 + 8 * (e >> 2) + 4 * hh + (e & 3);
-        const f32x4_t ri = rowinfo[i];
-        const int lim = __float_as_int(ri[2]), pos = __float_as_int(ri[3]);
-        const float zj = fmaf(ri[1], (float)bias_dist(pos, key), acc[e] * ri[0]);
-        if (kvalid && key < lim) {  // (lim = 0 for rows beyond Nq)
-          A.scores[((long long)bh * g.Nq + i) * A.nks + key] = zj;
-          rmax[qb][e] = fmaxf(rmax[qb][e], zj);
+        for (int e = 0; e < 16; ++e) acc[e] *= cf[qb];
+      } else {
+        const int rel = lim[qb] - j0 - 4 * hh, pos = qb * 32 + li + (g.Nk - g.Nq) - j0 - 4 * hh;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const int k = 8 * (e >> 2) + (e & 3);
+          const float zj = fmaf(yb[qb], (float)max(pos - k, 0), acc[e] * cf[qb]);
+          acc[e] = k < rel ? zj : -kInf;
         }
+      }
+      float m = max16(acc);
+      m = fmaxf(m, __shfl_xor(m, 32));
+      cm[qb] = fmaxf(cm[qb], m);
+      top[qb] = fmaxf(top[qb], from_ordered_bits(rowmax[qb * 32 + li]));  // (an older value only writes more)
+      if (m > top[qb] - 1.0f && lim[qb] > 0) {  // (m = -inf for rows that see none of the block; lim = 0 beyond the last row)
+        if (m > top[qb]) {
+          top[qb] = m;
+          atomicMax(&rowmax[qb * 32 + li], ordered_bits(m));
+        }
+        mask[qb] |= 1u << (blk % kBlocksPerChunk);
+        float* dst = A.scores + ((long long)bh * g.Nq + qb * 32 + li) * A.nks;
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const int j = j0 + 8 * q4 + 4 * hh;
+          if (j < A.nks)  // nks and j are multiples of 4
+            *reinterpret_cast<f32x4_t*>(dst + j) = f32x4_t{acc[4 * q4], acc[4 * q4 + 1], acc[4 * q4 + 2], acc[4 * q4 + 3]};
+        }
+      }
+      if (blk % kBlocksPerChunk + kWaves >= kBlocksPerChunk || blk + kWaves >= nblk) {  // this wave's last block of the chunk
+        if (hh == 0) {
+          wmax[blk / kBlocksPerChunk][wave][qb * 32 + li] = cm[qb];
+          wmask[blk / kBlocksPerChunk][wave][qb * 32 + li] = mask[qb];
+        }
+        cm[qb] = -kInf;
+        mask[qb] = 0u;
       }
     }
   }
-  // a query's maximum over the keys this wave saw: across the 32 lanes of its half wave
-#pragma unroll
-  for (int qb = 0; qb < 2; ++qb) {
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      float v = rmax[qb][e];
-#pragma unroll
-      for (int sft = 16; sft >= 1; sft >>= 1) v = fmaxf(v, __shfl_xor(v, sft));
-      if (li == 0) wmax[wave][qb * 32 + 8 * (e >> 2) + 4 * hh + (e & 3)] = v;
-    }
-  }
   __syncthreads();
-  if (tid < g.Nq) {
-    float mx = wmax[0][tid];
+  for (int e = tid; e < A.chunks_per_wg * NQB * 32; e += kThreads) {
+    const int c = e / (NQB * 32), i = e % (NQB * 32);
+    if (i >= g.Nq || chunk0 + c >= A.nchunks) continue;
+    float mx = wmax[c][0][i];
+    uint32_t mk = wmask[c][0][i];
 #pragma unroll
-    for (int w = 1; w < kWaves; ++w) mx = fmaxf(mx, wmax[w][tid]);
-    A.cmax[((long long)bh * g.Nq + tid) * A.nchunks + blockIdx.x] = mx;
+    for (int w = 1; w < kWaves; ++w) {
+      mx = fmaxf(mx, wmax[c][w][i]);
+      mk |= wmask[c][w][i];
+    }
+    A.cmax[((long long)bh * g.Nq + i) * A.nchunks + chunk0 + c] = pack_cmax(mx, mk);
   }
 }
 
-// Sum of two values over the workgroup; every thread gets the totals.  `buf` holds 2 * 2 * 16
+// Sum of two values over the workgroup; every thread gets the totals.  `buf` holds 2 * 2 * NT / 64
 // floats: calls alternate between its halves (parity), so one barrier per call is enough.
+template <int NT>
 __device__ __forceinline__ float2 decode_block_sum(float a, float b, float* buf, int parity) {
-  constexpr int kW = kDecodeSolveThreads / 64;
+  constexpr int kW = NT / 64;
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) {
     a += __shfl_xor(a, off);
@@ -262,17 +321,30 @@ __device__ __forceinline__ float2 decode_block_sum(float a, float b, float* buf,
   return make_float2(sa, sb);
 }
 
-template <typename T, int D, int AM>
-__global__ __launch_bounds__(kDecodeSolveThreads) void decode_solve_kernel(DecodeArgs A) {
-  constexpr int kW = kDecodeSolveThreads / 64;
-  constexpr int kSlots = kDecodeSolveThreads / D;  // threads with the same feature share out the support
+// One Newton step of sum_j [z_j - tau]_+^r = 1 from the sums F = sum x^r, G = sum x^(r-1); true when tau is final.
+__device__ __forceinline__ bool decode_newton(float F, float G, float r, float& tau) {
+  if (!(G > 0.f)) return true;
+  const float step = (F - 1.0f) / (r * G);  // f = F - 1, f' = -r G; G > 0 while tau < max
+  if (!(step > 0.f)) return true;
+  tau += step;
+  return step <= 1e-6f * fmaxf(1.0f, fabsf(tau));  // what is left is a small multiple of the last step
+}
+
+// NT threads per row.  The work of a typical row (a few chunks read again, a handful of candidates) is a chain of
+// memory round trips and wave-wide sums: up to 64 candidates are one wave's, held in registers, with no barrier
+// after the list is made.  Many rows run with 256 threads (more rows in flight per CU: 48 heads x 64 rows of 32768
+// keys 60 us with 1024), few rows with 1024 (a long support then has the whole workgroup).
+template <typename T, int D, int AM, int NT>
+__global__ __launch_bounds__(NT) void decode_solve_kernel(DecodeArgs A) {
+  constexpr int kW = NT / 64;
+  constexpr int kSlots = NT / D;                   // threads with the same feature share out the support
   __shared__ float2 list[kDecodeListCap];          // (key index bits, z)
   __shared__ float red[2 * 2 * kW];
   __shared__ float wmax[kW];
   __shared__ int count;
   __shared__ float osum[kSlots * D];
   const Geom& g = A.g;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int row = blockIdx.x, i = row % g.Nq, bh = row / g.Nq, b = bh / g.H, h = bh % g.H;
   const int lim = row_limit(g, i);
   const long long o_idx = (long long)b * g.q_sb + (long long)h * g.q_sh + (long long)i * g.q_sn;
@@ -282,75 +354,139 @@ __global__ __launch_bounds__(kDecodeSolveThreads) void decode_solve_kernel(Decod
     return;
   }
   const float* z = A.scores + (long long)row * A.nks;
-  const float* cmax = A.cmax + (long long)row * A.nchunks;
+  const uint32_t* cmax = A.cmax + (long long)row * A.nchunks;
   const float r = 1.0f / (g.alpha - 1.0f);
-  // row maximum from the chunks' maxima
-  float m = -kInf;
-  for (int c = tid; c < A.nchunks; c += kDecodeSolveThreads) m = fmaxf(m, cmax[c]);
+  // lower bound of the row maximum from the chunks' rounded maxima
+  uint32_t first_words = kCmaxNone;  // the words of chunks 0..63: every wave's own copy
+  if (lane < A.nchunks) first_words = cmax[lane];
+  float m = cmax_floor(first_words);
+  for (int c = 64 + tid; c < A.nchunks; c += NT) m = fmaxf(m, cmax_floor(cmax[c]));
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-  if ((tid & 63) == 0) wmax[tid >> 6] = m;
+  if (lane == 0) wmax[wave] = m;
   if (tid == 0) count = 0;
   __syncthreads();
 #pragma unroll
   for (int w = 0; w < kW; ++w) m = fmaxf(m, wmax[w]);
   // keys with a non-zero term at the lowest threshold tau_lo = max - 1 (there the maximum's own term is 1,
-  // so the sum is >= 1 and the root is >= tau_lo); a wave takes a chunk at a time and skips those whose
-  // maximum is out of reach
-  const float tau_lo = m - 1.0f;
-  for (int c = tid >> 6; c < A.nchunks; c += kW) {
-    if (!(cmax[c] > tau_lo)) continue;
-    for (int v = 0; v < A.chunk / 256; ++v) {
-      const int j = c * A.chunk + (v * 64 + (tid & 63)) * 4;
-      if (j >= lim) continue;
-      const f32x4_t zv = *reinterpret_cast<const f32x4_t*>(z + j);  // nks is a multiple of 4: the word is inside the row
+  // so the sum is >= 1 and the root is >= tau_lo), or a few more: the waves take the chunks in reach in turn
+  const float floor_lo = m - 1.0f;
+  int turn = 0;
+  for (int c0 = 0; c0 < A.nchunks; c0 += 64) {
+    const uint32_t word = c0 == 0 ? first_words : (c0 + lane < A.nchunks ? cmax[c0 + lane] : kCmaxNone);
+    unsigned long long hot = __ballot((word & 0xffffu) != 0u && cmax_ceil(word) > floor_lo);
+    while (hot != 0ull) {
+      const int k = __builtin_ctzll(hot);
+      hot &= hot - 1ull;
+      if ((turn++ % kW) != wave) continue;
+      const uint32_t written = (uint32_t)__builtin_amdgcn_readlane((int)word, k);
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        if (j + k < lim && zv[k] > tau_lo) {
-          const int pos = atomicAdd(&count, 1);
-          if (pos < kDecodeListCap) list[pos] = make_float2(__int_as_float(j + k), zv[k]);
+      for (int v = 0; v < kDecodeChunk / 256; ++v) {
+        const int in_chunk = (v * 64 + lane) * 4, j = (c0 + k) * kDecodeChunk + in_chunk;
+        if (j >= lim || ((written >> (in_chunk >> 5)) & 1u) == 0u) continue;
+        const f32x4_t zv = *reinterpret_cast<const f32x4_t*>(z + j);  // nks is a multiple of 4: the word is inside the row
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+          if (j + kk < lim && zv[kk] > floor_lo) {
+            const int pos = atomicAdd(&count, 1);
+            if (pos < kDecodeListCap) list[pos] = make_float2(__int_as_float(j + kk), zv[kk]);
+          }
         }
       }
     }
   }
   __syncthreads();
   const int total = count;
+  const T* Vh = reinterpret_cast<const T*>(A.V) + (long long)b * g.kv_sb + (long long)h * g.kv_sh;
+  auto value = [&](int j, int c) -> float {
+    const long long vi = (long long)j * g.kv_sn + c;
+    if constexpr (sizeof(T) == 2)
+      return __uint_as_float((uint32_t)reinterpret_cast<const uint16_t*>(Vh)[vi] << 16);
+    else
+      return reinterpret_cast<const float*>(Vh)[vi];
+  };
+  if (total <= 64) {
+    if (wave != 0) return;
+    const float2 en = lane < total ? list[lane] : make_float2(0.f, -kInf);
+    float top = en.y;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) top = fmaxf(top, __shfl_xor(top, off));
+    float tau = top - 1.0f;
+    for (int it = 0; it < 96; ++it) {
+      const float x = fmaxf(en.y - tau, 0.f);
+      float F = x > 0.f ? pow_r<AM>(x, r) : 0.f, G = x > 0.f ? pow_rm1<AM>(x, r) : 0.f;
+#pragma unroll
+      for (int off = 32; off >= 1; off >>= 1) {
+        F += __shfl_xor(F, off);
+        G += __shfl_xor(G, off);
+      }
+      if (decode_newton(F, G, r, tau)) break;
+    }
+    if (lane == 0) A.tau[row] = tau;
+    const float x = fmaxf(en.y - tau, 0.f);
+    const float p = x > 0.f ? pow_r<AM>(x, r) : 0.f;
+    unsigned long long sup = __ballot(p > 0.f);
+    float acc[D / 64];
+#pragma unroll
+    for (int t = 0; t < D / 64; ++t) acc[t] = 0.f;
+    while (sup != 0ull) {  // four value rows on their way at a time (a row past the last one has weight zero)
+      float pe[4], ve[4][D / 64];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int k = sup != 0ull ? __builtin_ctzll(sup) : 0;
+        pe[u] = sup != 0ull ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(p), k)) : 0.f;
+        const int j = __builtin_amdgcn_readlane(__float_as_int(en.x), k);
+        sup &= sup - 1ull;  // (0 stays 0)
+#pragma unroll
+        for (int t = 0; t < D / 64; ++t) ve[u][t] = value(j, t * 64 + lane);
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int t = 0; t < D / 64; ++t)
+          if (pe[u] > 0.f) acc[t] = fmaf(pe[u], ve[u][t], acc[t]);
+    }
+#pragma unroll
+    for (int t = 0; t < D / 64; ++t) Elem<T>::store(A.O, o_idx + t * 64 + lane, acc[t]);
+    return;
+  }
   const bool in_lds = total <= kDecodeListCap;
   const int n_items = in_lds ? total : lim;
-  float tau = tau_lo;
+  // item e: its key and score; -inf where the score was not written (beyond reach)
+  auto item = [&](int e) -> float2 {
+    if (in_lds) return list[e];
+    const bool written = ((cmax[e / kDecodeChunk] >> ((e % kDecodeChunk) >> 5)) & 1u) != 0u;
+    return make_float2(__int_as_float(e), written ? z[e] : -kInf);
+  };
+  float top = -kInf;
+  for (int e = tid; e < n_items; e += NT) top = fmaxf(top, item(e).y);
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) top = fmaxf(top, __shfl_xor(top, off));
+  if (lane == 0) wmax[wave] = top;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kW; ++w) top = fmaxf(top, wmax[w]);
+  float tau = top - 1.0f;
   for (int it = 0; it < 96; ++it) {
     float F = 0.f, G = 0.f;
-    for (int e = tid; e < n_items; e += kDecodeSolveThreads) {
-      const float x = (in_lds ? list[e].y : z[e]) - tau;
+    for (int e = tid; e < n_items; e += NT) {
+      const float x = item(e).y - tau;
       if (x > 0.f) {
         F += pow_r<AM>(x, r);
         G += pow_rm1<AM>(x, r);
       }
     }
-    const float2 s = decode_block_sum(F, G, red, it & 1);
-    if (!(s.y > 0.f)) break;
-    const float step = (s.x - 1.0f) / (r * s.y);  // Newton: f = F - 1, f' = -r G; G > 0 while tau < max
-    if (!(step > 0.f)) break;
-    tau += step;
-    if (step <= 1e-6f * fmaxf(1.0f, fabsf(tau))) break;  // what is left is a small multiple of the last step
+    const float2 s = decode_block_sum<NT>(F, G, red, it & 1);
+    if (decode_newton(s.x, s.y, r, tau)) break;
   }
   if (tid == 0) A.tau[row] = tau;
   // O_i = sum_j p_ij v_j
-  const T* Vh = reinterpret_cast<const T*>(A.V) + (long long)b * g.kv_sb + (long long)h * g.kv_sh;
   const int slot = tid / D, c = tid % D;
   float acc = 0.f;
   for (int e = slot; e < n_items; e += kSlots) {
-    const float2 en = in_lds ? list[e] : make_float2(__int_as_float(e), z[e]);
+    const float2 en = item(e);
     const float x = en.y - tau;
-    if (x > 0.f) {
-      const long long vi = (long long)__float_as_int(en.x) * g.kv_sn + c;
-      float v;
-      if constexpr (sizeof(T) == 2)
-        v = __uint_as_float((uint32_t)reinterpret_cast<const uint16_t*>(Vh)[vi] << 16);
-      else
-        v = reinterpret_cast<const float*>(Vh)[vi];
-      acc = fmaf(pow_r<AM>(x, r), v, acc);
-    }
+    if (x > 0.f) acc = fmaf(pow_r<AM>(x, r), value(__float_as_int(en.x), c), acc);
   }
   osum[slot * D + c] = acc;
   __syncthreads();

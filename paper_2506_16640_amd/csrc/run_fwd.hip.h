@@ -70,24 +70,40 @@ bool launch_fwd_sparse_am(const FwdSparseArgs& a, int am, int nblocks, hipStream
   }
 }
 
-template <typename T, int D>
-bool launch_decode(const DecodeArgs& a, int am, hipStream_t st, void* const* ev) {
-  const Geom& g = a.g;
-  const dim3 sgrid((unsigned)a.nchunks, (unsigned)(g.B * g.H));
-  if (g.Nq >= kDecodeMfmaRows)  // more rows than the per-row dot products are worth: matrix cores
-    hipLaunchKernelGGL((decode_scores_mfma_kernel<T, D>), sgrid, dim3(kThreads), 0, st, a);
+template <typename T, int D, int AM>
+bool launch_decode_solve(const DecodeArgs& a, hipStream_t st) {
+  const long long rows = (long long)a.g.B * a.g.H * a.g.Nq;
+  if (rows >= kDecodeManyRows)
+    hipLaunchKernelGGL((decode_solve_kernel<T, D, AM, 256>), dim3((unsigned)rows), dim3(256), 0, st, a);
   else
-    hipLaunchKernelGGL((decode_scores_kernel<T, D>), sgrid, dim3(kThreads), decode_scores_lds(g.Nq, D, sizeof(T)), st, a);
+    hipLaunchKernelGGL((decode_solve_kernel<T, D, AM, 1024>), dim3((unsigned)rows), dim3(1024), 0, st, a);
+  return launch_ok();
+}
+
+template <typename T, int D>
+bool launch_decode(const DecodeArgs& a_in, int am, hipStream_t st, void* const* ev) {
+  DecodeArgs a = a_in;
+  const Geom& g = a.g;
+  const long long heads = (long long)g.B * g.H;
+  if (g.Nq >= (sizeof(T) == 2 ? kDecodeMfmaRows : kDecodeMfmaRowsF32)) {  // more rows than the per-row dot products are worth
+    a.chunks_per_wg = decode_chunks_per_wg(heads, a.nchunks);
+    const dim3 grid((unsigned)((a.nchunks + a.chunks_per_wg - 1) / a.chunks_per_wg), (unsigned)heads);
+    if (g.Nq <= 32)
+      hipLaunchKernelGGL((decode_scores_mfma_kernel<T, D, 1>), grid, dim3(kThreads), 0, st, a);
+    else
+      hipLaunchKernelGGL((decode_scores_mfma_kernel<T, D, 2>), grid, dim3(kThreads), 0, st, a);
+  } else {
+    hipLaunchKernelGGL((decode_scores_kernel<T, D>), dim3((unsigned)a.nchunks, (unsigned)heads), dim3(kThreads),
+                       decode_scores_lds(g.Nq, D, sizeof(T)), st, a);
+  }
   if (!launch_ok()) return false;
   record(ev, ENTMAX_FWD_PHASE_LISTS + 1, st);
-  const dim3 grid((unsigned)(g.B * g.H * g.Nq)), block(kDecodeSolveThreads);
   switch (am) {
-    case 1: hipLaunchKernelGGL((decode_solve_kernel<T, D, 1>), grid, block, 0, st, a); break;
-    case 2: hipLaunchKernelGGL((decode_solve_kernel<T, D, 2>), grid, block, 0, st, a); break;
-    case 3: hipLaunchKernelGGL((decode_solve_kernel<T, D, 3>), grid, block, 0, st, a); break;
-    default: hipLaunchKernelGGL((decode_solve_kernel<T, D, 0>), grid, block, 0, st, a); break;
+    case 1: return launch_decode_solve<T, D, 1>(a, st);
+    case 2: return launch_decode_solve<T, D, 2>(a, st);
+    case 3: return launch_decode_solve<T, D, 3>(a, st);
+    default: return launch_decode_solve<T, D, 0>(a, st);
   }
-  return launch_ok();
 }
 
 }  // namespace
@@ -121,10 +137,10 @@ int run_fwd(const entmax_attn_params* p, const Layout& L, const void* Q, const v
       da.O = O;
       da.tau = tau;
       da.scores = reinterpret_cast<float*>(ws);
-      da.cmax = reinterpret_cast<float*>(ws + L.off_dec_cmax);
+      da.cmax = reinterpret_cast<uint32_t*>(ws + L.off_dec_cmax);
       da.nks = L.dec_nks;
       da.nchunks = L.dec_nchunks;
-      da.chunk = L.dec_chunk;
+      da.chunks_per_wg = 1;
       if (!launch_decode<T, D>(da, alpha_mode(p->alpha), st, ev)) return ENTMAX_ATTN_LAUNCH_FAILED;
     } else {
       record(ev, ENTMAX_FWD_PHASE_PREPARE + 1, st);

@@ -97,3 +97,19 @@ def test_decode_forward_then_backward(use_saved):
     g = gpu_run(data, 1.5, "bf16", use_saved=use_saved)
     r = oracle_run(data, 1.5)
     print(use_saved, compare(g, r, label="decode fwd+bwd"))
+
+
+@pytest.mark.parametrize("nq,nk", [(2, 31), (2, 32), (2, 33), (3, 511), (3, 513), (32, 2049), (33, 2113), (64, 6147)])
+@pytest.mark.parametrize("rising", [False, True])
+def test_decode_scores_left_out(nq, nk, rising):
+    """The matrix-core score kernel writes a row's scores of a 32-key block only where they can matter.  Edges of the
+    blocks, of the 512-key chunks and of the 32-row query blocks; `rising`: every later key scores higher, so every
+    block is above the rows' largest score so far."""
+    data = _case(nq, nk, 64, "bf16", "head", seed=19, B=1, H=2)
+    if rising:
+        data["Q"][...] = np.abs(data["Q"])
+        data["K"][...] = np.linspace(0.05, 0.5, nk)[None, None, :, None]
+        data["Q"], data["K"] = (synth.bf16_round(data[x]) for x in ("Q", "K"))
+    g = gpu_run(data, 1.5, "bf16", bwd=False)
+    r = oracle_run(data, 1.5, bwd=False)
+    print(nq, nk, rising, compare(g, r, bwd=False, label=f"decode blocks {nq}x{nk}"))
