@@ -232,6 +232,7 @@ struct FwdTile {
   static constexpr int kOcc = sizeof(T) == 2 ? (D == 64 ? 3 : 2) : 1;
 };
 
+constexpr int kListHeaderBytes = 32;  // of a list sweep's LDS: overflow flags and votes
 // Keys per LDS tile and workgroups per CU of the list sweeps (fwd_sparse.hip.h, bwd_sparse.hip.h), as measured:
 // at D = 64 four 32-key blocks per tile and three workgroups per CU; at D = 128 the query fragments take twice
 // the registers, and two blocks per tile with four workgroups per CU run a quarter faster (no spills).
@@ -244,18 +245,17 @@ struct ListCfg {
   static constexpr int kDepth = 1;
   // cells per thread that the collecting sweep keeps in LDS (20 bytes each)
   static constexpr int kLdsCells = kOcc == 4 ? 1 : 4;
-  // Per wave, one bit per 32-key block of the head: set by the forward's first sweep where a key of the block can
-  // still be a candidate (fwd_sparse.hip.h), so that the second sweep skips the others; blocks beyond the words'
-  // range are always visited.  LDS is handed out in pieces of 1280 bytes (measured: 53760 bytes per workgroup run
-  // three to a CU, 54080 only two, which costs the sweeps 40 %), so at D = 64 the words take what is left of the
-  // 42nd piece: 30 per wave, 30720 keys.  At D = 128 (four workgroups of 32 pieces) there is room for 128.
-  static constexpr int kFlagWords = (sizeof(T) == 2 && D == 64) ? 30 : 128;
-  // sequences shorter than this do not keep the bits: nearly every block of a wave has some lane that passes
-  // (measured at n = 4096: 97 %), so there is nothing to skip
-  static constexpr int kFlagMinKeys = 16384;
-  // dynamic LDS of a list-sweep kernel: two tile buffers, the overflow flags, the cells, the block bits
-  static constexpr size_t kLdsBytes = 2 * (size_t)kTile * D * sizeof(T) + 16 + (size_t)kLdsCells * kThreads * 20 +
-                                      (size_t)kWaves * kFlagWords * 4;
+  // Per wave, one bit per 32-key block of the head: the blocks that can hold a candidate, so that the forward's second
+  // sweep skips the others (mark_blocks() in fwd_sparse.hip.h); blocks beyond the words' range are always visited.
+  // LDS is handed out in pieces of 1280 bytes (measured: 53760 bytes per workgroup run three to a CU, 54080 only two,
+  // which costs the sweeps 40 %), so at D = 64 the words take what is left of the 42nd piece: 28 per wave, 28672 keys.
+  // At D = 128 (four workgroups of 32 pieces) there is room for 128.
+  static constexpr int kMarkWords = (sizeof(T) == 2 && D == 64) ? 28 : 128;
+  // sequences of at least this length: two query blocks per workgroup (fwd_lists_pair_kernel)
+  static constexpr int kPairMinKeys = 16384;
+  // dynamic LDS of a list-sweep kernel: two tile buffers, flags and votes, the cells, the marks
+  static constexpr size_t kLdsBytes = 2 * (size_t)kTile * D * sizeof(T) + kListHeaderBytes + (size_t)kLdsCells * kThreads * 20 +
+                                      (size_t)kWaves * kMarkWords * 4;
 };
 
 // SPLIT: the workgroup takes one 32-row group (rg_) of the block instead of four, and its four waves share out

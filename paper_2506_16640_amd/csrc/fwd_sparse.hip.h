@@ -6,10 +6,10 @@
 // subset S of the row's scores gives tau_S <= tau, because dropping terms can
 // only lower f(tau) = sum_j [(alpha-1) s_j - tau]_+^r - 1.  So
 //   fwd_lists_kernel (matrix cores, K tiles through LDS, two sweeps)
-//     1. row-max sweep that also keeps the second largest per-cell maximum:
+//     1. row-max sweep that also keeps each lane's largest 32-key blocks:
 //        tau_lb = max(left end of the bracket of App. A eq. (bounds),
-//                     solution of the two-element sub-problem) <= tau;
-//     2. second Q K^T sweep: every key with (alpha-1) s_ij > tau_lb goes on the
+//                     solution of the sub-problem of those blocks' largest scores) <= tau;
+//     2. second Q K^T sweep, over the blocks that can hold a candidate: every key with (alpha-1) s_ij > tau_lb goes on the
 //        row's candidate list (key index + raw score).  Every key of the
 //        support is on that list; nothing else of the row can matter.
 //   fwd_finish_kernel (no matrix work, one lane pair per row)
@@ -119,22 +119,78 @@ struct CellBuf {
   }
 };
 
+// Scores acc of the 32-key block at key j0 (masked where the row does not see the key): appends the cells above the cutoff.
+template <typename C, typename CB>
+__device__ __forceinline__ void append_cells(const C& q, const f32x16_t& acc, int j0, float cut, CB& cb, int& ncell,
+                                             unsigned& n_cand_tiles) {
+  // maxima of the four 4-key groups of the lane, then of the block
+  float gm[4];
+#pragma unroll
+  for (int gq = 0; gq < 4; ++gq) gm[gq] = fmaxf(fmaxf(acc[4 * gq], acc[4 * gq + 1]), fmaxf(acc[4 * gq + 2], acc[4 * gq + 3]));
+  const float lm = fmaxf(fmaxf(gm[0], gm[1]), fmaxf(gm[2], gm[3]));
+  // masked entries are -inf and never exceed the cutoff
+  if (__ballot(lm > cut) == 0ull) return;
+  ++n_cand_tiles;
+#pragma unroll
+  for (int cl = 0; cl < 4; ++cl) {
+    if (gm[cl] > cut) {
+      cb.store(ncell, f32x4_t{acc[4 * cl], acc[4 * cl + 1], acc[4 * cl + 2], acc[4 * cl + 3]}, j0 + q.key_of(4 * cl));
+      ++ncell;
+    }
+  }
+}
+
+// keys of the block at j0 that the lane's row does not see
+template <typename C>
+__device__ __forceinline__ void mask_block(const C& q, f32x16_t& acc, int j0) {
+  const int rel = q.lim - j0;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc[e] = (q.key_of(e) < rel) ? acc[e] : -kInf;
+}
+
+// A cell holds at most four candidates, so there are at least as many candidates as cells.  One pass: the scores
+// above the cutoff go to the list.  Returns how many there are; more than CAP: the block's lists are discarded.
+template <int CAP, typename CB>
+__device__ __forceinline__ int cells_to_list(const CB& cb, int ncell, float cut, uint2* mylist, int& cnt) {
+  int total = 0;
+  for (int k = 0; k < ncell; ++k) {
+    f32x4_t dv;
+    int jc;
+    cb.load(k, dv, jc);
+#pragma unroll
+    for (int rr = 0; rr < 4; ++rr) {
+      if (dv[rr] > cut) {
+        if (cnt < CAP) {
+          mylist[cnt * kListStride] = make_uint2((unsigned)(jc + rr), __float_as_uint(dv[rr]));
+          ++cnt;
+        }
+        ++total;
+      }
+    }
+  }
+  return total;
+}
+
+// candidates are the keys with a * dot > thr: in raw units, dot > cut.  Rounding may move a key that
+// sits on the threshold (probability ~ 0) in or out of the list; the consumers recompute its value.
+// Scale 0 (a = 0): every visible key ties; they all qualify iff thr < 0.
+__device__ __forceinline__ float raw_cut(float a, bool live, float thr) {
+  return !live ? kInf : (a > 0.f ? thr / a : (thr < 0.f ? -3.0e38f : kInf));
+}
+
 // One sweep over the visible key tiles of the block: every key whose shifted score
 // a * dot - thr is positive ends up in the lane's list.  Returns false (workgroup-uniform) if
 // some list overflowed; the sweep is abandoned early in that case.  ovf: three ints of LDS;
-// lds_cells: CellBuf<CAP, LS>::kLdsBytes bytes of LDS.  blockbits: NULL, or this wave's ListCfg::kFlagWords words
+// lds_cells: CellBuf<CAP, LS>::kLdsBytes bytes of LDS.  marks: NULL, or this wave's ListCfg::kMarkWords words
 // of LDS with one bit per 32-key block of the head: a block whose bit is clear holds no candidate of any row of
 // the wave and is not computed (blocks beyond the words' range always are).
 template <typename C, typename T, int D, int CAP, int LS>
 __device__ __forceinline__ bool collect_sweep(const C& q, const Geom& g, const void* K, char* tiles, int* ovf, char* lds_cells,
                                               bool live, float thr, void* cells, uint2* mylist, int& cnt, unsigned& n_qk,
-                                              unsigned& n_cand_tiles, const uint32_t* blockbits = nullptr,
+                                              unsigned& n_cand_tiles, const uint32_t* marks = nullptr,
                                               int strip_no = -1) {
   constexpr int KT = C::KT, NSB = C::NSB;
-  // candidates are the keys with a * dot > thr: in raw units, dot > cut.  Rounding may move a key that
-  // sits on the threshold (probability ~ 0) in or out of the list; the consumers recompute its value.
-  // Scale 0 (a = 0): every visible key ties; they all qualify iff thr < 0.
-  const float cut = !live ? kInf : (q.a > 0.f ? thr / q.a : (thr < 0.f ? -3.0e38f : kInf));
+  const float cut = raw_cut(q.a, live, thr);
   if (q.tid < 3) ovf[q.tid] = 0;
   CellBuf<CAP, LS> cb;
   cb.init(cells, lds_cells, q.tid, strip_no < 0 ? (int)blockIdx.x : strip_no);  // (which of the scratch strips is this workgroup's)
@@ -149,11 +205,11 @@ __device__ __forceinline__ bool collect_sweep(const C& q, const Geom& g, const v
         if (!q.tile_in_wave_window(kt)) return;
         const bool interior = (kt + 1) * KT <= q.wave_lim_min;
         uint32_t act = interior ? ((1u << NSB) - 1u) : q.visible_bits(kt);
-        if (blockbits && (kt + 1) * NSB <= ListCfg<T, D>::kFlagWords * 32) {
+        if (marks && (kt + 1) * NSB <= ListCfg<T, D>::kMarkWords * 32) {
           const int jb = kt * NSB;
-          act &= __builtin_amdgcn_readfirstlane(blockbits[jb >> 5]) >> (jb & 31);
-          if (act == 0u) return;
+          act &= __builtin_amdgcn_readfirstlane(marks[jb >> 5]) >> (jb & 31);
         }
+        if (act == 0u) return;
         f32x16_t acc[NSB];
         if (interior && act == (1u << NSB) - 1u) {
           q.scores_all(tl, acc, kt);
@@ -167,28 +223,8 @@ __device__ __forceinline__ bool collect_sweep(const C& q, const Geom& g, const v
           if (!(act & (1u << sb))) continue;
           int j0 = kt * KT + sb * 32;
           ++n_qk;
-          if (j0 + 32 > q.wave_lim_min) {
-            int rel = q.lim - j0;
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[sb][e] = (q.key_of(e) < rel) ? acc[sb][e] : -kInf;
-          }
-          // maxima of the four 4-key groups of the lane, then of the block
-          float gm[4];
-#pragma unroll
-          for (int gq = 0; gq < 4; ++gq)
-            gm[gq] = fmaxf(fmaxf(acc[sb][4 * gq], acc[sb][4 * gq + 1]), fmaxf(acc[sb][4 * gq + 2], acc[sb][4 * gq + 3]));
-          float lm = fmaxf(fmaxf(gm[0], gm[1]), fmaxf(gm[2], gm[3]));
-          // masked entries are -inf and never exceed the cutoff
-          if (__ballot(lm > cut) == 0ull) continue;
-          ++n_cand_tiles;
-#pragma unroll
-          for (int cl = 0; cl < 4; ++cl) {
-            if (gm[cl] > cut) {
-              cb.store(ncell, f32x4_t{acc[sb][4 * cl], acc[sb][4 * cl + 1], acc[sb][4 * cl + 2], acc[sb][4 * cl + 3]},
-                       j0 + q.key_of(4 * cl));
-              ++ncell;
-            }
-          }
+          if (j0 + 32 > q.wave_lim_min) mask_block(q, acc[sb], j0);
+          append_cells(q, acc[sb], j0, cut, cb, ncell, n_cand_tiles);
         }
         // once per tile: a strip that overflowed (its last cell was overwritten: the lists are discarded)
         if (__ballot(ncell > CAP) != 0ull && q.lane == 0) ovf[kt & 1] = 1;
@@ -198,30 +234,84 @@ __device__ __forceinline__ bool collect_sweep(const C& q, const Geom& g, const v
   // the sweep ended on a barrier: both flags are final
   bool fits = (ovf[0] | ovf[1]) == 0;
   if (fits) {
-    // a cell holds at most four candidates, so there are at least as many candidates as cells.  One pass: the
-    // scores above the cutoff go to the list; a list that would grow beyond CAP raises the third flag, and the
-    // block's lists are then discarded as a whole.
-    int total = 0;
-    for (int k = 0; k < ncell; ++k) {
-      f32x4_t dv;
-      int jc;
-      cb.load(k, dv, jc);
-#pragma unroll
-      for (int rr = 0; rr < 4; ++rr) {
-        if (dv[rr] > cut) {
-          if (cnt < CAP) {
-            mylist[cnt * kListStride] = make_uint2((unsigned)(jc + rr), __float_as_uint(dv[rr]));
-            ++cnt;
-          }
-          ++total;
-        }
-      }
-    }
+    const int total = cells_to_list<CAP>(cb, ncell, cut, mylist, cnt);
     if (total > CAP) ovf[2] = 1;
     __syncthreads();
     fits = ovf[2] == 0;
   }
   return fits;
+}
+
+// The first sweep's memory of where a lane's large scores are: its kTopBlocks largest 32-key blocks by the lane's largest
+// score of each, in descending order.  An entry is that score with the block's number in place of its lowest mantissa bits,
+// so that one v_med3 per place keeps the order (t1 >= t2: the middle one of t1, t2, x is the new t2).
+// It is there for two reasons: the second sweep computes only the blocks that can hold a candidate (bf16, alpha 1.5: 56 % of
+// them at B 4, H 12, n 4096, D 64; 41 % at B 2, H 16, n 8192, D 128; 54 and 34 % do), and the lower bound of the threshold comes
+// from up to twelve scores instead of two (top_blocks_bound()), which keeps more rows of long supports on the lists.  Forward
+// calls before and after: 186 -> 181 us, 663 -> 637 us; B 8, H 12, n 1024: 76 -> 71 us; alpha 1.25, n 4096: 492 -> 437 us.
+// Eight places instead of six: 183, 647 us (registers).  The second sweep by waves on their own, without barriers, straight
+// from global memory or through LDS of their own: 200 to 207 and 830 to 850 us (K no longer shared by four waves).
+constexpr int kTopBlocks = 6;
+struct BlockNumbers {  // how the numbers of a head's blocks are packed
+  uint32_t keep;       // the score's bits that stay
+  float eps;           // a score differs from its entry by less than eps |entry|
+  __device__ __forceinline__ explicit BlockNumbers(int Nk) {
+    const int bits = 32 - __builtin_clz((unsigned)((Nk - 1) >> 5) | 1u);
+    keep = ~((1u << bits) - 1u);
+    eps = __uint_as_float((uint32_t)(127 + bits - 22) << 23);
+  }
+  __device__ __forceinline__ float upper(float t) const { return fmaf(fabsf(t), eps, t); }  // (both increasing in t)
+  __device__ __forceinline__ float lower(float t) const { return fmaf(-fabsf(t), eps, t); }
+};
+struct TopBlocks {
+  float t[kTopBlocks];
+  __device__ __forceinline__ void init() {
+#pragma unroll
+    for (int k = 0; k < kTopBlocks; ++k) t[k] = __uint_as_float(0xff700000u);  // below every entry, names block 0
+  }
+  // (the bounds keep the bits of a masked block's -inf, or of an infinite score, from becoming a NaN)
+  __device__ __forceinline__ void take(float lm, const BlockNumbers& bn, int jb) {
+    const float x = __uint_as_float((__float_as_uint(__builtin_amdgcn_fmed3f(lm, -3.0e38f, 3.0e38f)) & bn.keep) | (uint32_t)jb);
+#pragma unroll
+    for (int k = kTopBlocks - 1; k > 0; --k) t[k] = __builtin_amdgcn_fmed3f(t[k - 1], t[k], x);
+    t[0] = fmaxf(t[0], x);
+  }
+  // the row's second largest block maximum (a little low): a second, distinct score; below -2.9e38: there is none
+  __device__ __forceinline__ float runner_up(const BlockNumbers& bn) const {
+    const float p0 = __shfl_xor(t[0], 32), p1 = __shfl_xor(t[1], 32);
+    return bn.lower(fmaxf(fminf(t[0], p0), fmaxf(t[1], p1)));
+  }
+};
+
+// Marks in the wave's words the 32-key blocks that can hold a candidate of one of its rows: those among the lanes' top
+// blocks whose score may exceed the cutoff.  A block that fell out of a lane's top blocks scored no more than the last of
+// them; where that one may exceed the cutoff as well, every block the wave sees is marked.  (Blocks beyond the words
+// are always computed.)
+template <typename C>
+__device__ __forceinline__ void mark_blocks(const C& q, const TopBlocks& top, const BlockNumbers& bn, float cut,
+                                            uint32_t* words, int nwords) {
+  if (__ballot(bn.upper(top.t[kTopBlocks - 1]) > cut) == 0ull) {
+    for (int w = q.lane; w < nwords; w += 64) words[w] = 0u;
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int k = 0; k < kTopBlocks - 1; ++k) {
+      const bool pass = bn.upper(top.t[k]) > cut;
+      if (__ballot(pass) == 0ull) break;
+      if (pass) {
+        const uint32_t jb = __float_as_uint(top.t[k]) & ~bn.keep;
+        if ((int)(jb >> 5) < nwords) atomicOr(words + (jb >> 5), 1u << (jb & 31));
+      }
+    }
+  } else {
+    int first = 0;
+    if constexpr (C::BIAS) first = q.kt_first_wave * C::NSB;
+    const int last = (q.wave_lim_max + 31) >> 5;
+    for (int w = q.lane; w < nwords; w += 64) {
+      const int f = min(max(first - 32 * w, 0), 32), l = min(max(last - 32 * w, 0), 32);
+      words[w] = (uint32_t)((1ull << l) - 1ull) & ~(uint32_t)((1ull << f) - 1ull);
+    }
+  }
+  __builtin_amdgcn_wave_barrier();
 }
 
 // Lower bound of the threshold from the two-element sub-problem {y1 >= y2} (y = (alpha-1) s) and the left
@@ -251,35 +341,51 @@ __device__ __forceinline__ float two_key_bound(float y1, float y2, float r) {
   return fmaxf(lo, t - 4e-6f * fmaxf(1.0f, fabsf(t)));
 }
 
-// BITS: the kernel for long sequences (Nk >= ListCfg::kFlagMinKeys), which keeps the block bits described below
-template <typename T, int D, int AM, bool BIAS, bool BITS>
+// The same from the up to 2 kTopBlocks scores of the row that its two lanes' top blocks name (distinct keys, each a little
+// low), starting at the bound lo: Newton steps from the left, as above.  A row of many close scores has far fewer keys above
+// this bound than above the two-key one.
+template <int AM>
+__device__ __forceinline__ float top_blocks_bound(const TopBlocks& top, const BlockNumbers& bn, float a, float lo, float r) {
+  float v[kTopBlocks];
+#pragma unroll
+  for (int k = 0; k < kTopBlocks; ++k) v[k] = a * bn.lower(top.t[k]);
+  float t = lo;
+#pragma unroll 1
+  for (int it = 0; it < 4; ++it) {
+    float f = 0.f, fp = 0.f;
+#pragma unroll
+    for (int k = 0; k < kTopBlocks; ++k) {
+      const float x = fmaxf(v[k] - t, 0.f);
+      const float g = x > 0.f ? pow_rm1<AM>(x, r) : 0.f;
+      f = fmaf(g, x, f);
+      fp += g;
+    }
+    f += __shfl_xor(f, 32);
+    fp += __shfl_xor(fp, 32);
+    const bool up = f > 1.0f;  // (then fp > 0)
+    if (__ballot(up) == 0ull) break;
+    if (up) t += (f - 1.0f) / (r * fp);
+  }
+  // (entries of no key are about -3e38: a row whose a is so small that they could count keeps the bound it has)
+  return a > 1.0e-30f ? fmaxf(lo, t - 4e-6f * fmaxf(1.0f, fabsf(t))) : lo;
+}
+
+template <typename T, int D, int AM, bool BIAS>
 __device__ __forceinline__ void fwd_lists_block(const FwdSparseArgs& A, int bh_, int blk_, char* smem, int strip_no = -1) {
   using C = QCtx<T, D, ListCfg<T, D>::kTile, BIAS>;
   constexpr int KT = C::KT, NSB = C::NSB, TB = C::kTileBytes;
   const Geom& g = A.g;
   char* tiles = smem;  // 2 buffers x 1 slot
   int* ovf = reinterpret_cast<int*>(smem + 2 * TB);  // sticky overflow flags: [0], [1] by tile parity, [2] list
-  char* lds_cells = smem + 2 * TB + 16;
+  int* votes = ovf + 4;                              // the waves' votes (see below)
+  char* lds_cells = smem + 2 * TB + kListHeaderBytes;
   using Cfg = ListCfg<T, D>;
-  uint32_t* allbits = reinterpret_cast<uint32_t*>(lds_cells + (size_t)Cfg::kLdsCells * kThreads * 20);
-  // Long sequences: the first sweep notes, per wave, the 32-key blocks in which some lane's largest score comes
-  // within the bracket's width of that lane's running maximum.  The final cutoff is at least (final maximum) - 1/a
-  // in raw units (App. A eq. (bounds), left end), and the running maximum never exceeds the final one: a block
-  // that fails this test for every lane holds no candidate, and the second sweep does not compute it.
-  // At n = 32768 (B 1, H 12) 44 % of the blocks keep their bit against 12 % that hold a candidate: a lane's
-  // running maximum is beaten O(log n) times along the sweep, and a block stays if any of its 64 lanes passes.
-  // Neither the running two-key bound as the cutoff (42 %) nor a first pass over every eighth tile to raise the
-  // running maxima early (44 %) changed that.
-  constexpr bool keep_bits = BITS;
-  if (keep_bits)
-    for (int w = threadIdx.x; w < kWaves * Cfg::kFlagWords; w += kThreads) allbits[w] = 0u;  // (first barrier: the sweep's)
-
-  if (threadIdx.x < kWaves) ovf[threadIdx.x] = 0;  // during the first sweep: the waves' votes (see `votes` below)
+  if (threadIdx.x < kListHeaderBytes / 4) ovf[threadIdx.x] = 0;
 
   C q;
   q.init(g, A.Q, bh_, blk_);
   q.init_window(g);
-  uint32_t* mybits = allbits + q.wave * Cfg::kFlagWords;
+  uint32_t* words = reinterpret_cast<uint32_t*>(lds_cells + (size_t)Cfg::kLdsCells * kThreads * 20) + q.wave * Cfg::kMarkWords;
   const int flag_idx = q.bh * A.nqb + q.qb;
   const long long row_idx = (long long)q.bh * g.Nq + (q.valid ? q.i : 0);
   const bool live = q.valid && q.lim > 0;
@@ -300,21 +406,21 @@ __device__ __forceinline__ void fwd_lists_block(const FwdSparseArgs& A, int bh_,
   unsigned n_vis = 0, n_qk2 = 0, n_cand_tiles = 0;
 
   // ---------------------------------------------- 1. row max and runner-up
-  // m1 >= m2 are the two largest per-cell maxima seen by this lane: two distinct scores of the row
-  float m1 = -kInf, m2 = -kInf;
-  // BITS: the bracket's width in raw units, a little wider than needed (rounding); lanes without a live row never pass
+  float m1 = -kInf;
+  const BlockNumbers bn(g.Nk);
+  TopBlocks top;
+  top.init();
+  // the bracket's width in raw units, a little wider than needed (rounding)
   const float reach = (q.valid && q.lim > 0) ? (q.a > 0.f ? 1.0001f / q.a : 3.0e38f) : -kInf;
   // Dense rows are found out on the first tile: where, for three quarters of a wave's rows, half of the keys of
   // the tile's first block come within the bracket's width of the block's largest score, the lists would overflow anyway (a row of
   // the paper's sparse setting has a handful of such keys).  A block all of whose waves vote so is handed to the
   // tiled kernel after two tiles instead of after a full sweep (a matter of time only: the tiled kernel handles
-  // any row).  votes: one word per wave in the overflow flags' place, which the second sweep zeroes again.
-  int* votes = ovf;
+  // any row).
   int kt_vote = 0;  // the first tile of the sweep
   if constexpr (BIAS) kt_vote = q.kt_first;
   auto max_body = [&](int kt, const char* tl) {
         if (!q.tile_in_wave_window(kt)) return;
-        uint32_t bits = 0u;
         if ((kt + 1) * KT <= q.wave_lim_min) {
           f32x16_t acc[NSB];
           q.scores_all(tl, acc, kt);
@@ -327,9 +433,8 @@ __device__ __forceinline__ void fwd_lists_block(const FwdSparseArgs& A, int bh_,
               for (int e = 0; e < 16; ++e) near += (acc[0][e] + reach > lm) ? 1 : 0;
               if (__popcll(__ballot(near >= 8)) >= 48 && q.lane == 0) votes[q.wave] = 1;
             }
-            m2 = fmaxf(m2, fminf(m1, lm));
             m1 = fmaxf(m1, lm);
-            if (keep_bits && __ballot(lm + reach > m1) != 0ull) bits |= 1u << sb;
+            top.take(lm, bn, kt * NSB + sb);
           }
           n_vis += NSB;
         } else {
@@ -346,13 +451,10 @@ __device__ __forceinline__ void fwd_lists_block(const FwdSparseArgs& A, int bh_,
               for (int e = 0; e < 16; ++e) acc[e] = (q.key_of(e) < rel) ? acc[e] : -kInf;
             }
             float lm = max16(acc);
-            m2 = fmaxf(m2, fminf(m1, lm));
             m1 = fmaxf(m1, lm);
-            if (keep_bits && __ballot(lm + reach > m1) != 0ull) bits |= 1u << sb;
+            top.take(lm, bn, kt * NSB + sb);
           }
         }
-        // (each wave writes only its own words)
-        if (bits != 0u && (kt + 1) * NSB <= Cfg::kFlagWords * 32 && q.lane == 0) mybits[(kt * NSB) >> 5] |= bits << ((kt * NSB) & 31);
       };
   auto all_dense = [&]() { return (votes[0] & votes[1] & votes[2] & votes[3]) != 0; };
   sweep_tiles<C, T, D, 1, 0, ListCfg<T, D>::kDepth>(
@@ -365,24 +467,24 @@ __device__ __forceinline__ void fwd_lists_block(const FwdSparseArgs& A, int bh_,
     if (A.stats && q.lane == 0) atomicAdd(&A.stats[ENTMAX_STAT_FWD_LIST_QK], (unsigned long long)n_vis);
     return;
   }
-  {
-    float p1 = __shfl_xor(m1, 32), p2 = __shfl_xor(m2, 32);
-    float hi1 = fmaxf(m1, p1);
-    m2 = fmaxf(fminf(m1, p1), fmaxf(m2, p2));
-    m1 = hi1;
-  }
+  m1 = fmaxf(m1, __shfl_xor(m1, 32));
+  const float m2 = top.runner_up(bn);
   const float y1 = live ? q.a * m1 : 0.f;
   float lo = y1 - 1.0f;  // App. A eq. (bounds), left end
   float hi = live ? y1 - __builtin_amdgcn_exp2f(-(g.alpha - 1.0f) * __builtin_amdgcn_logf((float)q.lim)) : 0.f;
   // two-element sub-problem {y1, y2}: its threshold is a lower bound of the row's
-  if (live && m2 > -kInf) lo = two_key_bound<AM>(y1, q.a * m2, 1.0f / (g.alpha - 1.0f));
+  if (live && m2 > -2.9e38f) lo = two_key_bound<AM>(y1, q.a * m2, 1.0f / (g.alpha - 1.0f));
+  // (a row of at most three blocks keeps the two-key bound: its lists overflow only where it keeps nearly every key, and
+  // such rows are the tiled kernel's)
+  if (live && q.lim > 96) lo = top_blocks_bound<AM>(top, bn, q.a, lo, 1.0f / (g.alpha - 1.0f));
   lo = fminf(lo, hi);
 
   // ---------------------------------------------- 2. candidate lists at tau_lb
   uint2* mylist = A.cand + list_entry<kCandCap>(q.bh, A.nqb, q.qb, q.wave, q.lane);
   int cnt = 0;
-  const bool fits = collect_sweep<C, T, D, kCandCap, ListCfg<T, D>::kLdsCells>(q, g, A.K, tiles, ovf, lds_cells, live, lo, A.cells, mylist, cnt, n_qk2, n_cand_tiles,
-                                                                                     keep_bits ? mybits : nullptr, strip_no);
+  mark_blocks(q, top, bn, raw_cut(q.a, live, lo), words, min((((q.block_lim + 31) >> 5) + 31) >> 5, Cfg::kMarkWords));
+  const bool fits = collect_sweep<C, T, D, kCandCap, Cfg::kLdsCells>(q, g, A.K, tiles, ovf, lds_cells, live, lo, A.cells, mylist, cnt,
+                                                                     n_qk2, n_cand_tiles, words, strip_no);
   if (!fits) {
     // the tiled kernel takes the block, and with it what the first sweep found out about every row
     if (q.tid == 0) A.dense_flag[flag_idx] = kFlagWithBounds;
@@ -406,7 +508,7 @@ __device__ __forceinline__ void fwd_lists_block(const FwdSparseArgs& A, int bh_,
   }
 }
 
-template <typename T, int D, int AM, bool BIAS, bool BITS>
+template <typename T, int D, int AM, bool BIAS>
 __global__ __launch_bounds__(kThreads, (ListCfg<T, D>::kOcc)) void fwd_lists_kernel(FwdSparseArgs A) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   PairItem it;
@@ -434,12 +536,12 @@ __global__ __launch_bounds__(kThreads, (ListCfg<T, D>::kOcc)) void fwd_lists_ker
     const int blk = part ? it.second : it.first;
     if (blk < 0) break;
     if (part) __syncthreads();
-    fwd_lists_block<T, D, AM, BIAS, BITS>(A, it.bh, blk, smem);
+    fwd_lists_block<T, D, AM, BIAS>(A, it.bh, blk, smem);
   }
 }
 
 // ------------------------------------------------- long sequences: two query blocks per workgroup
-// The same two sweeps as fwd_lists_block<.., BITS = true> for the adjacent blocks 2 sblk and 2 sblk + 1 at once:
+// The same two sweeps as fwd_lists_block for the adjacent blocks 2 sblk and 2 sblk + 1 at once:
 // every wave holds its 32-row group of both blocks (64 query rows), so that a K fragment read from LDS feeds two
 // matrix instructions and a K tile staged through LDS serves 256 rows.  Each block keeps its own lists, flags,
 // bounds and block bits, exactly as if it had run alone.  Used where the launch still fills the chip with half as
@@ -504,11 +606,6 @@ __device__ __forceinline__ void fwd_lists_pair(const FwdSparseArgs& A, int bh_, 
   auto needed = [&](int kt) { return q[0].tile_in_window(kt) || q[1].tile_in_window(kt); };
   // 32-key blocks of tile kt some row of the wave's group of block k sees
   auto visible = [&](int k, int kt) -> uint32_t { return q[k].tile_in_wave_window(kt) ? q[k].visible_bits(kt) : 0u; };
-  auto mask_block = [&](int k, f32x16_t& acc, int j0) {
-    const int rel = q[k].lim - j0;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) acc[e] = (q[k].key_of(e) < rel) ? acc[e] : -kInf;
-  };
   // the K fragments of a 32-key block, shared by both groups
   auto load_k = [&](const char* tl, int sb, Frag<T> (&kf)[NC]) {
 #pragma unroll
@@ -533,7 +630,7 @@ __device__ __forceinline__ void fwd_lists_pair(const FwdSparseArgs& A, int bh_, 
     auto take = [&](int k, f32x16_t& acc, int sb) {
       const int j0 = kt * KT + sb * 32;
       ++n_vis[k];
-      if (j0 + 32 > q[k].wave_lim_min) mask_block(k, acc, j0);
+      if (j0 + 32 > q[k].wave_lim_min) mask_block(q[k], acc, j0);
       const float lm = max16(acc);
       m2[k] = fmaxf(m2[k], fminf(m1[k], lm));
       m1[k] = fmaxf(m1[k], lm);
@@ -597,7 +694,7 @@ __device__ __forceinline__ void fwd_lists_pair(const FwdSparseArgs& A, int bh_, 
   int ncell[2] = {0, 0};
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
-    cut[k] = !live[k] ? kInf : (q[k].a > 0.f ? lo[k] / q[k].a : (lo[k] < 0.f ? -3.0e38f : kInf));
+    cut[k] = raw_cut(q[k].a, live[k], lo[k]);
     cb[k].init(A.cells, lds_cells + k * CellBuf<kCandCap, LS>::kLdsBytes, tid, 2 * (int)blockIdx.x + k);
   }
   sweep_tiles<C, T, D, 1, 0, ListCfg<T, D>::kDepth>(
@@ -630,22 +727,8 @@ __device__ __forceinline__ void fwd_lists_pair(const FwdSparseArgs& A, int bh_, 
             if ((act[k] & (1u << sb)) == 0u) continue;
             f32x16_t& acc = accs[k];
             ++n_qk2[k];
-            if (j0 + 32 > q[k].wave_lim_min) mask_block(k, acc, j0);
-            float gm[4];
-#pragma unroll
-            for (int gq = 0; gq < 4; ++gq)
-              gm[gq] = fmaxf(fmaxf(acc[4 * gq], acc[4 * gq + 1]), fmaxf(acc[4 * gq + 2], acc[4 * gq + 3]));
-            const float lm = fmaxf(fmaxf(gm[0], gm[1]), fmaxf(gm[2], gm[3]));
-            if (__ballot(lm > cut[k]) == 0ull) continue;
-            ++n_cand_tiles[k];
-#pragma unroll
-            for (int cl = 0; cl < 4; ++cl) {
-              if (gm[cl] > cut[k]) {
-                cb[k].store(ncell[k], f32x4_t{acc[4 * cl], acc[4 * cl + 1], acc[4 * cl + 2], acc[4 * cl + 3]},
-                            j0 + q[k].key_of(4 * cl));
-                ++ncell[k];
-              }
-            }
+            if (j0 + 32 > q[k].wave_lim_min) mask_block(q[k], acc, j0);
+            append_cells(q[k], acc, j0, cut[k], cb[k], ncell[k], n_cand_tiles[k]);
           }
         }
 #pragma unroll
@@ -661,22 +744,7 @@ __device__ __forceinline__ void fwd_lists_pair(const FwdSparseArgs& A, int bh_, 
     fits[k] = (ovf[3 * k] | ovf[3 * k + 1]) == 0;
     if (fits[k]) {
       uint2* mylist = A.cand + list_entry<kCandCap>(q[k].bh, A.nqb, q[k].qb, wave, lane);
-      int total = 0;
-      for (int c = 0; c < ncell[k]; ++c) {
-        f32x4_t dv;
-        int jc;
-        cb[k].load(c, dv, jc);
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-          if (dv[rr] > cut[k]) {
-            if (cnt[k] < kCandCap) {
-              mylist[cnt[k] * kListStride] = make_uint2((unsigned)(jc + rr), __float_as_uint(dv[rr]));
-              ++cnt[k];
-            }
-            ++total;
-          }
-        }
-      }
+      const int total = cells_to_list<kCandCap>(cb[k], ncell[k], cut[k], mylist, cnt[k]);
       if (total > kCandCap) ovf[3 * k + 2] = 1;
     }
   }
@@ -724,7 +792,7 @@ __global__ __launch_bounds__(kThreads, (ListCfg<T, D>::kOcc)) void fwd_lists_pai
     if (2 * sblk + 1 < A.nqb)
       fwd_lists_pair<T, D, AM, BIAS>(A, it.bh, sblk, smem);
     else  // a head's odd last block
-      fwd_lists_block<T, D, AM, BIAS, true>(A, it.bh, 2 * sblk, smem, 2 * (int)blockIdx.x);
+      fwd_lists_block<T, D, AM, BIAS>(A, it.bh, 2 * sblk, smem, 2 * (int)blockIdx.x);
   }
 }
 

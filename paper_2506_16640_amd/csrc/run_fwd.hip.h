@@ -35,7 +35,7 @@ bool launch_fwd_sparse(const FwdSparseArgs& a, int nblocks, hipStream_t st, void
   size_t smem = ListCfg<T, D>::kLdsBytes;
   const int nsb = (a.nqb + 1) / 2;
   const long long pair_grid = (long long)a.g.B * a.g.H * ((nsb + 1) / 2);
-  const bool long_seq = a.g.Nk >= ListCfg<T, D>::kFlagMinKeys;
+  const bool long_seq = a.g.Nk >= ListCfg<T, D>::kPairMinKeys;
   bool launched = false;
   if constexpr (sizeof(T) == 2 && D == 64) {  // (the only combination the two-block kernel is built for)
     if (a.force_long || (long_seq && pair_grid >= kPairMinWorkgroups)) {
@@ -48,11 +48,7 @@ bool launch_fwd_sparse(const FwdSparseArgs& a, int nblocks, hipStream_t st, void
     }
   }
   if (a.unpaired) nblocks = a.g.B * a.g.H * a.nqb;
-  if (launched) {
-  } else if (long_seq || a.force_long)
-    hipLaunchKernelGGL((fwd_lists_kernel<T, D, AM, BIAS, true>), dim3((unsigned)nblocks), dim3(kThreads), smem, st, a);
-  else
-    hipLaunchKernelGGL((fwd_lists_kernel<T, D, AM, BIAS, false>), dim3((unsigned)nblocks), dim3(kThreads), smem, st, a);
+  if (!launched) hipLaunchKernelGGL((fwd_lists_kernel<T, D, AM, BIAS>), dim3((unsigned)nblocks), dim3(kThreads), smem, st, a);
   if (!launch_ok()) return false;
   record(ev, ENTMAX_FWD_PHASE_LISTS + 1, st);
   hipLaunchKernelGGL((fwd_finish_kernel<T, D, AM>), dim3((unsigned)(a.g.B * a.g.H * a.nqb + a.ride.workgroups())),
