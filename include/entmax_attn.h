@@ -161,9 +161,10 @@ enum {
  *        pool that runs to the end of the buffer; the size the library asks for holds six entries per row on
  *        average (under half the size of O at D = 64), and a larger buffer gives a larger pool.  A 128-row query
  *        block that finds the pool used up, or has a half row with more than 16 support entries, is marked for
- *        the backward's tiled kernels instead (same results up to rounding; slower).  When the pool runs out,
- *        which blocks are marked depends on the order the workgroups arrive in.  Needs Nk <= 2^22 (as everything).  Opaque; valid only together
- *        with this call's tau and the same params, inputs and saved_bytes.
+ *        the backward's tiled kernels instead (same results up to rounding; slower).  Which blocks are marked
+ *        depends on the inputs and saved_bytes alone: room is counted out in a fixed order, first to the blocks whose
+ *        candidates (at least their supports) fit the backward's lists.  Needs Nk <= 2^22 (as everything).  Opaque;
+ *        valid only together with this call's tau and the same params, inputs and saved_bytes.
  *   saved_bytes: size of `saved` (ignored when saved is NULL); less than entmax_attn_saved_bytes(p) is
  *        refused with WORKSPACE_TOO_SMALL before anything is launched.
  *   workspace: device scratch of at least entmax_attn_workspace_bytes(p, 0)

@@ -40,14 +40,15 @@ constexpr int kBlockNoLists = 2;
 constexpr int kSavedPerRow = 6;
 constexpr int kSavedPoolFloor = kThreads * kBwdCap;
 constexpr int kSavedPoolPad = 4;
-// The pool is cut into up to kSavedSubPools equal parts with a cursor each, and the 32-row groups take their part
-// in turn (group number modulo the number of parts): pieces are handed out by a returning atomic, and atomics on
+// The pool is cut into up to kSavedSubPools equal parts with a cursor each, and the blocks take their part
+// in turn: pieces are handed out to 32-row groups by a returning atomic, and atomics on
 // one address queue up behind each other (one cursor for the 6144 groups of a 4 x 12 x 4096 problem doubled the
 // time of the kernel that fills the pool).  The cursors sit kSavedCursorStride bytes apart so that they do not
-// share a memory channel either.  Every part serves at least kSavedGroupsPerPart groups.
+// share a memory channel either.  Every part serves at least kSavedGroupsPerPart groups (16 blocks, three of them at
+// the most a block can ask for: a part is shared out by whole blocks).
 constexpr int kSavedSubPools = 64;
 constexpr int kSavedCursorStride = 4352;
-constexpr int kSavedGroupsPerPart = 16;
+constexpr int kSavedGroupsPerPart = 64;
 inline int saved_pool_parts(long long groups) {
   int n = 1;
   while (n < kSavedSubPools && groups / (2 * n) >= kSavedGroupsPerPart) n *= 2;

@@ -30,14 +30,15 @@ struct FwdArgs {
   unsigned long long* stats;
   int nqb;         // query blocks per head
   int mask_words;  // uint32 words of one wave's tile mask
-  const int* dense_flag;  // NULL: run every block; else [B*H*nqb], run only the blocks whose flag is set
+  const int* dense_flag;  // NULL: run every block; else [B*H*nqb], run only the blocks whose flag is above zero
   const int* dense_count; // with dense_flag: the number of set flags, then the first kSplitMaxBlocks flagged blocks'
                           // numbers bh * nqb + qb in any order (decides how the blocks are shared out, see fwd_kernel)
   const float2* bounds;   // with dense_flag: [B*H*Nq]; for a block whose flag is kFlagWithBounds the list kernel left
                           // (lower bound of the threshold, (alpha-1) x largest score) of every row here
 };
 
-// values of a block's flag in dense_flag: left to the tiled kernel without / with the rows' bounds
+// values of a block's flag in dense_flag: left to the tiled kernel without / with the rows' bounds (not above zero:
+// finished from its lists, see FwdSparseArgs::dense_flag)
 constexpr int kFlagDense = 1;
 constexpr int kFlagWithBounds = 2;
 
@@ -609,7 +610,7 @@ __global__ __launch_bounds__(kThreads, (FwdTile<T, D>::kOcc)) void fwd_kernel(Fw
   for (int part = 0; part < 2; ++part) {
     const int blk = part ? it.second : it.first;
     if (blk < 0) break;
-    if (A.dense_flag && __builtin_amdgcn_readfirstlane(A.dense_flag[it.bh * A.nqb + blk]) == 0) continue;
+    if (A.dense_flag && __builtin_amdgcn_readfirstlane(A.dense_flag[it.bh * A.nqb + blk]) <= 0) continue;
     __syncthreads();
     fwd_block<T, D, AM, BIAS, false>(A, it.bh, blk, 0, smem);
   }

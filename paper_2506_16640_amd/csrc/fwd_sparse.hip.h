@@ -51,7 +51,7 @@ struct FwdSparseArgs {
                     // every 32-row group takes one contiguous piece (lane after lane, entry after entry)
   char* pool_cursor;       // with list: the pool's parts each have a 64-bit cursor (entries handed out so far, zeroed
                            // by the list kernel), kSavedCursorStride bytes apart
-  int pool_parts;          // with list: parts the pool is cut into (a power of two)
+  int pool_shift;          // with list: the pool is cut into 1 << pool_shift parts
   long long pool_part_cap; // with list: entries a part holds
   int* slcnt;       // with list: [B*H*Nq][2] per half row: (place of its first entry in the pool) << 5 | entries
   int* bwd_flag;    // with list: [B*H*nqb] not 0: the backward cannot take its list path for this block
@@ -61,8 +61,10 @@ struct FwdSparseArgs {
   void* cells;      // sweep scratch: one CellBuf<kCandCap> per workgroup of the list sweep's grid
   int* lcnt;        // [B*H*Nq][2] list lengths
   float2* bounds;   // [B*H*Nq] (tau_lb, right end of the bracket)
-  int* dense_flag;  // [B*H*nqb] 1: block left to the tiled kernel; behind them: how many are set (zeroed by the
-                    // list kernel, counted by the finish kernel), then the first kSplitMaxBlocks flagged blocks' numbers
+  int* dense_flag;  // [B*H*nqb] above zero: block left to the tiled kernel (kFlagDense, kFlagWithBounds), else lists
+                    // were made: minus what the block asks of the pool (pool_want()).  Behind them: how many
+                    // are left to the tiled kernel (zeroed by the list kernel, counted by the finish kernel), then the
+                    // first kSplitMaxBlocks of these blocks' numbers
   unsigned long long* stats;
   int nqb;
   int force_long;      // run the long-sequence kernels whatever the sizes (params.path = 2: test aid)
@@ -178,12 +180,27 @@ __device__ __forceinline__ float raw_cut(float a, bool live, float thr) {
   return !live ? kInf : (a > 0.f ? thr / a : (thr < 0.f ? -3.0e38f : kInf));
 }
 
+// What a block asks of the `saved` pool, before its supports are known: a half row's support is part of its candidate
+// list, and more than kBwdCap entries of one half row send the block to the backward's tiled kernels.  So: the sum of
+// min(candidates, kBwdCap) in the low 16 bits (256 half rows: at most 4096), and above them how many of the block's four
+// row groups hold a half row with more candidates than that -- where none does, the block's lists are sure to be used.
+// word: LDS, zero before; complete after the workgroup's next barrier.
+__device__ __forceinline__ void pool_want(int* word, int cnt, int lane) {
+  const int c = min(cnt, kBwdCap);
+  int sum = 0;
+#pragma unroll
+  for (int k = 0; k < 5; ++k) sum += (int)__popcll(__ballot(((c >> k) & 1) != 0)) << k;
+  const int longer = __ballot(cnt > kBwdCap) != 0ull ? 1 << 16 : 0;
+  if (lane == 0) atomicAdd(word, sum | longer);
+}
+static_assert(kBwdCap < 32 && kThreads * kBwdCap < (1 << 16), "five bits a half row, 16 a block");
+
 // One sweep over the visible key tiles of the block: every key whose shifted score
 // a * dot - thr is positive ends up in the lane's list.  Returns false (workgroup-uniform) if
 // some list overflowed; the sweep is abandoned early in that case.  ovf: three ints of LDS;
 // lds_cells: CellBuf<CAP, LS>::kLdsBytes bytes of LDS.  marks: NULL, or this wave's ListCfg::kMarkWords words
 // of LDS with one bit per 32-key block of the head: a block whose bit is clear holds no candidate of any row of
-// the wave and is not computed (blocks beyond the words' range always are).
+// the wave and is not computed (blocks beyond the words' range always are).  With the forward's lists (CAP = kCandCap), ovf[3] is a word for pool_want().
 template <typename C, typename T, int D, int CAP, int LS>
 __device__ __forceinline__ bool collect_sweep(const C& q, const Geom& g, const void* K, char* tiles, int* ovf, char* lds_cells,
                                               bool live, float thr, void* cells, uint2* mylist, int& cnt, unsigned& n_qk,
@@ -236,6 +253,7 @@ __device__ __forceinline__ bool collect_sweep(const C& q, const Geom& g, const v
   if (fits) {
     const int total = cells_to_list<CAP>(cb, ncell, cut, mylist, cnt);
     if (total > CAP) ovf[2] = 1;
+    if constexpr (CAP == kCandCap) pool_want(ovf + 3, cnt, q.lane);
     __syncthreads();
     fits = ovf[2] == 0;
   }
@@ -376,7 +394,7 @@ __device__ __forceinline__ void fwd_lists_block(const FwdSparseArgs& A, int bh_,
   constexpr int KT = C::KT, NSB = C::NSB, TB = C::kTileBytes;
   const Geom& g = A.g;
   char* tiles = smem;  // 2 buffers x 1 slot
-  int* ovf = reinterpret_cast<int*>(smem + 2 * TB);  // sticky overflow flags: [0], [1] by tile parity, [2] list
+  int* ovf = reinterpret_cast<int*>(smem + 2 * TB);  // sticky overflow flags: [0], [1] by tile parity, [2] list; [3] pool_want()
   int* votes = ovf + 4;                              // the waves' votes (see below)
   char* lds_cells = smem + 2 * TB + kListHeaderBytes;
   using Cfg = ListCfg<T, D>;
@@ -490,7 +508,7 @@ __device__ __forceinline__ void fwd_lists_block(const FwdSparseArgs& A, int bh_,
     if (q.tid == 0) A.dense_flag[flag_idx] = kFlagWithBounds;
     if (q.valid && q.hh == 0) A.bounds[row_idx] = make_float2(lo, y1);
   } else {
-    if (q.tid == 0) A.dense_flag[flag_idx] = 0;
+    if (q.tid == 0) A.dense_flag[flag_idx] = -ovf[3];
     if (q.valid) {
       A.lcnt[row_idx * 2 + q.hh] = cnt;
       if (q.hh == 0) A.bounds[row_idx] = make_float2(lo, hi);
@@ -523,7 +541,7 @@ __global__ __launch_bounds__(kThreads, (ListCfg<T, D>::kOcc)) void fwd_lists_ker
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     A.dense_flag[A.g.B * A.g.H * A.nqb] = 0;
   }
-  if (blockIdx.x == 0 && A.pool_cursor && (int)threadIdx.x < A.pool_parts)
+  if (blockIdx.x == 0 && A.pool_cursor && (int)threadIdx.x < (1 << A.pool_shift))
     *reinterpret_cast<unsigned long long*>(A.pool_cursor + (size_t)threadIdx.x * kSavedCursorStride) = 0ull;
   if (A.kcount) {
     // this workgroup's share of its head's per-key counters starts at zero for the finish kernel
@@ -564,11 +582,11 @@ __device__ __forceinline__ void fwd_lists_pair(const FwdSparseArgs& A, int bh_, 
   constexpr uint32_t kAll = (1u << NSB) - 1u;
   const Geom& g = A.g;
   char* tiles = smem;
-  int* ovf = reinterpret_cast<int*>(smem + 2 * TB);  // [2 blocks][3], see collect_sweep
+  int* ovf = reinterpret_cast<int*>(smem + 2 * TB);  // [2 blocks][3], see collect_sweep; [6], [7]: the blocks' pool_want()
   char* lds_cells = smem + 2 * TB + 32;
   uint32_t* allbits = reinterpret_cast<uint32_t*>(lds_cells + 2 * (size_t)LS * kThreads * 20);  // [2][kWaves][W]
   for (int w = threadIdx.x; w < 2 * kWaves * W; w += kThreads) allbits[w] = 0u;
-  if (threadIdx.x < 6) ovf[threadIdx.x] = 0;  // (first barrier: init_window's or the first sweep's)
+  if (threadIdx.x < 8) ovf[threadIdx.x] = 0;  // (first barrier: init_window's or the first sweep's)
 
   C q[2];
 #pragma unroll
@@ -746,13 +764,14 @@ __device__ __forceinline__ void fwd_lists_pair(const FwdSparseArgs& A, int bh_, 
       uint2* mylist = A.cand + list_entry<kCandCap>(q[k].bh, A.nqb, q[k].qb, wave, lane);
       const int total = cells_to_list<kCandCap>(cb[k], ncell[k], cut[k], mylist, cnt[k]);
       if (total > kCandCap) ovf[3 * k + 2] = 1;
+      pool_want(ovf + 6 + k, cnt[k], lane);
     }
   }
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < 2; ++k) {
     fits[k] = fits[k] && ovf[3 * k + 2] == 0;
-    if (tid == 0) A.dense_flag[flag_idx[k]] = fits[k] ? 0 : 1;
+    if (tid == 0) A.dense_flag[flag_idx[k]] = fits[k] ? -ovf[6 + k] : kFlagDense;
     if (fits[k] && q[k].valid) {
       A.lcnt[row_idx[k] * 2 + q[k].hh] = cnt[k];
       if (q[k].hh == 0) A.bounds[row_idx[k]] = make_float2(lo[k], hi[k]);
@@ -776,7 +795,7 @@ __global__ __launch_bounds__(kThreads, (ListCfg<T, D>::kOcc)) void fwd_lists_pai
   const int nsb = (A.nqb + 1) >> 1;  // pairs of adjacent blocks per head
   const PairItem it = pair_item(nsb);
   if (blockIdx.x == 0 && threadIdx.x == 0) A.dense_flag[A.g.B * A.g.H * A.nqb] = 0;
-  if (blockIdx.x == 0 && A.pool_cursor && (int)threadIdx.x < A.pool_parts)
+  if (blockIdx.x == 0 && A.pool_cursor && (int)threadIdx.x < (1 << A.pool_shift))
     *reinterpret_cast<unsigned long long*>(A.pool_cursor + (size_t)threadIdx.x * kSavedCursorStride) = 0ull;
   if (A.kcount) {
     // this workgroup's share of its head's per-key counters starts at zero for the finish kernel
@@ -893,7 +912,16 @@ __global__ __launch_bounds__(kThreads) void fwd_finish_kernel(FwdSparseArgs A) {
   RowLane rl;
   rl.init(g, A.nqb);
   // (the flag is tested further down: every load that does not depend on another is issued first)
-  const int block_dense = A.dense_flag[rl.bh * A.nqb + rl.qb];
+  const int blk = rl.bh * A.nqb + rl.qb;
+  const int block_word = A.dense_flag[blk];
+  // the blocks that share this one's part of the pool: block b of run r (a run: as many blocks as parts) is in part
+  // (b + r) modulo the parts, so that a part's blocks are at all places of their heads; lane l looks at run l first
+  const int my_run = blk >> A.pool_shift, pool_mask = (1 << A.pool_shift) - 1, part = (blk + my_run) & pool_mask;
+  auto part_word = [&](int run) -> int {
+    const long long other = ((long long)run << A.pool_shift) + ((part - run) & pool_mask);
+    return other < (long long)g.B * g.H * A.nqb ? A.dense_flag[other] : 0;
+  };
+  const int first_part_word = A.list ? part_word(threadIdx.x & 63) : 0;
   constexpr int DH = D / 2;
   const float r = 1.0f / (g.alpha - 1.0f);
   const long long row_idx = (long long)rl.bh * g.Nq + (rl.valid ? rl.i : 0);
@@ -916,23 +944,39 @@ __global__ __launch_bounds__(kThreads) void fwd_finish_kernel(FwdSparseArgs A) {
   uint2 early[kEarly];
 #pragma unroll
   for (int e = 0; e < kEarly; ++e) early[e] = mylist[e * kListStride];
-  if (block_dense != 0) {  // the tiled kernel owns this block, and so do the backward's tiled kernels
-    if (A.list && threadIdx.x == 0) A.bwd_flag[rl.bh * A.nqb + rl.qb] = kBlockNoLists;
+  if (block_word > 0) {  // the tiled kernel owns this block, and so do the backward's tiled kernels
+    if (A.list && threadIdx.x == 0) A.bwd_flag[blk] = kBlockNoLists;
     if (threadIdx.x == 0) {
       int* count = A.dense_flag + g.B * g.H * A.nqb;
       const int slot = atomicAdd(count, 1);
-      if (slot < kSplitMaxBlocks) count[1 + slot] = rl.bh * A.nqb + rl.qb;
+      if (slot < kSplitMaxBlocks) count[1 + slot] = blk;
     }
     return;
   }
-  // The 32-row group's piece of the pool, sized before the supports are known: a half row's support is part of
-  // its candidate list, and a half row with more than kBwdCap support entries sends the block to the backward's
-  // tiled kernels anyway.  One returning atomic per wave, in flight together with the first list entries.
+  // The 32-row group's piece of the pool, sized before the supports are known (see pool_want()).  Whether a block gets
+  // one is settled by the blocks' wants alone: the blocks that share its part of the pool are counted in turn, first those whose
+  // lists are sure to be used, then those whose supports may turn out too long for the backward, and it does while
+  // the part holds what has been counted.  So the outputs do not depend on the order in which the workgroups run, and
+  // blocks that the backward cannot use take no room from blocks that are sure to be used.  (By arrival, B 3, H 12, n 3081
+  // with per-query scales kept 115 to 117 blocks on the backward's lists, dQ differing by 1.3e-3 between calls; so it
+  // keeps the same 159.  The kernel itself: 44.1 -> 44.4 us at B 4, H 12, n 4096, D 64.)  Where in the part a group's piece lies is
+  // without effect and left to a returning atomic.
   uint2* suplist = nullptr;
   int sup_off = 0;
   bool pool_full = false;
   if (A.list) {
     const int lane = threadIdx.x & 63;
+    const bool my_long = (-block_word >> 16) != 0;
+    auto counted_before = [&](int w, int run) -> int {  // entries of a block that is counted before this one
+      const bool is_long = (-w >> 16) != 0;
+      return w < 0 && (my_long ? !is_long || run < my_run : !is_long && run < my_run) ? -w & 0xffff : 0;
+    };
+    int ahead = counted_before(first_part_word, lane);
+    for (int r0 = 64; r0 <= (g.B * g.H * A.nqb - 1) >> A.pool_shift; r0 += 64)  // (parts of more than 64 blocks)
+      ahead += counted_before(part_word(r0 + lane), r0 + lane);
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) ahead += __shfl_xor(ahead, off);
+    pool_full = (long long)ahead + (-block_word & 0xffff) > A.pool_part_cap;
     const int want = min(cnt, kBwdCap);
     int incl = want;  // inclusive running sum over the lanes
 #pragma unroll
@@ -941,15 +985,12 @@ __global__ __launch_bounds__(kThreads) void fwd_finish_kernel(FwdSparseArgs A) {
       if (lane >= sft) incl += up;
     }
     const int total = __builtin_amdgcn_readlane(incl, 63);
-    // the groups take the pool's parts in turn
-    const int part = (int)(((unsigned)blockIdx.x * kWaves + (threadIdx.x >> 6)) & (unsigned)(A.pool_parts - 1));
     unsigned long long base = 0ull;
-    if (lane == 0 && total > 0)
+    if (lane == 0 && total > 0 && !pool_full)
       base = atomicAdd(reinterpret_cast<unsigned long long*>(A.pool_cursor + (size_t)part * kSavedCursorStride),
                        (unsigned long long)total);
     base = ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(base >> 32)) << 32) |
            (unsigned)__builtin_amdgcn_readfirstlane((int)base);
-    pool_full = total > 0 && base + (unsigned long long)total > (unsigned long long)A.pool_part_cap;
     sup_off = pool_full ? 0 : (int)(part * A.pool_part_cap + (long long)base) + incl - want;
     if (!pool_full) suplist = A.list + sup_off;
   }
@@ -1064,8 +1105,8 @@ __global__ __launch_bounds__(kThreads) void fwd_finish_kernel(FwdSparseArgs A) {
   if (A.list) {
     // a support longer than the backward's lists hold, or no room left in the pool, sends the block to the
     // backward's tiled kernels
-    const int any_long = __syncthreads_or((scnt > kBwdCap || pool_full) ? 1 : 0);
-    if (threadIdx.x == 0) A.bwd_flag[rl.bh * A.nqb + rl.qb] = any_long ? kBlockListsUnused : 0;
+    const int any_long = __syncthreads_or(scnt > kBwdCap ? 1 : 0);
+    if (threadIdx.x == 0) A.bwd_flag[blk] = pool_full ? kBlockNoLists : (any_long ? kBlockListsUnused : 0);
   }
   if (A.stats) {
     unsigned sup = n_support, cands = (unsigned)cnt;

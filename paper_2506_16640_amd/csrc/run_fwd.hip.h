@@ -166,8 +166,9 @@ int run_fwd(const entmax_attn_params* p, const Layout& L, const void* Q, const v
     // with a `saved` buffer the rows' supports are listed for the backward
     sa.list = saved ? reinterpret_cast<uint2*>(saved + L.sv_pool) : nullptr;
     sa.pool_cursor = saved ? saved + L.sv_cursor : nullptr;
-    sa.pool_parts = saved_pool_parts((long long)p->B * p->H * L.nqg);
-    sa.pool_part_cap = saved ? saved_pool_entries(L, saved_bytes) / sa.pool_parts : 0;
+    const int parts = saved_pool_parts((long long)p->B * p->H * L.nqg);  // (a power of two)
+    sa.pool_shift = __builtin_ctz((unsigned)parts);
+    sa.pool_part_cap = saved ? saved_pool_entries(L, saved_bytes) / parts : 0;
     sa.slcnt = saved ? reinterpret_cast<int*>(saved + L.sv_lcnt) : nullptr;
     sa.bwd_flag = saved ? reinterpret_cast<int*>(saved + L.sv_flags) : nullptr;
     sa.kcount = saved ? reinterpret_cast<int*>(saved + L.sv_kcount) : nullptr;

@@ -34,7 +34,7 @@ __device__ __forceinline__ void transpose_perm_part(const TransposeJobs& jobs, i
   if (head_flag && head_flag[bh] == 0) return;  // no consumer for this head's copy
   if (block_flag) {
     int any = 0;
-    for (int k = tid; k < nqb; k += kThreads) any |= block_flag[bh * nqb + k];
+    for (int k = tid; k < nqb; k += kThreads) any |= block_flag[bh * nqb + k] > 0 ? 1 : 0;
     if (__syncthreads_or(any) == 0) return;
   }
   const TransposeJob& jb = jobs.job[bz];
