@@ -179,7 +179,8 @@ __global__ __launch_bounds__(kThreads) void decode_scores_kernel(DecodeArgs A) {
 // What bounds it is reading K once; the fp32 scores of 64 rows would be twice the bytes of K.  So a row's scores of a
 // block are written only if the largest of them is above the row's largest score so far less one, whatever wave of
 // the workgroup found that: a key at or below (largest score) - 1 has probability zero (App. A, lower end of the
-// bracket).  Which blocks of a chunk were written is noted beside the chunk's maximum (pack_cmax).
+// bracket).  Which blocks of a chunk were written is noted beside the chunk's maximum (pack_cmax).  The two lanes of a row
+// each write half of a block's scores: the first one decides for both (the row's largest score may change under their reads).
 // Measured: 48 heads, 64 rows, 32768 keys, D 64: 156 us with every score written, 57 us so (two blocks on their way instead of one: the same); 128 heads, 5 rows, 6007
 // keys, D 128: 41 us with per-row dot products (5 us a row at 201 MB of K), 32 us so, which is 6.1 TB/s on K.
 template <typename T, int D, int NQB>
@@ -256,8 +257,11 @@ __global__ __launch_bounds__(kThreads) void decode_scores_mfma_kernel(DecodeArgs
       float m = max16(acc);
       m = fmaxf(m, __shfl_xor(m, 32));
       cm[qb] = fmaxf(cm[qb], m);
-      top[qb] = fmaxf(top[qb], from_ordered_bits(rowmax[qb * 32 + li]));  // (an older value only writes more)
-      if (m > top[qb] - 1.0f && lim[qb] > 0) {  // (m = -inf for rows that see none of the block; lim = 0 beyond the last row)
+      // (an older value only writes more)
+      top[qb] = fmaxf(top[qb], from_ordered_bits(__hip_atomic_load(&rowmax[qb * 32 + li], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)));
+      // (m = -inf for rows that see none of the block; lim = 0 beyond the last row)
+      const uint32_t rows = (uint32_t)__ballot(m > top[qb] - 1.0f && lim[qb] > 0);  // as lanes 0 to 31 see it
+      if ((rows >> li) & 1u) {
         if (m > top[qb]) {
           top[qb] = m;
           atomicMax(&rowmax[qb * 32 + li], ordered_bits(m));

@@ -113,3 +113,34 @@ def test_decode_scores_left_out(nq, nk, rising):
     g = gpu_run(data, 1.5, "bf16", bwd=False)
     r = oracle_run(data, 1.5, bwd=False)
     print(nq, nk, rising, compare(g, r, bwd=False, label=f"decode blocks {nq}x{nk}"))
+
+
+@pytest.mark.parametrize("B,H,nq,nk,d,dtype", [
+    (2, 192, 2, 2081, 64, "bf16"),   # 768 rows, four chunks to a workgroup and a last workgroup of one
+    (4, 64, 5, 2300, 128, "bf16"),   # two chunks to a workgroup, 256 threads a row in the solve
+    (1, 384, 33, 2112, 64, "bf16"),  # two 32-row query blocks, four chunks to a workgroup
+    (1, 12, 64, 4133, 128, "bf16"),  # the same in wide heads, one chunk to a workgroup
+    (2, 128, 16, 1100, 64, "fp32"),  # fp32 from 16 rows on
+    (1, 3, 40, 2600, 128, "fp32"),
+])
+def test_decode_left_out_scores_are_never_read(B, H, nq, nk, d, dtype):
+    """The workspace is full of large scores before the call: an unwritten score that is read would be the row's
+    largest.  The rows' largest scores rise along most of the keys, so that a row's lanes and the waves of a workgroup
+    keep raising the row's limit while others test against it."""
+    import torch
+    from paper_2506_16640_amd import binding
+    from tests.parity_util import to_dev
+    data = _case(nq, nk, d, dtype, "head", seed=23, B=B, H=H)
+    ramp = np.linspace(0.2, 1.0, nk, dtype=np.float32)[None, None, :, None]
+    data["K"][...] = synth.bf16_round(data["K"] * ramp)
+    q, k, v = (to_dev(data[x], dtype) for x in ("Q", "K", "V"))
+    beta, gamma = (torch.from_numpy(data[x]).float().cuda() for x in ("beta", "gamma"))
+    kw = dict(alpha=1.5, beta=beta, gamma=gamma, delta=data["delta"])
+    ws = torch.empty(binding.workspace_bytes(binding.make_params(q, k, 1.5, data["delta"], True, beta, 0), 0), dtype=torch.uint8,
+                     device="cuda")
+    r = oracle_run(data, 1.5, bwd=False)
+    for _ in range(3):
+        ws.view(torch.float32).fill_(1e30)
+        o, tau = binding.entmax_attn_fwd(q, k, v, workspace=ws, **kw)
+        g = {"O": o.float().cpu().numpy().astype(np.float64), "tau": tau.cpu().numpy().astype(np.float64)}
+        print(nq, nk, compare(g, r, bwd=False, label=f"decode poisoned {nq}x{nk} d{d} {dtype}"))
