@@ -415,8 +415,9 @@ __global__ __launch_bounds__(NT) void decode_solve_kernel(DecodeArgs A) {
     float top = en.y;
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) top = fmaxf(top, __shfl_xor(top, off));
-    float tau = top - 1.0f;
-    for (int it = 0; it < 96; ++it) {
+    // (no candidate at all: the largest score, which is then m exactly, is infinite or so large that one less is the same number)
+    float tau = (total > 0 ? top : m) - 1.0f;
+    for (int it = 0; total > 0 && it < 96; ++it) {
       const float x = fmaxf(en.y - tau, 0.f);
       float F = x > 0.f ? pow_r<AM>(x, r) : 0.f, G = x > 0.f ? pow_rm1<AM>(x, r) : 0.f;
 #pragma unroll
@@ -427,7 +428,7 @@ __global__ __launch_bounds__(NT) void decode_solve_kernel(DecodeArgs A) {
       if (decode_newton(F, G, r, tau)) break;
     }
     if (lane == 0) A.tau[row] = tau;
-    const float x = fmaxf(en.y - tau, 0.f);
+    const float x = lane < total ? fmaxf(en.y - tau, 0.f) : 0.f;
     const float p = x > 0.f ? pow_r<AM>(x, r) : 0.f;
     unsigned long long sup = __ballot(p > 0.f);
     float acc[D / 64];

@@ -144,3 +144,21 @@ def test_decode_left_out_scores_are_never_read(B, H, nq, nk, d, dtype):
         o, tau = binding.entmax_attn_fwd(q, k, v, workspace=ws, **kw)
         g = {"O": o.float().cpu().numpy().astype(np.float64), "tau": tau.cpu().numpy().astype(np.float64)}
         print(nq, nk, compare(g, r, bwd=False, label=f"decode poisoned {nq}x{nk} d{d} {dtype}"))
+
+
+@pytest.mark.parametrize("nq", [1, 3])
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("ties", [1, 100])
+def test_decode_scores_too_large_for_a_unit_step(nq, dtype, ties):
+    """(alpha-1) s = 2^26 for the largest keys: one less is the same fp32 number, no key lies above it, and the
+    threshold is the largest score itself, to fp32 (2^-24 of it off the threshold in exact arithmetic).  With a score
+    beyond fp32 it is infinite."""
+    data = _case(nq, 700, 64, dtype, "none", seed=29, B=1, H=2)
+    data["Q"][...], data["K"][...] = 0.0, 0.0
+    data["Q"][..., 0] = 2.0 ** 12
+    data["K"][:, :, 50:50 + ties, 0] = 2.0 ** 18
+    g = gpu_run(data, 1.5, dtype, bwd=False)
+    r = oracle_run(data, 1.5, bwd=False)
+    assert np.abs(g["tau"] / r["tau"] - 1.0).max() <= 2.0 ** -24, (g["tau"], r["tau"])
+    data["Q"][..., 0], data["K"][:, :, 50:50 + ties, 0] = 2.0 ** 100, 2.0 ** 100
+    assert np.all(gpu_run(data, 1.5, dtype, bwd=False)["tau"] == np.inf)
