@@ -81,7 +81,7 @@ inline int decode_chunks_per_wg(long long heads, int nchunks) {
   while (n > 1 && heads * ((nchunks + n - 1) / n) < 768) n /= 2;
   return n;
 }
-constexpr int kDecodeManyRows = 512;  // from this many query rows on the solve kernel runs with 256 threads a row
+constexpr int kDecodeManyRows = 513;  // from this many query rows on the solve kernel runs with 512 threads a row, not 1024
 inline bool decode_shape(int Nq, int Nk) {
   return Nq <= kDecodeRows || (Nq <= kDecodeRowsLong && (long long)Nk >= (long long)kDecodeLongRatio * Nq);
 }

@@ -336,15 +336,17 @@ __device__ __forceinline__ bool decode_newton(float F, float G, float r, float& 
 
 // NT threads per row.  The work of a typical row (a few chunks read again, a handful of candidates) is a chain of
 // memory round trips and wave-wide sums: up to 64 candidates are one wave's, held in registers, with no barrier
-// after the list is made.  Many rows run with 256 threads (more rows in flight per CU: 48 heads x 64 rows of 32768
-// keys 60 us with 1024), few rows with 1024 (a long support then has the whole workgroup).
+// after the list is made.  Many rows run with 512 threads each, so that twice as many are in flight (48 heads x 64 rows of
+// 32768 keys, this kernel: 60 us with 1024).  256 would leave long supports half of the chip's waves, since LDS holds four
+// rows to a CU (48 heads x 64 rows of 8192 keys, delta = 0, gamma = -1/2, whole call: 908 against 1971 us; 676 with the
+// value rows of four keys requested together; 849 with 1024 threads and one value row at a time).
 template <typename T, int D, int AM, int NT>
 __global__ __launch_bounds__(NT) void decode_solve_kernel(DecodeArgs A) {
   constexpr int kW = NT / 64;
   constexpr int kSlots = NT / D;                   // threads with the same feature share out the support
   __shared__ float2 list[kDecodeListCap];          // (key index bits, z)
   __shared__ float red[2 * 2 * kW];
-  __shared__ float wmax[kW];
+  __shared__ float wmax[kW], wtop[kW];
   __shared__ int count;
   __shared__ float osum[kSlots * D];
   const Geom& g = A.g;
@@ -357,7 +359,7 @@ __global__ __launch_bounds__(NT) void decode_solve_kernel(DecodeArgs A) {
     if (tid == 0) A.tau[row] = 0.f;
     return;
   }
-  const float* z = A.scores + (long long)row * A.nks;
+  float* z = A.scores + (long long)row * A.nks;
   const uint32_t* cmax = A.cmax + (long long)row * A.nchunks;
   const float r = 1.0f / (g.alpha - 1.0f);
   // lower bound of the row maximum from the chunks' rounded maxima
@@ -375,32 +377,48 @@ __global__ __launch_bounds__(NT) void decode_solve_kernel(DecodeArgs A) {
   // keys with a non-zero term at the lowest threshold tau_lo = max - 1 (there the maximum's own term is 1,
   // so the sum is >= 1 and the root is >= tau_lo), or a few more: the waves take the chunks in reach in turn
   const float floor_lo = m - 1.0f;
-  int turn = 0;
-  for (int c0 = 0; c0 < A.nchunks; c0 += 64) {
-    const uint32_t word = c0 == 0 ? first_words : (c0 + lane < A.nchunks ? cmax[c0 + lane] : kCmaxNone);
-    unsigned long long hot = __ballot((word & 0xffffu) != 0u && cmax_ceil(word) > floor_lo);
-    while (hot != 0ull) {
-      const int k = __builtin_ctzll(hot);
-      hot &= hot - 1ull;
-      if ((turn++ % kW) != wave) continue;
-      const uint32_t written = (uint32_t)__builtin_amdgcn_readlane((int)word, k);
+  // body(first key + 4 * lane, in the chunk; chunk; its word) for the chunks whose word is `wanted`, twice 256 keys each
+  auto each_chunk = [&](auto wanted, auto body) {
+    int turn = 0;
+    for (int c0 = 0; c0 < A.nchunks; c0 += 64) {
+      const uint32_t word = c0 == 0 ? first_words : (c0 + lane < A.nchunks ? cmax[c0 + lane] : kCmaxNone);
+      unsigned long long hot = __ballot(c0 + lane < A.nchunks && wanted(word));
+      while (hot != 0ull) {
+        const int k = __builtin_ctzll(hot);
+        hot &= hot - 1ull;
+        if ((turn++ % kW) != wave) continue;
+        const uint32_t written = (uint32_t)__builtin_amdgcn_readlane((int)word, k);
 #pragma unroll
-      for (int v = 0; v < kDecodeChunk / 256; ++v) {
-        const int in_chunk = (v * 64 + lane) * 4, j = (c0 + k) * kDecodeChunk + in_chunk;
-        if (j >= lim || ((written >> (in_chunk >> 5)) & 1u) == 0u) continue;
-        const f32x4_t zv = *reinterpret_cast<const f32x4_t*>(z + j);  // nks is a multiple of 4: the word is inside the row
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-          if (j + kk < lim && zv[kk] > floor_lo) {
-            const int pos = atomicAdd(&count, 1);
-            if (pos < kDecodeListCap) list[pos] = make_float2(__int_as_float(j + kk), zv[kk]);
-          }
+        for (int v = 0; v < kDecodeChunk / 256; ++v) {
+          const int in_chunk = (v * 64 + lane) * 4;
+          body((c0 + k) * kDecodeChunk + in_chunk, ((written >> (in_chunk >> 5)) & 1u) != 0u);
         }
       }
     }
-  }
+  };
+  float top = -kInf;  // the largest score itself
+  each_chunk([&](uint32_t word) { return (word & 0xffffu) != 0u && cmax_ceil(word) > floor_lo; },
+             [&](int j, bool written) {
+               if (j >= lim || !written) return;
+               const f32x4_t zv = *reinterpret_cast<const f32x4_t*>(z + j);  // nks is a multiple of 4: the word is inside the row
+#pragma unroll
+               for (int kk = 0; kk < 4; ++kk) {
+                 if (j + kk < lim && zv[kk] > floor_lo) {
+                   top = fmaxf(top, zv[kk]);
+                   const int pos = atomicAdd(&count, 1);
+                   if (pos < kDecodeListCap) list[pos] = make_float2(__int_as_float(j + kk), zv[kk]);
+                 }
+               }
+             });
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) top = fmaxf(top, __shfl_xor(top, off));
+  if (lane == 0) wtop[wave] = top;
   __syncthreads();
   const int total = count;
+#pragma unroll
+  for (int w = 0; w < kW; ++w) top = fmaxf(top, wtop[w]);
+  // (no candidate at all: the largest score, which is then m exactly, is infinite or so large that one less is the same number)
+  float tau = (total > 0 ? top : m) - 1.0f;
   const T* Vh = reinterpret_cast<const T*>(A.V) + (long long)b * g.kv_sb + (long long)h * g.kv_sh;
   auto value = [&](int j, int c) -> float {
     const long long vi = (long long)j * g.kv_sn + c;
@@ -412,11 +430,6 @@ __global__ __launch_bounds__(NT) void decode_solve_kernel(DecodeArgs A) {
   if (total <= 64) {
     if (wave != 0) return;
     const float2 en = lane < total ? list[lane] : make_float2(0.f, -kInf);
-    float top = en.y;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) top = fmaxf(top, __shfl_xor(top, off));
-    // (no candidate at all: the largest score, which is then m exactly, is infinite or so large that one less is the same number)
-    float tau = (total > 0 ? top : m) - 1.0f;
     for (int it = 0; total > 0 && it < 96; ++it) {
       const float x = fmaxf(en.y - tau, 0.f);
       float F = x > 0.f ? pow_r<AM>(x, r) : 0.f, G = x > 0.f ? pow_rm1<AM>(x, r) : 0.f;
@@ -455,44 +468,47 @@ __global__ __launch_bounds__(NT) void decode_solve_kernel(DecodeArgs A) {
     for (int t = 0; t < D / 64; ++t) Elem<T>::store(A.O, o_idx + t * 64 + lane, acc[t]);
     return;
   }
-  const bool in_lds = total <= kDecodeListCap;
-  const int n_items = in_lds ? total : lim;
-  // item e: its key and score; -inf where the score was not written (beyond reach)
-  auto item = [&](int e) -> float2 {
-    if (in_lds) return list[e];
-    const bool written = ((cmax[e / kDecodeChunk] >> ((e % kDecodeChunk) >> 5)) & 1u) != 0u;
-    return make_float2(__int_as_float(e), written ? z[e] : -kInf);
-  };
-  float top = -kInf;
-  for (int e = tid; e < n_items; e += NT) top = fmaxf(top, item(e).y);
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) top = fmaxf(top, __shfl_xor(top, off));
-  if (lane == 0) wmax[wave] = top;
-  __syncthreads();
-#pragma unroll
-  for (int w = 0; w < kW; ++w) top = fmaxf(top, wmax[w]);
-  float tau = top - 1.0f;
-  for (int it = 0; it < 96; ++it) {
-    float F = 0.f, G = 0.f;
-    for (int e = tid; e < n_items; e += NT) {
-      const float x = item(e).y - tau;
-      if (x > 0.f) {
-        F += pow_r<AM>(x, r);
-        G += pow_rm1<AM>(x, r);
-      }
-    }
-    const float2 s = decode_block_sum<NT>(F, G, red, it & 1);
-    if (decode_newton(s.x, s.y, r, tau)) break;
-  }
-  if (tid == 0) A.tau[row] = tau;
-  // O_i = sum_j p_ij v_j
+  // tau, then the thread's share of O_i = sum_j p_ij v_j over n items; B items' scores and value rows are requested at a
+  // time, the sum runs in their order
   const int slot = tid / D, c = tid % D;
   float acc = 0.f;
-  for (int e = slot; e < n_items; e += kSlots) {
-    const float2 en = item(e);
-    const float x = en.y - tau;
-    if (x > 0.f) acc = fmaf(pow_r<AM>(x, r), value(__float_as_int(en.x), c), acc);
+  auto solve = [&](auto key_of, auto score_of, int n, auto b_tag) {
+    constexpr int B = decltype(b_tag)::value;
+    for (int it = 0; it < 96; ++it) {
+      float F = 0.f, G = 0.f;
+      for (int e = tid; e < n; e += NT) {
+        const float x = score_of(e) - tau;
+        if (x > 0.f) {
+          F += pow_r<AM>(x, r);
+          G += pow_rm1<AM>(x, r);
+        }
+      }
+      const float2 s = decode_block_sum<NT>(F, G, red, it & 1);
+      if (decode_newton(s.x, s.y, r, tau)) break;
+    }
+    for (int e0 = slot; e0 < n; e0 += B * kSlots) {
+      float x[B], v[B];
+#pragma unroll
+      for (int u = 0; u < B; ++u) x[u] = e0 + u * kSlots < n ? score_of(e0 + u * kSlots) - tau : 0.f;
+#pragma unroll
+      for (int u = 0; u < B; ++u) v[u] = x[u] > 0.f ? value(key_of(e0 + u * kSlots), c) : 0.f;
+#pragma unroll
+      for (int u = 0; u < B; ++u)
+        if (x[u] > 0.f) acc = fmaf(pow_r<AM>(x[u], r), v[u], acc);
+    }
+  };
+  if (total <= kDecodeListCap) {
+    solve([&](int e) { return __float_as_int(list[e].x); }, [&](int e) { return list[e].y; }, total, std::integral_constant<int, 1>());
+  } else {
+    // the row itself is read again and again: the scores that were not written become -inf once and for all
+    each_chunk([&](uint32_t word) { return (word & 0xffffu) != 0xffffu; },
+               [&](int j, bool written) {
+                 if (j < A.nks && !written) *reinterpret_cast<f32x4_t*>(z + j) = f32x4_t{-kInf, -kInf, -kInf, -kInf};
+               });
+    __syncthreads();
+    solve([](int e) { return e; }, [&](int e) { return z[e]; }, lim, std::integral_constant<int, 4>());
   }
+  if (tid == 0) A.tau[row] = tau;
   osum[slot * D + c] = acc;
   __syncthreads();
   if (tid < D) {

@@ -70,7 +70,7 @@ template <typename T, int D, int AM>
 bool launch_decode_solve(const DecodeArgs& a, hipStream_t st) {
   const long long rows = (long long)a.g.B * a.g.H * a.g.Nq;
   if (rows >= kDecodeManyRows)
-    hipLaunchKernelGGL((decode_solve_kernel<T, D, AM, 256>), dim3((unsigned)rows), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((decode_solve_kernel<T, D, AM, 512>), dim3((unsigned)rows), dim3(512), 0, st, a);
   else
     hipLaunchKernelGGL((decode_solve_kernel<T, D, AM, 1024>), dim3((unsigned)rows), dim3(1024), 0, st, a);
   return launch_ok();

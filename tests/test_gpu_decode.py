@@ -127,23 +127,46 @@ def test_decode_left_out_scores_are_never_read(B, H, nq, nk, d, dtype):
     """The workspace is full of large scores before the call: an unwritten score that is read would be the row's
     largest.  The rows' largest scores rise along most of the keys, so that a row's lanes and the waves of a workgroup
     keep raising the row's limit while others test against it."""
-    import torch
-    from paper_2506_16640_amd import binding
-    from tests.parity_util import to_dev
     data = _case(nq, nk, d, dtype, "head", seed=23, B=B, H=H)
     ramp = np.linspace(0.2, 1.0, nk, dtype=np.float32)[None, None, :, None]
     data["K"][...] = synth.bf16_round(data["K"] * ramp)
+    _compare_on_a_poisoned_workspace(data, 1.5, dtype, f"decode poisoned {nq}x{nk} d{d} {dtype}")
+
+
+def _compare_on_a_poisoned_workspace(data, alpha, dtype, label):
+    import torch
+    from paper_2506_16640_amd import binding
+    from tests.parity_util import to_dev
     q, k, v = (to_dev(data[x], dtype) for x in ("Q", "K", "V"))
-    beta, gamma = (torch.from_numpy(data[x]).float().cuda() for x in ("beta", "gamma"))
-    kw = dict(alpha=1.5, beta=beta, gamma=gamma, delta=data["delta"])
-    ws = torch.empty(binding.workspace_bytes(binding.make_params(q, k, 1.5, data["delta"], True, beta, 0), 0), dtype=torch.uint8,
+    beta, gamma = (None if data[x] is None else torch.from_numpy(data[x]).float().cuda() for x in ("beta", "gamma"))
+    kw = dict(alpha=alpha, beta=beta, gamma=gamma, delta=data["delta"])
+    ws = torch.empty(binding.workspace_bytes(binding.make_params(q, k, alpha, data["delta"], True, beta, 0), 0), dtype=torch.uint8,
                      device="cuda")
-    r = oracle_run(data, 1.5, bwd=False)
+    r = oracle_run(data, alpha, bwd=False)
     for _ in range(3):
         ws.view(torch.float32).fill_(1e30)
         o, tau = binding.entmax_attn_fwd(q, k, v, workspace=ws, **kw)
         g = {"O": o.float().cpu().numpy().astype(np.float64), "tau": tau.cpu().numpy().astype(np.float64)}
-        print(nq, nk, compare(g, r, bwd=False, label=f"decode poisoned {nq}x{nk} d{d} {dtype}"))
+        print(label, compare(g, r, bwd=False, label=label))
+    return r
+
+
+@pytest.mark.parametrize("nq,B,H", [(3, 1, 2), (5, 4, 26)])  # 6 rows (1024 threads each), 520 rows (512 threads)
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("near,alpha", [(60, 1.5), (300, 1.25), (1500, 2.0), (3800, 1.5), (5000, 1.5), (5000, 1.25), (5000, 1.7)])
+def test_decode_long_lists(near, alpha, nq, B, H, d):
+    """`near` keys with scores close together, the others far below and falling along the sequence, so that most of
+    their blocks are not written: one wave's rows, lists in LDS, and rows of more than 4096 candidates, which are read
+    again where they stand with the unwritten scores left out."""
+    nk = 6200
+    data = _case(nq, nk, d, "bf16", "none", seed=31, B=B, H=H)
+    data["Q"] *= 0.25
+    data["Q"][..., 0] = 4.0
+    data["K"][:, :, :near, 0] = 0.0
+    data["K"][:, :, near:, 0] = np.linspace(-24.0, -400.0, nk - near, dtype=np.float32) * (d / 64) ** 0.5
+    data["Q"], data["K"] = (synth.bf16_round(data[x]) for x in ("Q", "K"))
+    r = _compare_on_a_poisoned_workspace(data, alpha, "bf16", f"decode long lists {near} a{alpha} {nq}x{B}x{H} d{d}")
+    assert r["support"].max() <= near
 
 
 @pytest.mark.parametrize("nq", [1, 3])
