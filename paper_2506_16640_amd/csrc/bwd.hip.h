@@ -39,6 +39,8 @@ struct BwdArgs {
   const int* head_flag;  // NULL: every head, whole; else [B*H]: 0 skip the head, 1 only its flagged query blocks,
                          // 2 the whole head
   const int* block_flag; // with head_flag: [B*H*nqb] the query blocks the list path left over
+  uint16_t* dk_rest;     // 16-bit outputs, with head_flag: [B*H][npad_k][D] the low halves of the fp32 dK, dV of heads whose
+  uint16_t* dv_rest;     // flag is 1 (dK and dV take the high halves): bwd_keys_kernel adds its share to the whole sums
   int nqb, nkb, nqg, mask_words;
   int xcd_room;  // workgroups of the kernel being launched that one XCD holds at a time (see bwd_tiled_item)
   // whether query block qb of head bh is this path's (call only for heads whose flag is not 0)
@@ -467,6 +469,30 @@ __device__ __forceinline__ void bwd_dkv_block(const BwdArgs& A, int bh_, int blk
 
   // dk/dv[mm][4g + r] of lane l belongs to key jw0 + 8g + 4*(l/32) + r, feature 32 mm + l%32
   const float inv_am1 = 1.0f / am1;
+  if constexpr (sizeof(T) == 2) {
+    // The list path's share of a mixed head comes on top: the partial sums stay in fp32, and the total is rounded once
+    if (A.head_flag && __builtin_amdgcn_readfirstlane(A.head_flag[bh]) == 1) {
+      auto split = [](void* hi, long long at, uint16_t* lo, float v) {
+        reinterpret_cast<uint16_t*>(hi)[at] = (uint16_t)(__float_as_uint(v) >> 16);
+        *lo = (uint16_t)__float_as_uint(v);
+      };
+#pragma unroll
+      for (int mm = 0; mm < NM; ++mm) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const int row = jw0 + 8 * (e >> 2) + 4 * hh + (e & 3);
+          if (row < g.Nk) {
+            const long long idx = kv_base + (long long)row * g.kv_sn + mm * 32 + li;
+            const long long rest = ((long long)bh * g.npad_k + row) * D + mm * 32 + li;
+            split(A.dK, idx, A.dk_rest + rest, dk[mm][e] * inv_am1);
+            split(A.dV, idx, A.dv_rest + rest, dv[mm][e]);
+          }
+        }
+      }
+      if (A.stats && lane == 0) atomicAdd(&A.stats[ENTMAX_STAT_BWD_DKV_TILES], (unsigned long long)n_tiles);
+      return;
+    }
+  }
 #pragma unroll
   for (int mm = 0; mm < NM; ++mm) {
 #pragma unroll

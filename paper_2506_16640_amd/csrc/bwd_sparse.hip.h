@@ -21,7 +21,7 @@
 // A 128-row query block in which some half row holds more than kBwdCap support entries is flagged and
 // left to the tiled kernels of bwd.hip.h, which then run on the flagged blocks of that head only: dQ and the
 // row scalars of a block come from one path or the other, and dK, dV of such a head are the tiled kernels'
-// sums over the flagged blocks plus the key kernel's sums over the listed entries of the others.
+// sums over the flagged blocks (kept in fp32 until then) plus the key kernel's sums over the listed entries of the others.
 #pragma once
 #include "bwd.hip.h"
 #include "fwd_sparse.hip.h"
@@ -65,6 +65,8 @@ struct BwdSparseArgs {
   float* dbeta;        // per-head scale gradients, reduced by extra workgroups of the keys launch
   float* dgamma;       //   (scale_heads = 0: not here)
   int scale_heads;     // H for per-head scale parameters, else 0
+  const uint16_t* dk_rest;  // 16-bit outputs: low halves of the tiled kernels' share of a mixed head, see BwdArgs
+  const uint16_t* dv_rest;
   unsigned long long* stats;
   int nqb;
   TransposeRide ride;  // operand copies for the tiled kernels, as extra workgroups of the row launch
@@ -426,6 +428,30 @@ static __global__ __launch_bounds__(kOffsThreads) void key_offsets_kernel(BwdSpa
 // of the arrival order.  Keys whose segment holds more than kSortedKeyEntries (= 8) entries are served
 // by the first kLongKeyBlocks workgroups of the same launch (bwd_long_keys_part), which run alongside
 // the others; scale_heads more workgroups reduce dscale to d beta, d gamma.
+// A mixed head's sums as the tiled kernels left them: fp32, or the high halves of fp32 in the output and the low ones in `rest`.
+template <typename T>
+__device__ __forceinline__ float load_partial(const void* out, long long at, const uint16_t* rest) {
+  if constexpr (sizeof(T) == 2)
+    return __uint_as_float(((uint32_t)reinterpret_cast<const uint16_t*>(out)[at] << 16) | *rest);
+  else
+    return reinterpret_cast<const float*>(out)[at];
+}
+template <typename T>
+__device__ __forceinline__ void load_partial_row(const T* row, const uint16_t* rest, int n, float* out) {
+  load_row_f32<T>(row, n, out);
+  if constexpr (sizeof(T) == 2) {
+#pragma unroll
+    for (int c8 = 0; c8 < n / 8; ++c8) {
+      const u32x4_t w = *reinterpret_cast<const u32x4_t*>(rest + 8 * c8);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        out[8 * c8 + 2 * k] = __uint_as_float(__float_as_uint(out[8 * c8 + 2 * k]) | (w[k] & 0xffffu));
+        out[8 * c8 + 2 * k + 1] = __uint_as_float(__float_as_uint(out[8 * c8 + 2 * k + 1]) | (w[k] >> 16));
+      }
+    }
+  }
+}
+
 constexpr int kLongKeyBlocks = 1024;
 constexpr int kKeysPerBlock = kThreads / kSortedKeyEntries;  // 32
 
@@ -521,9 +547,10 @@ __global__ __launch_bounds__(kThreads) void bwd_keys_kernel(BwdSparseArgs A) {
   if (on) {
     const long long o = (long long)b * g.kv_sb + (long long)h * g.kv_sh + (long long)j * g.kv_sn + k * DL;
     if (hflag == kHeadMixed) {  // the tiled kernels wrote the flagged blocks' share: add it
+      const long long rest = ((long long)bh * g.npad_k + j) * D + k * DL;
       float ev[DL], ek[DL];
-      load_row_f32<T>(reinterpret_cast<const T*>(A.dV) + o, DL, ev);
-      load_row_f32<T>(reinterpret_cast<const T*>(A.dK) + o, DL, ek);
+      load_partial_row<T>(reinterpret_cast<const T*>(A.dV) + o, A.dv_rest + rest, DL, ev);
+      load_partial_row<T>(reinterpret_cast<const T*>(A.dK) + o, A.dk_rest + rest, DL, ek);
 #pragma unroll
       for (int t = 0; t < DL; ++t) {
         dv[t] += ev[t];
@@ -621,8 +648,9 @@ __device__ __forceinline__ void bwd_long_keys_part(const BwdSparseArgs& A, int v
 #pragma unroll
   for (int t = 0; t < PER; ++t) {
     if (mixed) {  // the tiled kernels wrote the flagged blocks' share: add it
-      av[t] += Elem<T>::load_one(A.dV, o + lane + 64 * t);
-      ak[t] += Elem<T>::load_one(A.dK, o + lane + 64 * t);
+      const long long rest = ((long long)bh * g.npad_k + j) * D + lane + 64 * t;
+      av[t] += load_partial<T>(A.dV, o + lane + 64 * t, A.dv_rest + rest);
+      ak[t] += load_partial<T>(A.dK, o + lane + 64 * t, A.dk_rest + rest);
     }
     Elem<T>::store(A.dV, o + lane + 64 * t, av[t]);
     Elem<T>::store(A.dK, o + lane + 64 * t, ak[t]);

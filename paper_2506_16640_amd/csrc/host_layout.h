@@ -25,7 +25,7 @@ struct Layout {
   long long q_sb, q_sh, q_sn, kv_sb, kv_sh, kv_sn;
   // workspace offsets
   size_t off_vt, off_cand, off_flcnt, off_bounds, off_flags, off_fcells, off_kt, off_qt, off_dot, off_mu, off_crow, off_dscale, off_mask, off_jlist, off_lcnt,
-      off_kcount, off_koffs, off_kcursor, off_csc_i, off_csc_pw, off_hflag, off_longkeys, off_bcells, off_fknorm, off_bknorm, sv_cursor, sv_lcnt,
+      off_kcount, off_koffs, off_kcursor, off_csc_i, off_csc_pw, off_hflag, off_longkeys, off_bcells, off_fknorm, off_bknorm, off_dk_rest, off_dv_rest, sv_cursor, sv_lcnt,
       sv_flags, sv_knorm, sv_kcount, sv_pool, total_saved, total_fwd, total_bwd;
   size_t off_dec_cmax;  // decode kernels: score rows at offset 0, then the chunk maxima
   int dec_nks, dec_nchunks, dec_chunk;
@@ -168,6 +168,15 @@ inline Layout make_layout(const entmax_attn_params* p) {
   o += align_up(list_groups * cell_bytes_per_workgroup(kBwdCap));
   L.off_bknorm = o;
   o += align_up(bh * sizeof(float));
+  // 16-bit outputs: the low halves of a mixed head's partial dK and dV, written when the copy of K^T and the support
+  // lists have been read.  They take these regions' place; only where the keys outnumber the queries so far that dV's do
+  // not fit the lists' place have they one of their own.
+  L.off_dk_rest = L.off_kt;
+  L.off_dv_rest = L.off_jlist;
+  if (L.esize == 2 && kt_bytes > list_bytes) {
+    L.off_dv_rest = o;
+    o += kt_bytes;
+  }
   L.total_bwd = o;
   return L;
 }

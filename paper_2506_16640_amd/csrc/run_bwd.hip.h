@@ -122,6 +122,8 @@ int run_bwd(const entmax_attn_params* p, const Layout& L, const void* Q, const v
       sa.long_keys = reinterpret_cast<int*>(ws + L.off_longkeys);
       sa.stats = reinterpret_cast<unsigned long long*>(stats);
       sa.nqb = L.nqb;
+      sa.dk_rest = reinterpret_cast<uint16_t*>(ws + L.off_dk_rest);
+      sa.dv_rest = reinterpret_cast<uint16_t*>(ws + L.off_dv_rest);
       sa.dbeta = dbeta;
       sa.dgamma = dgamma;
       sa.scale_heads = p->scale_layout == 1 ? H : 0;
@@ -171,6 +173,8 @@ int run_bwd(const entmax_attn_params* p, const Layout& L, const void* Q, const v
     a.stats = reinterpret_cast<unsigned long long*>(stats);
     a.head_flag = hf;
     a.block_flag = lists ? sa.block_flag : nullptr;
+    a.dk_rest = reinterpret_cast<uint16_t*>(ws + L.off_dk_rest);
+    a.dv_rest = reinterpret_cast<uint16_t*>(ws + L.off_dv_rest);
     a.nqb = L.nqb;
     a.nkb = L.nkb;
     a.nqg = L.nqg;

@@ -64,6 +64,12 @@ static void check_valid(const entmax_attn_params& p) {
   CHECK(L.off_bounds - L.off_flcnt >= bh * (size_t)p.Nq * 2 * sizeof(int));
   CHECK(L.off_flags - L.off_bounds >= bh * (size_t)p.Nq * 2 * sizeof(float));
   CHECK(L.off_longkeys - L.off_hflag >= (bh * (size_t)L.nqb + 2 * bh) * sizeof(int));
+  if (p.dtype == ENTMAX_ATTN_BF16) {  // the low halves of partial dK, dV: in the place of K^T, of the lists or behind everything
+    const size_t need = bh * (size_t)L.npad_k * p.D * sizeof(uint16_t);
+    CHECK(L.off_dk_rest == L.off_kt && L.off_qt - L.off_kt >= need && L.off_dv_rest % kAlign == 0);
+    CHECK(L.off_dv_rest == L.off_jlist ? L.off_lcnt - L.off_jlist >= need
+                                       : L.off_dv_rest >= L.off_bknorm + bh * sizeof(float) && L.total_bwd - L.off_dv_rest >= need);
+  }
   if (decode_shape(p.Nq, p.Nk)) {
     CHECK(L.off_dec_cmax >= bh * (size_t)p.Nq * (size_t)p.Nk * sizeof(float));
     CHECK(L.total_fwd >= L.off_dec_cmax + bh * (size_t)p.Nq * L.dec_nchunks * sizeof(float));
