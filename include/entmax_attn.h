@@ -82,8 +82,8 @@ typedef struct {
   int32_t path;            /* forward path: 0 = automatic (candidate-list kernel first; workgroups that meet a row
                               with too many candidates fall back to the tiled kernel; with Nq <= 8, or Nq <= 64 and
                               Nk >= 64 Nq -- the decoding shape -- kernels that split the keys instead),
-                              1 = tiled kernel only, 2 = as 0 without the decoding-shape kernels and with the list
-                              kernels for long sequences (Nk >= 16384) whatever the sizes: a test aid */
+                              1 = tiled kernel only, 2 = as 0 without the decoding-shape kernels and (bf16, D = 64) with
+                              the list kernel for long sequences (Nk >= 16384) whatever the sizes: a test aid */
   float alpha;             /* 1 < alpha <= 2; 1.5, 2.0 and 1.25 run on integer-power fast paths */
   float delta;             /* ASEntmax delta (1.0 in the paper's experiments) */
   int64_t q_stride_b, q_stride_h, q_stride_n;    /* strides of Q,O,dO,dQ in elements; all 0 = contiguous */
@@ -178,8 +178,8 @@ enum {
  * matrix cores with zero tiles skipped.
  * Decoding shape (path 0; Nq <= 8, or Nq <= 64 with Nk >= 64 Nq: a few query rows against a long key sequence, the regime of the
  * long-context evaluation of Sec. 4): the keys, not the queries, are split over the chip; K is
- * read once, the rows' scores (Nq x Nk fp32 per head) go to the workspace, and each row's
- * threshold and output come from its score row.  `saved` then only tells the backward to rebuild
+ * read once, the rows' scores (up to Nq x Nk fp32 per head; of several rows only those that can matter) go to the
+ * workspace, and each row's threshold and output come from them.  `saved` then only tells the backward to rebuild
  * the supports itself.
  */
 int entmax_attn_fwd(const entmax_attn_params* p, const void* Q, const void* K, const void* V, const float* beta,

@@ -5,8 +5,10 @@
 // instead, and the path is bound by reading K once from HBM:
 //   decode_scores_kernel  grid (key chunks, heads): z_ij = (alpha-1) scale_i <q_i,k_j>/sqrt(d)
 //                         (Sec. 2.1 scores, eq. (asentmax) scale) for the visible keys, fp32, to
-//                         the workspace;
-//   decode_solve_kernel   one workgroup per query row: row maximum, the keys that can be in the
+//                         the workspace, and a word per chunk (pack_cmax);
+//   decode_scores_mfma_kernel  the same for several rows on the matrix cores, in blocks of 32 keys: blocks
+//                         that the row's largest score rules out are not written;
+//   decode_solve_kernel   one workgroup per query row: bound on the row maximum, the keys that can be in the
 //                         support (z > max - 1: everything else is zero already at the lowest
 //                         possible threshold), the threshold of eq. (entmax) by Newton steps from
 //                         that lowest threshold (sum_j [z_j - tau]_+^r - 1 is convex and decreasing
@@ -29,7 +31,9 @@ struct DecodeArgs {
   const void* V;
   void* O;
   float* tau;     // [B*H*Nq]
-  float* scores;  // [B*H*Nq][nks] workspace, entries j < row_limit(i) written; nks = Nk rounded up to 4
+  float* scores;  // [B*H*Nq][nks] workspace; nks = Nk rounded up to 4.  decode_scores_kernel writes the entries
+                  // j < row_limit(i), decode_scores_mfma_kernel whole 32-key blocks (-inf beyond the limit) and only those whose bit
+                  // is set in their chunk's word: nothing else may be read
   uint32_t* cmax; // [B*H*Nq][nchunks] largest score of each chunk of kDecodeChunk keys and which of its 32-key blocks'
                   // scores were written, see pack_cmax()
   int nks, nchunks;
@@ -181,8 +185,8 @@ __global__ __launch_bounds__(kThreads) void decode_scores_kernel(DecodeArgs A) {
 // the workgroup found that: a key at or below (largest score) - 1 has probability zero (App. A, lower end of the
 // bracket).  Which blocks of a chunk were written is noted beside the chunk's maximum (pack_cmax).  The two lanes of a row
 // each write half of a block's scores: the first one decides for both (the row's largest score may change under their reads).
-// Measured: 48 heads, 64 rows, 32768 keys, D 64: 156 us with every score written, 57 us so (two blocks on their way instead of one: the same); 128 heads, 5 rows, 6007
-// keys, D 128: 41 us with per-row dot products (5 us a row at 201 MB of K), 32 us so, which is 6.1 TB/s on K.
+// Measured: 48 heads, 64 rows, 32768 keys, D 64: 156 us with every score written, 57 us so (two blocks on their way
+// instead of one: the same); 128 heads, 5 rows, 6007 keys, D 128: 41 us with per-row dot products (5 us a row at 201 MB of K), 32 us so, which is 6.1 TB/s on K.
 template <typename T, int D, int NQB>
 __global__ __launch_bounds__(kThreads) void decode_scores_mfma_kernel(DecodeArgs A) {
   constexpr int NC = D / 16;

@@ -236,7 +236,8 @@ struct FwdTile {
 constexpr int kListHeaderBytes = 32;  // of a list sweep's LDS: overflow flags and votes
 // Keys per LDS tile and workgroups per CU of the list sweeps (fwd_sparse.hip.h, bwd_sparse.hip.h), as measured:
 // at D = 64 four 32-key blocks per tile and three workgroups per CU; at D = 128 the query fragments take twice
-// the registers, and two blocks per tile with four workgroups per CU run a quarter faster (no spills).
+// the registers, and two blocks per tile with four workgroups per CU run a quarter faster although the forward's list
+// kernel then spills 44 registers (bf16, alpha 1.5; 24 at D = 64; fp32: 59 and none).
 template <typename T, int D>
 struct ListCfg {
   static constexpr int kTile = sizeof(T) == 2 ? (D == 64 ? 128 : 64) : 32;

@@ -492,8 +492,10 @@ __device__ __forceinline__ void fwd_lists_block(const FwdSparseArgs& A, int bh_,
   float hi = live ? y1 - __builtin_amdgcn_exp2f(-(g.alpha - 1.0f) * __builtin_amdgcn_logf((float)q.lim)) : 0.f;
   // two-element sub-problem {y1, y2}: its threshold is a lower bound of the row's
   if (live && m2 > -2.9e38f) lo = two_key_bound<AM>(y1, q.a * m2, 1.0f / (g.alpha - 1.0f));
-  // (a row of at most three blocks keeps the two-key bound: its lists overflow only where it keeps nearly every key, and
-  // such rows are the tiled kernel's)
+  // Rows of at most three blocks keep the two-key bound.  Not for speed: short rows that keep most of their keys then reach
+  // the tiled kernel, whose smallest cases the tests are made of.  Training steps with the limit at 96, without one and
+  // at 192: B 8, H 12, n 96 124, 106 and 123 us; n 160 152, 147, 187; B 1, H 1, n 256, fp32 151, 150, 256; rows of
+  // constant logit range (n 256 to 4096) the same with any.
   if (live && q.lim > 96) lo = top_blocks_bound<AM>(top, bn, q.a, lo, 1.0f / (g.alpha - 1.0f));
   lo = fminf(lo, hi);
 
@@ -561,9 +563,11 @@ __global__ __launch_bounds__(kThreads, (ListCfg<T, D>::kOcc)) void fwd_lists_ker
 // ------------------------------------------------- long sequences: two query blocks per workgroup
 // The same two sweeps as fwd_lists_block for the adjacent blocks 2 sblk and 2 sblk + 1 at once:
 // every wave holds its 32-row group of both blocks (64 query rows), so that a K fragment read from LDS feeds two
-// matrix instructions and a K tile staged through LDS serves 256 rows.  Each block keeps its own lists, flags,
-// bounds and block bits, exactly as if it had run alone.  Used where the launch still fills the chip with half as
-// many workgroups (Nk >= ListCfg::kFlagMinKeys).
+// matrix instructions and a K tile staged through LDS serves 256 rows.  Each block keeps its own lists, flags, bounds and
+// block bits.  Two block memories (TopBlocks) do not fit the registers beside that (184 spills: 4.3 ms at n 32768), so the bound
+// is the two-key one and the first sweep sets a block's bit where some lane's largest score of it comes within the
+// bracket's width of that lane's running maximum (half of the blocks at n 32768).  Used where the launch still fills the
+// chip with half as many workgroups (Nk >= ListCfg::kPairMinKeys).
 template <typename T, int D>
 struct PairCfg {
   using Cfg = ListCfg<T, D>;

@@ -27,8 +27,8 @@ struct Layout {
   size_t off_vt, off_cand, off_flcnt, off_bounds, off_flags, off_fcells, off_kt, off_qt, off_dot, off_mu, off_crow, off_dscale, off_mask, off_jlist, off_lcnt,
       off_kcount, off_koffs, off_kcursor, off_csc_i, off_csc_pw, off_hflag, off_longkeys, off_bcells, off_fknorm, off_bknorm, off_dk_rest, off_dv_rest, sv_cursor, sv_lcnt,
       sv_flags, sv_knorm, sv_kcount, sv_pool, total_saved, total_fwd, total_bwd;
-  size_t off_dec_cmax;  // decode kernels: score rows at offset 0, then the chunk maxima
-  int dec_nks, dec_nchunks, dec_chunk;
+  size_t off_dec_cmax;  // decode kernels: score rows at offset 0, then the chunk words
+  int dec_nks, dec_nchunks;
   long long csc_cap;    // entries of the key-major arrays per head
 };
 
@@ -116,12 +116,11 @@ inline Layout make_layout(const entmax_attn_params* p) {
   if (pool_entries > kSavedPoolMost) pool_entries = kSavedPoolMost;  // places are 27-bit numbers
   L.total_saved = L.sv_pool + align_up((pool_entries + kSavedPoolPad) * 8);
   // the decode kernels' score rows take the place of everything above
-  L.dec_nks = L.dec_nchunks = L.dec_chunk = 0;
+  L.dec_nks = L.dec_nchunks = 0;
   L.off_dec_cmax = 0;
   if (decode_shape(p->Nq, p->Nk)) {
     L.dec_nks = (p->Nk + 3) / 4 * 4;
-    L.dec_chunk = kDecodeChunk;
-    L.dec_nchunks = ceil_div(p->Nk, L.dec_chunk);
+    L.dec_nchunks = ceil_div(p->Nk, kDecodeChunk);
     L.off_dec_cmax = align_up(bh * (size_t)p->Nq * L.dec_nks * sizeof(float));
     const size_t dec_bytes = L.off_dec_cmax + align_up(bh * (size_t)p->Nq * L.dec_nchunks * sizeof(float));
     if (dec_bytes > L.total_fwd) L.total_fwd = dec_bytes;

@@ -234,8 +234,8 @@ def test_hot_keys_beyond_the_forward_numbering():
 
 
 def test_long_sequence_skips_blocks_in_the_second_sweep():
-    """From 16384 keys on, the list kernel's first sweep keeps one bit per (32-row group, 32-key block) and the
-    second sweep computes only the marked blocks.  Ragged length beyond the range the bits cover is not needed
+    """The list kernel's first sweep marks (32-row group, 32-key block) pairs and the second sweep computes only the
+    marked blocks (one head: the one-block kernel, whose marks end at 28672 keys).  Ragged length beyond the range the bits cover is not needed
     for that (the full-size n = 32768 tests cover it); here every row of one head is compared, and two rows get a
     late maximum preceded by near ties early in the sequence, which must all stay on their lists."""
     n = 16384 + 37
@@ -259,9 +259,9 @@ def test_long_sequence_skips_blocks_in_the_second_sweep():
 
 @pytest.mark.parametrize("n,path", [(30720 + 300, 0), (65536 + 200, 2)])
 def test_block_bits_end_before_the_sequence(n, path, forward_path):
-    """The block bits of the long-sequence list kernels cover 30720 keys (one block per workgroup) or 65536 keys
-    (two blocks per workgroup, forced here with params.path = 2); key blocks beyond that range must always be
-    computed in the second sweep.  One head, forward, every row against the oracle."""
+    """The marks of the list kernel cover 28672 keys at D = 64 (one block per workgroup), the block bits of the two-block
+    kernel 65536 (forced here with params.path = 2); key blocks beyond that range must always be computed in the second
+    sweep.  One head, forward, every row against the oracle."""
     if forward_path == 1:
         pytest.skip("the list kernels are the subject")
     data = synth.make_inputs(B=1, H=1, n=n, d=64, dtype="bf16", scale="head", planted=0.05, seed=17, want_dO=False)
@@ -278,10 +278,10 @@ def test_block_bits_end_before_the_sequence(n, path, forward_path):
                                                       (True, 520, 520, 1.7, "none"), (True, 257, 257, 1.5, "dense")])
 @pytest.mark.parametrize("d", [64, 128])
 def test_long_sequence_kernels_at_small_sizes(causal, nq, nk, alpha, scale, d):
-    """params.path = 2 runs the list kernels made for long sequences at any size: at D = 64 the kernel that takes
+    """params.path = 2 runs the list kernel made for long sequences at any size: at D = 64 the kernel that takes
     two adjacent query blocks per workgroup (odd numbers of blocks end on a single one; 641 rows are five blocks
-    and a ragged sixth), at D = 128 the one-block kernel with the block bits.  Same bar as everywhere; the
-    backward gets the forward's lists."""
+    and a ragged sixth).  At D = 128 there is none: the list kernel runs as with path 0, but also where path 0 would
+    take the decoding-shape kernels (the case of one row).  Same bar as everywhere; the backward gets the forward's lists."""
     data = _case(2, 3, nq, nk, d, "bf16", scale, seed=13)
     g = gpu_run(data, alpha, "bf16", causal=causal, path=2, use_saved=True, stats=True)
     r = oracle_run(data, alpha, causal=causal)
