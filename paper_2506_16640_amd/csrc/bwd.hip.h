@@ -39,7 +39,7 @@ struct BwdArgs {
   const int* head_flag;  // NULL: every head, whole; else [B*H]: 0 skip the head, 1 only its flagged query blocks,
                          // 2 the whole head
   const int* block_flag; // with head_flag: [B*H*nqb] the query blocks the list path left over
-  uint16_t* dk_rest;     // 16-bit outputs, with head_flag: [B*H][npad_k][D] the low halves of the fp32 dK, dV of heads whose
+  uint16_t* dk_rest;     // 16-bit outputs, with head_flag: [B*H*Nk][D] the low halves of the fp32 dK, dV of heads whose
   uint16_t* dv_rest;     // flag is 1 (dK and dV take the high halves): bwd_keys_kernel adds its share to the whole sums
   int nqb, nkb, nqg, mask_words;
   int xcd_room;  // workgroups of the kernel being launched that one XCD holds at a time (see bwd_tiled_item)
@@ -483,7 +483,7 @@ __device__ __forceinline__ void bwd_dkv_block(const BwdArgs& A, int bh_, int blk
           const int row = jw0 + 8 * (e >> 2) + 4 * hh + (e & 3);
           if (row < g.Nk) {
             const long long idx = kv_base + (long long)row * g.kv_sn + mm * 32 + li;
-            const long long rest = ((long long)bh * g.npad_k + row) * D + mm * 32 + li;
+            const long long rest = ((long long)bh * g.Nk + row) * D + mm * 32 + li;
             split(A.dK, idx, A.dk_rest + rest, dk[mm][e] * inv_am1);
             split(A.dV, idx, A.dv_rest + rest, dv[mm][e]);
           }
