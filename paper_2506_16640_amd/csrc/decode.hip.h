@@ -186,7 +186,8 @@ __global__ __launch_bounds__(kThreads) void decode_scores_kernel(DecodeArgs A) {
 // bracket).  Which blocks of a chunk were written is noted beside the chunk's maximum (pack_cmax).  The two lanes of a row
 // each write half of a block's scores: the first one decides for both (the row's largest score may change under their reads).
 // Measured: 48 heads, 64 rows, 32768 keys, D 64: 156 us with every score written, 57 us so (two blocks on their way
-// instead of one: the same); 128 heads, 5 rows, 6007 keys, D 128: 41 us with per-row dot products (5 us a row at 201 MB of K), 32 us so, which is 6.1 TB/s on K.
+// instead of one: the same); 128 heads, 5 rows, 6007 keys, D 128: 41 us with per-row dot products (5 us a row at 201 MB of
+// K), 32 us so, which is 6.1 TB/s on K (read again every time: part of it stays in the last-level cache).
 template <typename T, int D, int NQB>
 __global__ __launch_bounds__(kThreads) void decode_scores_mfma_kernel(DecodeArgs A) {
   constexpr int NC = D / 16;
