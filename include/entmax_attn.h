@@ -112,7 +112,7 @@ enum {
   ENTMAX_STAT_FWD_CANDIDATES = 14,   /* candidate-list kernel: keys put on the lists */
   ENTMAX_STAT_FWD_SUPPORT = 15,      /* candidate-list kernel: non-zero probabilities (exact support size, summed) */
   ENTMAX_STAT_FWD_SPARSE_BLOCKS = 16, /* workgroups finished by the candidate-list kernel */
-  ENTMAX_STAT_FWD_LIST_QK = 17,      /* candidate-list kernel: score tiles computed (both sweeps) */
+  ENTMAX_STAT_FWD_LIST_QK = 17,      /* candidate-list kernel: score tiles computed (its sweep, and the second one where it is needed) */
   ENTMAX_STAT_BWD_LIST_QK = 18,      /* support-list backward: score tiles computed by its one sweep */
   ENTMAX_STAT_BWD_SUPPORT = 19,      /* support-list backward: (row, key) entries with p > 0 */
   ENTMAX_STAT_FWD_WINDOW_SKIPPED = 20, /* with alibi_slopes: visible tiles (counted in FWD_TILES_VISIBLE) that no sweep
@@ -126,7 +126,7 @@ enum {
  * before the first kernel and entry k after the last kernel of phase k-1. */
 enum {
   ENTMAX_FWD_PHASE_PREPARE = 0,   /* with alibi_slopes: the heads' largest key norms (else empty) */
-  ENTMAX_FWD_PHASE_LISTS = 1,     /* candidate-list kernel: two Q K^T sweeps (row maximum, candidates);
+  ENTMAX_FWD_PHASE_LISTS = 1,     /* candidate-list kernel: a Q K^T sweep, then the scores of the keys that can matter;
                                      decoding shape: the score rows, one pass over K */
   ENTMAX_FWD_PHASE_FINISH = 2,    /* threshold and output from the candidate lists (decoding shape: from the
                                      score rows) */
@@ -174,7 +174,7 @@ enum {
  * f(tau) = sum_j [(alpha-1) s_ij - tau]_+^(1/(alpha-1)) - 1 inside the bracket of
  * App. A eq. (bounds)); the n x n score matrix is never stored.  Rows with few
  * candidates above a lower bound of tau are finished from a short per-row list
- * after two sweeps; denser rows run the tile-wise iteration and P.V on the
+ * after one sweep (two where a row has more of them than the sweep remembers); denser rows run the tile-wise iteration and P.V on the
  * matrix cores with zero tiles skipped.
  * Decoding shape (path 0; Nq <= 8, or Nq <= 64 with Nk >= 64 Nq: a few query rows against a long key sequence, the regime of the
  * long-context evaluation of Sec. 4): the keys, not the queries, are split over the chip; K is

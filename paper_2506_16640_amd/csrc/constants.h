@@ -13,14 +13,13 @@ constexpr int kBlockRows = 128;  // rows (queries or keys) owned by a workgroup:
 constexpr int kPairMinWorkgroups = 768;
 // The forward's list kernel takes one query block per workgroup instead of a causal pair where the pairs would
 // leave the chip short of workgroups (fewer than three per CU; B 8, H 12, n 1024: 51 -> 47 us).  Launches of less
-// than half a workgroup per CU keep the pairs, whose scratch strips are half as many; a pair takes as long as its two
-// blocks one after the other, so that a head of two blocks would be done in two thirds of the time with one block each
-// (not built: the scratch sizes follow this rule).
+// than half a workgroup per CU keep the pairs, whose scratch strips are half as many, but for heads of two blocks, which have a strip
+// for each all the same.
 constexpr int kUnpairedBelowWorkgroups = 768;
 constexpr int kUnpairedFromWorkgroups = 128;
 inline bool fwd_lists_unpaired(long long heads, int nqb) {
   const long long pairs = heads * ((nqb + 1) / 2);
-  return nqb >= 2 && pairs >= kUnpairedFromWorkgroups && pairs < kUnpairedBelowWorkgroups;
+  return nqb >= 2 && (nqb == 2 || pairs >= kUnpairedFromWorkgroups) && pairs < kUnpairedBelowWorkgroups;
 }
 
 constexpr int kCandCap = 32;     // candidate entries per lane = per half row (forward lists)

@@ -76,12 +76,6 @@ __device__ __forceinline__ float sum8(float x) {
   return dpp_add<0x4E>(x);
 }
 
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-// acc + a.lo * b.lo + a.hi * b.hi for two packed bf16 pairs, in fp32
-__device__ __forceinline__ float dot2_bf16(uint32_t a, uint32_t b, float acc) {
-  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, a), __builtin_bit_cast(bf16x2_t, b), acc, false);
-}
-
 // Eight lanes share a key row (each a contiguous eighth of its features), so a wave's load
 // instruction covers eight whole rows; a thread keeps four rows in flight.
 template <typename T, int D>

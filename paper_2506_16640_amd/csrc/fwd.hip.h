@@ -234,30 +234,33 @@ struct FwdTile {
 };
 
 constexpr int kListHeaderBytes = 32;  // of a list sweep's LDS: overflow flags and votes
+constexpr int kScanBytes = 272;       // ... of the forward's: ScanLds
 // Keys per LDS tile and workgroups per CU of the list sweeps (fwd_sparse.hip.h, bwd_sparse.hip.h), as measured:
 // at D = 64 four 32-key blocks per tile and three workgroups per CU; at D = 128 the query fragments take twice
-// the registers, and two blocks per tile with four workgroups per CU run a quarter faster although the forward's list
-// kernel then spills 44 registers (bf16, alpha 1.5; 24 at D = 64; fp32: 59 and none).
+// the registers, and two blocks per tile with four workgroups per CU run the backward's sweep a quarter faster; the forward's,
+// which works on two blocks of scores at a time, takes three there too (B 2, H 16, n 8192: 357 us; 577 with four, 128 registers).
 template <typename T, int D>
 struct ListCfg {
   static constexpr int kTile = sizeof(T) == 2 ? (D == 64 ? 128 : 64) : 32;
   static constexpr int kOcc = (sizeof(T) == 2 && D == 128) ? 4 : 3;
+  static constexpr int kFwdOcc = 3;
   // key tiles in flight (sweep_tiles).  Measured at B 4, H 12, n 4096, D 64: two in flight cost registers
   // (spills at three workgroups per CU: 145 us against 139; no spills at two per CU: 188 us)
   static constexpr int kDepth = 1;
   // cells per thread that the collecting sweep keeps in LDS (20 bytes each)
   static constexpr int kLdsCells = kOcc == 4 ? 1 : 4;
-  // Per wave, one bit per 32-key block of the head: the blocks that can hold a candidate, so that the forward's second
-  // sweep skips the others (mark_blocks() in fwd_sparse.hip.h); blocks beyond the words' range are always visited.
-  // LDS is handed out in pieces of 1280 bytes (measured: 53760 bytes per workgroup run three to a CU, 54080 only two,
-  // which costs the sweeps 40 %), so at D = 64 the words take what is left of the 42nd piece: 28 per wave, 28672 keys.
-  // At D = 128 (four workgroups of 32 pieces) there is room for 128.
-  static constexpr int kMarkWords = (sizeof(T) == 2 && D == 64) ? 28 : 128;
+  // accumulator registers of a group of the sweep's memory (TopGroups in fwd_sparse.hip.h)
+  static constexpr int kGroup = 8;
   // sequences of at least this length: two query blocks per workgroup (fwd_lists_pair_kernel)
   static constexpr int kPairMinKeys = 16384;
-  // dynamic LDS of a list-sweep kernel: two tile buffers, flags and votes, the cells, the marks
-  static constexpr size_t kLdsBytes = 2 * (size_t)kTile * D * sizeof(T) + kListHeaderBytes + (size_t)kLdsCells * kThreads * 20 +
-                                      (size_t)kWaves * kMarkWords * 4;
+  // The forward's list kernels bring their tiles straight to LDS (sweep_ring(): three buffers), and its rare second sweep keeps all its cells in
+  // scratch memory; fp32 (whose rows are too long for that swizzle at D = 128) stays with two buffers and registers.
+  static constexpr bool kRing = sizeof(T) == 2;
+  static constexpr int kFwdCells = kRing ? 0 : kLdsCells;
+  static constexpr size_t kFwdTiles = (kRing ? 3 : 2) * (size_t)kTile * D * sizeof(T);
+  static constexpr size_t kFwdLdsBytes = kFwdTiles + kListHeaderBytes + kScanBytes + (size_t)kFwdCells * kThreads * 20;
+  // dynamic LDS of the backward's list-sweep kernel: two tile buffers, flags and votes, the cells
+  static constexpr size_t kLdsBytes = 2 * (size_t)kTile * D * sizeof(T) + kListHeaderBytes + (size_t)kLdsCells * kThreads * 20;
 };
 
 // SPLIT: the workgroup takes one 32-row group (rg_) of the block instead of four, and its four waves share out

@@ -5,13 +5,14 @@
 // threshold is bounded below by any sub-problem: solving eq. (entmax) on a
 // subset S of the row's scores gives tau_S <= tau, because dropping terms can
 // only lower f(tau) = sum_j [(alpha-1) s_j - tau]_+^r - 1.  So
-//   fwd_lists_kernel (matrix cores, K tiles through LDS, two sweeps)
-//     1. row-max sweep that also keeps each lane's largest 32-key blocks:
+//   fwd_lists_kernel (matrix cores, K tiles through LDS, one sweep)
+//     1. a sweep over the scores that keeps the row maximum and each lane's (half row's) largest groups of eight keys:
 //        tau_lb = max(left end of the bracket of App. A eq. (bounds),
-//                     solution of the sub-problem of those blocks' largest scores) <= tau;
-//     2. second Q K^T sweep, over the blocks that can hold a candidate: every key with (alpha-1) s_ij > tau_lb goes on the
+//                     solution of the sub-problem of those groups' largest scores) <= tau;
+//     2. the scores of the keys of the groups above tau_lb once more, from memory: every key with (alpha-1) s_ij > tau_lb goes on the
 //        row's candidate list (key index + raw score).  Every key of the
-//        support is on that list; nothing else of the row can matter.
+//        support is on that list; nothing else of the row can matter.  Rows with more such groups than were kept are
+//        looked through on their own, or swept a second time.
 //   fwd_finish_kernel (no matrix work, one lane pair per row)
 //     3. the threshold by the same safeguarded steps as the tiled kernel
 //        (closed-form local-model root for alpha 1.5 / 2, Halley / Newton
@@ -195,19 +196,16 @@ __device__ __forceinline__ void pool_want(int* word, int cnt, int lane) {
 }
 static_assert(kBwdCap < 32 && kThreads * kBwdCap < (1 << 16), "five bits a half row, 16 a block");
 
-// One sweep over the visible key tiles of the block: every key whose shifted score
-// a * dot - thr is positive ends up in the lane's list.  Returns false (workgroup-uniform) if
+// One sweep over the visible key tiles of the block: every key whose raw score exceeds the lane's cut ends up in its
+// list, behind the cnt entries that are there.  Returns false (workgroup-uniform) if
 // some list overflowed; the sweep is abandoned early in that case.  ovf: three ints of LDS;
-// lds_cells: CellBuf<CAP, LS>::kLdsBytes bytes of LDS.  marks: NULL, or this wave's ListCfg::kMarkWords words
-// of LDS with one bit per 32-key block of the head: a block whose bit is clear holds no candidate of any row of
-// the wave and is not computed (blocks beyond the words' range always are).  With the forward's lists (CAP = kCandCap), ovf[3] is a word for pool_want().
-template <typename C, typename T, int D, int CAP, int LS>
+// lds_cells: CellBuf<CAP, LS>::kLdsBytes bytes of LDS.  wave_on (wave-uniform): false: no lane of this wave looks for
+// anything, and it only helps to bring the tiles.  With the forward's lists (CAP = kCandCap), ovf[3] is a word for pool_want().
+template <typename C, typename T, int D, int CAP, int LS, bool RING = false>
 __device__ __forceinline__ bool collect_sweep(const C& q, const Geom& g, const void* K, char* tiles, int* ovf, char* lds_cells,
-                                              bool live, float thr, void* cells, uint2* mylist, int& cnt, unsigned& n_qk,
-                                              unsigned& n_cand_tiles, const uint32_t* marks = nullptr,
-                                              int strip_no = -1) {
+                                              float cut, void* cells, uint2* mylist, int& cnt, unsigned& n_qk,
+                                              unsigned& n_cand_tiles, bool wave_on = true, int strip_no = -1) {
   constexpr int KT = C::KT, NSB = C::NSB;
-  const float cut = raw_cut(q.a, live, thr);
   if (q.tid < 3) ovf[q.tid] = 0;
   CellBuf<CAP, LS> cb;
   cb.init(cells, lds_cells, q.tid, strip_no < 0 ? (int)blockIdx.x : strip_no);  // (which of the scratch strips is this workgroup's)
@@ -216,38 +214,43 @@ __device__ __forceinline__ bool collect_sweep(const C& q, const Geom& g, const v
   slots[0].base = reinterpret_cast<const char*>(reinterpret_cast<const T*>(K) + (long long)q.b * g.kv_sb +
                                                 (long long)q.h * g.kv_sh);
   slots[0].row_bytes = g.kv_sn * (long long)sizeof(T);
-  sweep_tiles<C, T, D, 1, 0, ListCfg<T, D>::kDepth>(
-      tiles, slots, q.ntiles, g.Nk, q.tid, [&](int kt) { return q.tile_in_window(kt); },
-      [&](int kt, const char* tl) {
-        if (!q.tile_in_wave_window(kt)) return;
-        const bool interior = (kt + 1) * KT <= q.wave_lim_min;
-        uint32_t act = interior ? ((1u << NSB) - 1u) : q.visible_bits(kt);
-        if (marks && (kt + 1) * NSB <= ListCfg<T, D>::kMarkWords * 32) {
-          const int jb = kt * NSB;
-          act &= __builtin_amdgcn_readfirstlane(marks[jb >> 5]) >> (jb & 31);
-        }
-        if (act == 0u) return;
-        f32x16_t acc[NSB];
-        if (interior && act == (1u << NSB) - 1u) {
-          q.scores_all(tl, acc, kt);
-        } else {
+  auto body = [&](int kt, const char* tl) {
+    if (!wave_on || !q.tile_in_wave_window(kt)) return;
+    const bool interior = (kt + 1) * KT <= q.wave_lim_min;
+    const uint32_t act = interior ? ((1u << NSB) - 1u) : q.visible_bits(kt);
+    if (act == 0u) return;
+    f32x16_t acc[NSB];
+    if (interior) {
+      q.scores_all(tl, acc, kt);
+    } else {
 #pragma unroll
-          for (int sb = 0; sb < NSB; ++sb)
-            if (act & (1u << sb)) acc[sb] = q.scores(tl, sb, kt);
-        }
+      for (int sb = 0; sb < NSB; ++sb)
+        if (act & (1u << sb)) acc[sb] = q.scores(tl, sb, kt);
+    }
 #pragma unroll
-        for (int sb = 0; sb < NSB; ++sb) {
-          if (!(act & (1u << sb))) continue;
-          int j0 = kt * KT + sb * 32;
-          ++n_qk;
-          if (j0 + 32 > q.wave_lim_min) mask_block(q, acc[sb], j0);
-          append_cells(q, acc[sb], j0, cut, cb, ncell, n_cand_tiles);
-        }
-        // once per tile: a strip that overflowed (its last cell was overwritten: the lists are discarded)
-        if (__ballot(ncell > CAP) != 0ull && q.lane == 0) ovf[kt & 1] = 1;
-      },
-      // flags of the previous tile's parity were final before the barrier that ended that tile
-      [&](int kt) { return kt > 0 && ovf[(kt - 1) & 1] != 0; });
+    for (int sb = 0; sb < NSB; ++sb) {
+      if (!(act & (1u << sb))) continue;
+      int j0 = kt * KT + sb * 32;
+      ++n_qk;
+      if (j0 + 32 > q.wave_lim_min) mask_block(q, acc[sb], j0);
+      append_cells(q, acc[sb], j0, cut, cb, ncell, n_cand_tiles);
+    }
+    // once per tile: a strip that overflowed (its last cell was overwritten: the lists are discarded)
+    if (__ballot(ncell > CAP) != 0ull && q.lane == 0) ovf[kt & 1] = 1;
+  };
+  // flags of the previous tile's parity were final before the barrier that ended that tile
+  auto leave = [&](int kt) { return kt > 0 && ovf[(kt - 1) & 1] != 0; };
+  if constexpr (RING) {
+    TileRing<C, T, D> ring;
+    int first = 0;
+    if constexpr (C::BIAS) first = q.kt_first;
+    ring.start(tiles, slots[0], first, q.ntiles, g.Nk);
+    while (ring.kt < q.ntiles && !leave(ring.kt)) ring.step([&](const char* tl) { body(ring.kt, tl); });
+    ring.abandon();
+  } else {
+    sweep_tiles<C, T, D, 1, 0, ListCfg<T, D>::kDepth>(tiles, slots, q.ntiles, g.Nk, q.tid, [&](int kt) { return q.tile_in_window(kt); },
+                                                      body, leave);
+  }
   // the sweep ended on a barrier: both flags are final
   bool fits = (ovf[0] | ovf[1]) == 0;
   if (fits) {
@@ -260,76 +263,282 @@ __device__ __forceinline__ bool collect_sweep(const C& q, const Geom& g, const v
   return fits;
 }
 
-// The first sweep's memory of where a lane's large scores are: its kTopBlocks largest 32-key blocks by the lane's largest
-// score of each, in descending order.  An entry is that score with the block's number in place of its lowest mantissa bits,
-// so that one v_med3 per place keeps the order (t1 >= t2: the middle one of t1, t2, x is the new t2).
-// It is there for two reasons: the second sweep computes only the blocks that can hold a candidate (bf16, alpha 1.5: 56 % of
-// them at B 4, H 12, n 4096, D 64; 41 % at B 2, H 16, n 8192, D 128; 54 and 34 % do), and the lower bound of the threshold comes
-// from up to twelve scores instead of two (top_blocks_bound()), which keeps more rows of long supports on the lists.  Forward
-// calls before and after: 186 -> 181 us, 663 -> 637 us; B 8, H 12, n 1024: 76 -> 71 us; alpha 1.25, n 4096: 492 -> 437 us.
-// Eight places instead of six: 183, 647 us (registers).  The second sweep by waves on their own, without barriers, straight
-// from global memory or through LDS of their own: 200 to 207 and 830 to 850 us (K no longer shared by four waves).
-constexpr int kTopBlocks = 6;
-struct BlockNumbers {  // how the numbers of a head's blocks are packed
+// The sweep's memory of where a lane's large scores are: its kTopGroups largest groups by the lane's largest score of
+// each, in descending order.  A group is G (8 or 16) of the lane's 16 accumulator registers of a 32-key block; an entry is that score with
+// the group's number in place of its lowest mantissa bits, so that one v_med3 per place keeps the order (t1 >= t2: the middle
+// one of t1, t2, x is the new t2).  The entries give a lower bound of the threshold from up to sixteen scores (top_groups_bound()), and
+// those above it name every key that can be in the support: only these keys' scores are formed again (rescore_groups()),
+// and the sweep over the scores need not be repeated.
+constexpr int kTopGroups = 12;
+// Rows of strong scales need fewer places: a wave all of whose rows have (alpha-1) |scale| of kFewPlacesScale or more keeps this
+// many while it goes through the tiles that every row sees whole.  (Normal scores, alpha 1.5, n 1024 to 32768: of the lanes whose
+// (alpha-1) |scale| is 2.3 fewer than 1 in 1000 need more than eight, at 1.2 one to three in 100, of which 1 in 500 more than twelve.  Places cost
+// two vector instructions a block and each: with eight for all n 4096 101 us, n 32768 1060, with twelve for all the sweep 6 us longer.)
+constexpr int kFewPlaces = 8;
+constexpr float kFewPlacesScale = 3.0f;
+template <int G>
+struct GroupNumbers {  // how the numbers of a head's groups are packed
+  static constexpr int kPerBlock = 16 / G;  // groups of a lane in a 32-key block
   uint32_t keep;       // the score's bits that stay
   float eps;           // a score differs from its entry by less than eps |entry|
-  __device__ __forceinline__ explicit BlockNumbers(int Nk) {
-    const int bits = 32 - __builtin_clz((unsigned)((Nk - 1) >> 5) | 1u);
+  __device__ __forceinline__ explicit GroupNumbers(int Nk) {
+    const int bits = 32 - __builtin_clz((unsigned)(((Nk - 1) >> 5) * kPerBlock + kPerBlock - 1) | 1u);
     keep = ~((1u << bits) - 1u);
+    asm volatile("" : "+v"(keep));  // (in a vector register: an instruction takes one scalar operand, the group's number)
     eps = __uint_as_float((uint32_t)(127 + bits - 22) << 23);
   }
   __device__ __forceinline__ float upper(float t) const { return fmaf(fabsf(t), eps, t); }  // (both increasing in t)
   __device__ __forceinline__ float lower(float t) const { return fmaf(-fabsf(t), eps, t); }
 };
-struct TopBlocks {
-  float t[kTopBlocks];
+template <int G>
+struct TopGroups {
+  using Numbers = GroupNumbers<G>;
+  float t[kTopGroups];
   __device__ __forceinline__ void init() {
 #pragma unroll
-    for (int k = 0; k < kTopBlocks; ++k) t[k] = __uint_as_float(0xff700000u);  // below every entry, names block 0
+    for (int k = 0; k < kTopGroups; ++k) t[k] = __uint_as_float(0xff700000u);  // below every entry (-3.19e38)
   }
-  // (the bounds keep the bits of a masked block's -inf, or of an infinite score, from becoming a NaN)
-  __device__ __forceinline__ void take(float lm, const BlockNumbers& bn, int jb) {
-    const float x = __uint_as_float((__float_as_uint(__builtin_amdgcn_fmed3f(lm, -3.0e38f, 3.0e38f)) & bn.keep) | (uint32_t)jb);
+  __device__ __forceinline__ void take_one(float m, const Numbers& gn, int number) {
+    const float x = __uint_as_float((__float_as_uint(m) & gn.keep) | (uint32_t)number);
 #pragma unroll
-    for (int k = kTopBlocks - 1; k > 0; --k) t[k] = __builtin_amdgcn_fmed3f(t[k - 1], t[k], x);
+    for (int k = kTopGroups - 1; k > 0; --k) t[k] = __builtin_amdgcn_fmed3f(t[k - 1], t[k], x);
     t[0] = fmaxf(t[0], x);
   }
-  // the row's second largest block maximum (a little low): a second, distinct score; below -2.9e38: there is none
-  __device__ __forceinline__ float runner_up(const BlockNumbers& bn) const {
+  // the lane's 16 scores of block jb; returns the largest.  No entry is below `floor`: kFloor keeps the bits of a masked
+  // group's -inf from becoming a NaN; with kNothing, which is below what init() left, scores of -inf leave no entry.  (An infinite
+  // score may leave a NaN; its row has an infinite bound, and no key passes it.)
+  static constexpr float kFloor = -3.0e38f, kNothing = -3.4e38f;
+  __device__ __forceinline__ float take(const f32x16_t& acc, const Numbers& gn, int jb, float floor = kFloor) {
+    constexpr int P = GroupNumbers<G>::kPerBlock;
+    float m[P];
+#pragma unroll
+    for (int u = 0; u < P; ++u) {
+      m[u] = fmaxf(fmaxf(acc[G * u], acc[G * u + 1]), floor);
+#pragma unroll
+      for (int e = 2; e < G; e += 2) m[u] = fmaxf(fmaxf(m[u], acc[G * u + e]), acc[G * u + e + 1]);
+      take_one(m[u], gn, P * jb + u);
+    }
+    return P == 1 ? m[0] : fmaxf(m[0], m[P - 1]);
+  }
+  // the same in four parts of about equally many instructions, to be issued between matrix instructions; m, x: the caller's, kept
+  // from part to part
+  template <int PART, int K>
+  __device__ __forceinline__ void take_part(const f32x16_t& acc, const Numbers& gn, int jb, float floor, float (&m)[16 / G],
+                                            float (&x)[16 / G], float& most) {
+    constexpr int P = GroupNumbers<G>::kPerBlock, N = P * K;
+    if constexpr (PART == 0) {
+#pragma unroll
+      for (int u = 0; u < P; ++u) m[u] = fmaxf(fmaxf(acc[G * u], acc[G * u + 1]), floor);
+#pragma unroll
+      for (int e = 2; e < G; e += 2)
+#pragma unroll
+        for (int u = 0; u < P; ++u) m[u] = fmaxf(fmaxf(m[u], acc[G * u + e]), acc[G * u + e + 1]);
+    } else {
+      if constexpr (PART == 1) {
+#pragma unroll
+        for (int u = 0; u < P; ++u) {
+          int number = P * jb + u;
+          asm volatile("" : "+s"(number));  // (one instruction for both steps)
+          x[u] = __uint_as_float((__float_as_uint(m[u]) & gn.keep) | (uint32_t)number);
+        }
+        most = P == 1 ? fmaxf(most, m[0]) : fmaxf(fmaxf(most, m[0]), m[P - 1]);
+      }
+#pragma unroll
+      for (int op = (PART - 1) * N / 3; op < PART * N / 3; ++op) {
+        const int u = op / K, k = K - 1 - op % K;
+        t[k] = k > 0 ? __builtin_amdgcn_fmed3f(t[k > 0 ? k - 1 : 0], t[k], x[u]) : fmaxf(t[0], x[u]);
+      }
+    }
+  }
+  // how many of the entries may name a candidate
+  __device__ __forceinline__ int above(float cut, const Numbers& gn) const {
+    int n = 0;
+#pragma unroll
+    for (int k = 0; k < kTopGroups; ++k) n += (t[k] > -3.1e38f && gn.upper(t[k]) > cut) ? 1 : 0;
+    return n;
+  }
+  // the row's second largest group maximum (a little low): a second, distinct score; below -2.9e38: there is none
+  __device__ __forceinline__ float runner_up(const Numbers& gn) const {
     const float p0 = __shfl_xor(t[0], 32), p1 = __shfl_xor(t[1], 32);
-    return bn.lower(fmaxf(fminf(t[0], p0), fmaxf(t[1], p1)));
+    return gn.lower(fmaxf(fminf(t[0], p0), fmaxf(t[1], p1)));
   }
 };
 
-// Marks in the wave's words the 32-key blocks that can hold a candidate of one of its rows: those among the lanes' top
-// blocks whose score may exceed the cutoff.  A block that fell out of a lane's top blocks scored no more than the last of
-// them; where that one may exceed the cutoff as well, every block the wave sees is marked.  (Blocks beyond the words
-// are always computed.)
-template <typename C>
-__device__ __forceinline__ void mark_blocks(const C& q, const TopBlocks& top, const BlockNumbers& bn, float cut,
-                                            uint32_t* words, int nwords) {
-  if (__ballot(bn.upper(top.t[kTopBlocks - 1]) > cut) == 0ull) {
-    for (int w = q.lane; w < nwords; w += 64) words[w] = 0u;
-    __builtin_amdgcn_wave_barrier();
+// Sum over the eight lanes of an octet of eight values each: lane c of the octet gets the sum of value kMap(c) (see
+// octet_value()).  Each step sends half of the values to the partner and keeps the other half.
+template <int CTRL>
+__device__ __forceinline__ float dpp_move(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float octet_scatter_sum(const float (&s)[8], int c) {
+  const bool b2 = (c & 4) != 0, b1 = (c & 2) != 0, b0 = (c & 1) != 0;
+  float u[4], v[2];
 #pragma unroll
-    for (int k = 0; k < kTopBlocks - 1; ++k) {
-      const bool pass = bn.upper(top.t[k]) > cut;
-      if (__ballot(pass) == 0ull) break;
-      if (pass) {
-        const uint32_t jb = __float_as_uint(top.t[k]) & ~bn.keep;
-        if ((int)(jb >> 5) < nwords) atomicOr(words + (jb >> 5), 1u << (jb & 31));
-      }
+  for (int k = 0; k < 4; ++k)  // partner 7 - c (row_half_mirror): lanes 4 to 7 keep values 4 to 7
+    u[k] = (b2 ? s[k + 4] : s[k]) + dpp_move<0x141>(b2 ? s[k] : s[k + 4]);
+#pragma unroll
+  for (int k = 0; k < 2; ++k)  // partner c ^ 2 (quad_perm 2 3 0 1)
+    v[k] = (b1 ? u[k + 2] : u[k]) + dpp_move<0x4e>(b1 ? u[k] : u[k + 2]);
+  return (b0 ? v[1] : v[0]) + dpp_move<0xb1>(b0 ? v[0] : v[1]);  // partner c ^ 1 (quad_perm 1 0 3 2)
+}
+
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+// acc + a.lo * b.lo + a.hi * b.hi for two packed bf16 pairs, in fp32
+__device__ __forceinline__ float dot2_bf16(uint32_t a, uint32_t b, float acc) {
+  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, a), __builtin_bit_cast(bf16x2_t, b), acc, false);
+}
+
+// Scores of the keys of groups, from memory.  Eight lanes (an octet) take a group, each lane a 16-byte word of every 128 bytes of
+// a key row, so that a load instruction brings eight whole rows (D 64, bf16).
+template <typename C, typename T, int D, int G>
+struct OctetScores {
+  static constexpr int W = D * (int)sizeof(T) / 128;  // 16-byte words of a row per lane
+  static constexpr int KB = W <= 2 ? 8 : 4;           // keys whose words are requested together
+  static constexpr int P = GroupNumbers<G>::kPerBlock;
+  struct Row {  // the octet's row
+    int pos, lim;
+    float cut, w;
+    bool negated;
+    u32x4_t qw[W];
+  };
+  const Geom& g;
+  const char *Kbh, *Qbh;
+  uint32_t krow_bytes;
+  int c, q0;  // lane of the octet; first row of the wave
+  __device__ __forceinline__ OctetScores(const C& q, const Geom& g_, const void* Q, const void* K) : g(g_) {
+    c = q.lane & 7;
+    q0 = q.q0;
+    Kbh = reinterpret_cast<const char*>(reinterpret_cast<const T*>(K) + (long long)q.b * g.kv_sb + (long long)q.h * g.kv_sh) + 16 * c;
+    Qbh = reinterpret_cast<const char*>(reinterpret_cast<const T*>(Q) + (long long)q.b * g.q_sb + (long long)q.h * g.q_sh) + 16 * c;
+    krow_bytes = (uint32_t)(g.kv_sn * (long long)sizeof(T));
+  }
+  // id: the lane of the wave whose keys are looked at; all lanes of the wave call this together
+  __device__ __forceinline__ Row row(const C& q, float wave_cut, int id) const {
+    float w = 0.f;
+    if constexpr (C::BIAS) w = __shfl(q.w, id);
+    return row_of(q0 + (id & 31), __shfl(wave_cut, id), __shfl(q.c, id) < 0.f, w);
+  }
+  __device__ __forceinline__ Row row_of(int i, float cut, bool negated, float w) const {
+    Row r;
+    r.pos = i + (g.Nk - g.Nq);
+    r.lim = g.causal ? min(r.pos + 1, g.Nk) : g.Nk;
+    const char* qrow = Qbh + (long long)i * (g.q_sn * (long long)sizeof(T));
+#pragma unroll
+    for (int k = 0; k < W; ++k) r.qw[k] = *reinterpret_cast<const u32x4_t*>(qrow + 128 * k);
+    r.cut = cut;
+    r.negated = negated;
+    r.w = w;
+    return r;
+  }
+  // first key of group `number` of a lane of half hh; register r of the group: key 8 (r / 4) + r % 4 behind it
+  static __device__ __forceinline__ int first_key(int number, int hh) { return (number / P) * 32 + (number % P) * 16 + 4 * hh; }
+  __device__ __forceinline__ int key(int j0, int r0) const { return j0 + 8 * ((r0 + c) >> 2) + (c & 3); }
+  // scores of registers r0 .. r0 + 7 of N groups at keys j0[]: lane c gets that of register r0 + c
+  template <int N>
+  __device__ __forceinline__ void eight(const Row (&row)[N], const int (&j0)[N], int r0, float (&d)[N]) const {
+    float part[N][8];
+#pragma unroll
+    for (int rb = 0; rb < 8; rb += KB) {
+      u32x4_t kw[N][KB][W];
+#pragma unroll
+      for (int n = 0; n < N; ++n)
+#pragma unroll
+        for (int u = 0; u < KB; ++u) {
+          const int r = r0 + rb + u;
+          const int j = min(j0[n] + 8 * (r >> 2) + (r & 3), g.Nk - 1);  // (rows beyond the tensor: masked by lim)
+          const char* krow = Kbh + (unsigned long long)(uint32_t)j * krow_bytes;
+#pragma unroll
+          for (int k = 0; k < W; ++k) kw[n][u][k] = *reinterpret_cast<const u32x4_t*>(krow + 128 * k);
+        }
+      __builtin_amdgcn_sched_barrier(0);  // (all of them requested before the first is used)
+#pragma unroll
+      for (int n = 0; n < N; ++n)
+#pragma unroll
+        for (int u = 0; u < KB; ++u) {
+          float s = 0.f;
+#pragma unroll
+          for (int k = 0; k < W; ++k) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              if constexpr (sizeof(T) == 2)
+                s = dot2_bf16(kw[n][u][k][e], row[n].qw[k][e], s);
+              else
+                s = fmaf(__uint_as_float(kw[n][u][k][e]), __uint_as_float(row[n].qw[k][e]), s);
+            }
+          }
+          part[n][rb + u] = s;
+        }
     }
-  } else {
-    int first = 0;
-    if constexpr (C::BIAS) first = q.kt_first_wave * C::NSB;
-    const int last = (q.wave_lim_max + 31) >> 5;
-    for (int w = q.lane; w < nwords; w += 64) {
-      const int f = min(max(first - 32 * w, 0), 32), l = min(max(last - 32 * w, 0), 32);
-      words[w] = (uint32_t)((1ull << l) - 1ull) & ~(uint32_t)((1ull << f) - 1ull);
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+      d[n] = octet_scatter_sum(part[n], c);
+      if (row[n].negated) d[n] = -d[n];
+      if constexpr (C::BIAS) d[n] = fmaf(row[n].w, (float)bias_dist(row[n].pos, key(j0[n], r0)), d[n]);
+    }
+  }
+};
+
+constexpr int kRescoreWords = 64 * (kTopGroups + 1);  // of LDS, per wave, for rescore_groups()
+
+// The keys of the groups that the lanes' first `ne` entries name: their scores, and those above the row's cut go on the
+// lists.  The octets of the wave take the groups in turn, two at a time (D 64, bf16) so that sixteen groups are under way.
+// lds: kRescoreWords words of the wave's own.  wave_list: the wave's lists, entry s of lane l at s * kListStride + l.  Returns
+// false if the lane's list is too short.
+template <typename C, typename T, int D, int G>
+__device__ __forceinline__ bool rescore_groups(const C& q, const Geom& g, const void* Q, const void* K, const TopGroups<G>& top,
+                                               const GroupNumbers<G>& gn, float cut, int ne, int* lds, uint2* wave_list, int& cnt) {
+  using O = OctetScores<C, T, D, G>;
+  constexpr int N = O::W == 1 ? 2 : 1;  // groups an octet has under way
+  int* counts = lds;
+  int* slots = lds + 64;
+  const int oct = q.lane >> 3;
+  const O o(q, g, Q, K);
+  const int c = o.c;
+  auto lanes_below = [](unsigned long long m) {
+    return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+  };
+  counts[q.lane] = 0;
+  int n = 0;
+#pragma unroll
+  for (int k = 0; k < kTopGroups; ++k) {
+    const unsigned long long takers = __ballot(k < ne);
+    if (k < ne) slots[n + lanes_below(takers)] = (int)((__float_as_uint(top.t[k]) & ~gn.keep) << 6) | q.lane;
+    n += (int)__popcll(takers);
+  }
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll 1
+  for (int s0 = 0; s0 < n; s0 += 8 * N) {
+    int id[N], j0[N];
+    typename O::Row row[N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      const uint32_t slot = (uint32_t)slots[min(s0 + 8 * u + oct, n - 1)];
+      id[u] = (int)(slot & 63u);
+      j0[u] = O::first_key((int)(slot >> 6), id[u] >> 5);
+      row[u] = o.row(q, cut, id[u]);
+      if (s0 + 8 * u + oct >= n) row[u].lim = 0;
+    }
+#pragma unroll
+    for (int r0 = 0; r0 < G; r0 += 8) {
+      float d[N];
+      o.eight(row, j0, r0, d);
+#pragma unroll
+      for (int u = 0; u < N; ++u) {
+        const int j = o.key(j0[u], r0);
+        const bool pass = j < row[u].lim && d[u] > row[u].cut;
+        const unsigned mine = (unsigned)(__ballot(pass) >> (8 * oct)) & 0xffu;
+        // (an octet's place in its list: the hardware adds for the lanes of one instruction in their order)
+        int before = 0;
+        if (c == 0) before = atomicAdd(counts + id[u], (int)__popc(mine));
+        const int at = __shfl(before, q.lane & ~7) + (int)__popc(mine & ((1u << c) - 1u));
+        if (pass && at < kCandCap) wave_list[at * kListStride + id[u]] = make_uint2((unsigned)j, __float_as_uint(d[u]));
+      }
     }
   }
   __builtin_amdgcn_wave_barrier();
+  const int total = counts[q.lane];
+  cnt = min(total, kCandCap);
+  return total <= kCandCap;
 }
 
 // Lower bound of the threshold from the two-element sub-problem {y1 >= y2} (y = (alpha-1) s) and the left
@@ -359,20 +568,20 @@ __device__ __forceinline__ float two_key_bound(float y1, float y2, float r) {
   return fmaxf(lo, t - 4e-6f * fmaxf(1.0f, fabsf(t)));
 }
 
-// The same from the up to 2 kTopBlocks scores of the row that its two lanes' top blocks name (distinct keys, each a little
+// The same from the up to 2 kTopGroups scores of the row that its two lanes' top groups name (distinct keys, each a little
 // low), starting at the bound lo: Newton steps from the left, as above.  A row of many close scores has far fewer keys above
 // this bound than above the two-key one.
-template <int AM>
-__device__ __forceinline__ float top_blocks_bound(const TopBlocks& top, const BlockNumbers& bn, float a, float lo, float r) {
-  float v[kTopBlocks];
+template <int AM, int G>
+__device__ __forceinline__ float top_groups_bound(const TopGroups<G>& top, const GroupNumbers<G>& gn, float a, float lo, float r) {
+  float v[kTopGroups];
 #pragma unroll
-  for (int k = 0; k < kTopBlocks; ++k) v[k] = a * bn.lower(top.t[k]);
+  for (int k = 0; k < kTopGroups; ++k) v[k] = a * gn.lower(top.t[k]);
   float t = lo;
 #pragma unroll 1
   for (int it = 0; it < 4; ++it) {
     float f = 0.f, fp = 0.f;
 #pragma unroll
-    for (int k = 0; k < kTopBlocks; ++k) {
+    for (int k = 0; k < kTopGroups; ++k) {
       const float x = fmaxf(v[k] - t, 0.f);
       const float g = x > 0.f ? pow_rm1<AM>(x, r) : 0.f;
       f = fmaf(g, x, f);
@@ -388,125 +597,206 @@ __device__ __forceinline__ float top_blocks_bound(const TopBlocks& top, const Bl
   return a > 1.0e-30f ? fmaxf(lo, t - 4e-6f * fmaxf(1.0f, fabsf(t))) : lo;
 }
 
-template <typename T, int D, int AM, bool BIAS>
-__device__ __forceinline__ void fwd_lists_block(const FwdSparseArgs& A, int bh_, int blk_, char* smem, int strip_no = -1) {
-  using C = QCtx<T, D, ListCfg<T, D>::kTile, BIAS>;
-  constexpr int KT = C::KT, NSB = C::NSB, TB = C::kTileBytes;
-  const Geom& g = A.g;
-  char* tiles = smem;  // 2 buffers x 1 slot
-  int* ovf = reinterpret_cast<int*>(smem + 2 * TB);  // sticky overflow flags: [0], [1] by tile parity, [2] list; [3] pool_want()
-  int* votes = ovf + 4;                              // the waves' votes (see below)
-  char* lds_cells = smem + 2 * TB + kListHeaderBytes;
-  using Cfg = ListCfg<T, D>;
-  if (threadIdx.x < kListHeaderBytes / 4) ovf[threadIdx.x] = 0;
+// Counters only: how many different 32-key blocks the wave's lanes' first ne entries name.
+template <int G>
+__device__ __forceinline__ unsigned distinct_blocks(const TopGroups<G>& top, const GroupNumbers<G>& gn, int ne, int lane) {
+  unsigned n = 0;
+  int mine[kTopGroups];
+#pragma unroll
+  for (int k = 0; k < kTopGroups; ++k) mine[k] = k < ne ? (int)((__float_as_uint(top.t[k]) & ~gn.keep) / GroupNumbers<G>::kPerBlock) : -1;
+#pragma unroll 1
+  for (int l = 0; l < 64; ++l) {
+#pragma unroll
+    for (int k = 0; k < kTopGroups; ++k) {
+      const int jb = __builtin_amdgcn_readlane(mine[k], l);
+      if (jb < 0) continue;
+      ++n;  // counted once: every lane's further entries of the block are struck out
+#pragma unroll
+      for (int e = 0; e < kTopGroups; ++e) mine[e] = mine[e] == jb ? -1 : mine[e];
+    }
+  }
+  return n;
+}
 
-  C q;
-  q.init(g, A.Q, bh_, blk_);
-  q.init_window(g);
-  uint32_t* words = reinterpret_cast<uint32_t*>(lds_cells + (size_t)Cfg::kLdsCells * kThreads * 20) + q.wave * Cfg::kMarkWords;
+// Lanes that remember too few groups, up to kScanLanes of a block: every key their row sees is looked at, a quarter of them by each wave,
+// and what the waves find is put together in the keys' order.  (32 such rows at a time on the matrix cores, the keys shared out to the waves,
+// takes longer for the few that there are: n 1024 44 -> 56 us.)
+constexpr int kScanLanes = 8;
+struct ScanLds {
+  int lost_of_wave[kWaves];  // and, above 16 bits, how many entries of the wave's other lanes name a group to rescore
+  int lane[kScanLanes];  // thread of the workgroup
+  float cut[kScanLanes], w[kScanLanes];
+  int negated[kScanLanes];
+  int found[kScanLanes][kWaves];
+};
+static_assert(sizeof(ScanLds) == kScanBytes, "its place in LDS");
+// notes: [kScanLanes][kWaves][kCandCap] of LDS; kt_first: key tiles before it are not looked at
+template <typename C, typename T, int D, int G>
+__device__ __forceinline__ int scan_lanes(const FwdSparseArgs& A, const C& q, int nlost, int first_group, ScanLds* sl, uint2* notes) {
+  using O = OctetScores<C, T, D, G>;
+  constexpr int N = O::W == 1 ? 2 : 1;
+  const Geom& g = A.g;
+  const O o(q, g, A.Q, A.K);
+  const int oct = q.lane >> 3;
+#pragma unroll 1
+  for (int x = 0; x < nlost; ++x) {
+    const int id = __builtin_amdgcn_readfirstlane(sl->lane[x]);
+    typename O::Row row[N];
+    row[0] = o.row_of(q.qb * kBlockRows + (id >> 6) * 32 + (id & 31), sl->cut[x], sl->negated[x] != 0, sl->w[x]);
+    if (N > 1) row[N - 1] = row[0];
+    const int end = ((row[0].lim + 31) >> 5) * O::P;
+    const int share = ((end - first_group + kWaves * 8 - 1) / (kWaves * 8)) * 8;
+    const int from = first_group + q.wave * share, to = min(end, from + share);
+    int total = 0;
+#pragma unroll 1
+    for (int n0 = from; n0 < to; n0 += 8 * N) {
+      int j0[N];
+#pragma unroll
+      for (int u = 0; u < N; ++u) j0[u] = O::first_key(n0 + 8 * u + oct, (id >> 5) & 1);
+#pragma unroll
+      for (int r0 = 0; r0 < G; r0 += 8) {
+        float d[N];
+        o.eight(row, j0, r0, d);
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+          const int j = o.key(j0[u], r0);
+          const bool pass = n0 + 8 * u + oct < to && j < row[u].lim && d[u] > row[u].cut;
+          const unsigned long long all = __ballot(pass);
+          if (all == 0ull) continue;
+          const int at = total + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(all >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)all, 0u));
+          if (pass && at < kCandCap) notes[(x * kWaves + q.wave) * kCandCap + at] = make_uint2((unsigned)j, __float_as_uint(d[u]));
+          total += (int)__popcll(all);
+        }
+      }
+    }
+    if (q.lane == 0) sl->found[x][q.wave] = total;
+  }
+  __syncthreads();
+  int cnt = -1;  // the lane's own count, if it is one of them
+#pragma unroll 1
+  for (int x = 0; x < nlost; ++x) {
+    const int id = sl->lane[x];
+    int before = 0, total = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      const int n = sl->found[x][w];
+      if (w < q.wave) before += n;
+      total += n;
+    }
+    uint2* list = A.cand + list_entry<kCandCap>(q.bh, A.nqb, q.qb, id >> 6, id & 63);
+    if (q.lane < sl->found[x][q.wave] && before + q.lane < kCandCap)
+      list[(before + q.lane) * kListStride] = notes[(x * kWaves + q.wave) * kCandCap + min(q.lane, kCandCap - 1)];
+    if (id == q.tid) cnt = total;
+  }
+  return cnt;
+}
+
+// Groups to rescore in a wave from which on the second sweep is taken instead: kStart, and kPerTile for every 128 keys of the block.
+// Measured (kernel, never / 160 + 6 / 48 + 24 / 24 + 12): B 4, H 12, n 4096, alpha 1.25 220 / 195 / 221 / 196 us; per-query scales, B 3, n 1999, bias
+// 128 / 109 / 128 / 108; B 8, n 1024, alpha 1.5 41 / 41 / 41 / 54; n 4096 93 / 94 / 93 / 98.  fp32, one head of 256, scale 1: 45 us without, 40 with 24 + 24.
+template <typename T, int D>
+struct SweepAgain {
+  static constexpr int kStart = sizeof(T) == 2 ? 160 : 48;
+  static constexpr int kPerTile = sizeof(T) == 2 ? 6 : 24;
+};
+
+// What follows the sweep over the scores of a block: the rows' bounds, the scores of the keys that can matter, the lists.
+// m1: the lane's largest score; n_vis: blocks the wave computed; places: of the sweep's memory that were kept throughout.  All threads of the workgroup; the tile buffers are free.
+template <typename C, typename T, int D, int AM, int G, int LS, bool RING>
+__device__ __forceinline__ void make_lists(const FwdSparseArgs& A, const C& q, TopGroups<G>& top, float m1, char* smem, int strip_no,
+                                           unsigned n_vis, int places) {
+  const Geom& g = A.g;
+  int* ovf = reinterpret_cast<int*>(smem + ListCfg<T, D>::kFwdTiles);
+  char* lds_cells = smem + ListCfg<T, D>::kFwdTiles + kListHeaderBytes + sizeof(ScanLds);
+  const GroupNumbers<G> gn(g.Nk);
   const int flag_idx = q.bh * A.nqb + q.qb;
   const long long row_idx = (long long)q.bh * g.Nq + (q.valid ? q.i : 0);
   const bool live = q.valid && q.lim > 0;
-
-  if (q.block_lim == 0) {  // no row of this workgroup sees any key: the finish kernel writes the zeros
-    if (q.valid) {
-      A.lcnt[row_idx * 2 + q.hh] = 0;
-      if (q.hh == 0) A.bounds[row_idx] = make_float2(0.f, 0.f);
-    }
-    if (q.tid == 0) A.dense_flag[flag_idx] = 0;
-    return;
-  }
-
-  Slot slots[1];
-  slots[0].base = reinterpret_cast<const char*>(reinterpret_cast<const T*>(A.K) + (long long)q.b * g.kv_sb +
-                                                (long long)q.h * g.kv_sh);
-  slots[0].row_bytes = g.kv_sn * (long long)sizeof(T);
-  unsigned n_vis = 0, n_qk2 = 0, n_cand_tiles = 0;
-
-  // ---------------------------------------------- 1. row max and runner-up
-  float m1 = -kInf;
-  const BlockNumbers bn(g.Nk);
-  TopBlocks top;
-  top.init();
-  // the bracket's width in raw units, a little wider than needed (rounding)
-  const float reach = (q.valid && q.lim > 0) ? (q.a > 0.f ? 1.0001f / q.a : 3.0e38f) : -kInf;
-  // Dense rows are found out on the first tile: where, for three quarters of a wave's rows, half of the keys of
-  // the tile's first block come within the bracket's width of the block's largest score, the lists would overflow anyway (a row of
-  // the paper's sparse setting has a handful of such keys).  A block all of whose waves vote so is handed to the
-  // tiled kernel after two tiles instead of after a full sweep (a matter of time only: the tiled kernel handles
-  // any row).
-  int kt_vote = 0;  // the first tile of the sweep
-  if constexpr (BIAS) kt_vote = q.kt_first;
-  auto max_body = [&](int kt, const char* tl) {
-        if (!q.tile_in_wave_window(kt)) return;
-        if ((kt + 1) * KT <= q.wave_lim_min) {
-          f32x16_t acc[NSB];
-          q.scores_all(tl, acc, kt);
-#pragma unroll
-          for (int sb = 0; sb < NSB; ++sb) {
-            float lm = max16(acc[sb]);
-            if (sb == 0 && kt == kt_vote) {  // the vote, on the lane's 16 keys of the tile's first block
-              int near = 0;
-#pragma unroll
-              for (int e = 0; e < 16; ++e) near += (acc[0][e] + reach > lm) ? 1 : 0;
-              if (__popcll(__ballot(near >= 8)) >= 48 && q.lane == 0) votes[q.wave] = 1;
-            }
-            m1 = fmaxf(m1, lm);
-            top.take(lm, bn, kt * NSB + sb);
-          }
-          n_vis += NSB;
-        } else {
-          const uint32_t act = q.visible_bits(kt);
-#pragma unroll
-          for (int sb = 0; sb < NSB; ++sb) {
-            if (!(act & (1u << sb))) continue;
-            int j0 = kt * KT + sb * 32;
-            f32x16_t acc = q.scores(tl, sb, kt);
-            ++n_vis;
-            if (j0 + 32 > q.wave_lim_min) {
-              int rel = q.lim - j0;
-#pragma unroll
-              for (int e = 0; e < 16; ++e) acc[e] = (q.key_of(e) < rel) ? acc[e] : -kInf;
-            }
-            float lm = max16(acc);
-            m1 = fmaxf(m1, lm);
-            top.take(lm, bn, kt * NSB + sb);
-          }
-        }
-      };
-  auto all_dense = [&]() { return (votes[0] & votes[1] & votes[2] & votes[3]) != 0; };
-  sweep_tiles<C, T, D, 1, 0, ListCfg<T, D>::kDepth>(
-      tiles, slots, q.ntiles, g.Nk, q.tid, [&](int kt) { return q.tile_in_window(kt); }, max_body,
-      // (the votes of a tile are final before the barrier that ends it)
-      [&](int kt) { return kt == kt_vote + 1 && all_dense(); });
-  if (all_dense()) {  // (the sweep ended on a barrier)
-    __syncthreads();  // every thread has read the votes before the next block's zeroes them
-    if (q.tid == 0) A.dense_flag[flag_idx] = kFlagDense;
-    if (A.stats && q.lane == 0) atomicAdd(&A.stats[ENTMAX_STAT_FWD_LIST_QK], (unsigned long long)n_vis);
-    return;
-  }
+  const float r = 1.0f / (g.alpha - 1.0f);
   m1 = fmaxf(m1, __shfl_xor(m1, 32));
-  const float m2 = top.runner_up(bn);
+  const float m2 = top.runner_up(gn);
   const float y1 = live ? q.a * m1 : 0.f;
   float lo = y1 - 1.0f;  // App. A eq. (bounds), left end
   float hi = live ? y1 - __builtin_amdgcn_exp2f(-(g.alpha - 1.0f) * __builtin_amdgcn_logf((float)q.lim)) : 0.f;
   // two-element sub-problem {y1, y2}: its threshold is a lower bound of the row's
-  if (live && m2 > -2.9e38f) lo = two_key_bound<AM>(y1, q.a * m2, 1.0f / (g.alpha - 1.0f));
+  if (live && m2 > -2.9e38f) lo = two_key_bound<AM>(y1, q.a * m2, r);
   // Rows of at most three blocks keep the two-key bound.  Not for speed: short rows that keep most of their keys then reach
   // the tiled kernel, whose smallest cases the tests are made of.  Training steps with the limit at 96, without one and
   // at 192: B 8, H 12, n 96 124, 106 and 123 us; n 160 152, 147, 187; B 1, H 1, n 256, fp32 151, 150, 256; rows of
   // constant logit range (n 256 to 4096) the same with any.
-  if (live && q.lim > 96) lo = top_blocks_bound<AM>(top, bn, q.a, lo, 1.0f / (g.alpha - 1.0f));
+  if (live && q.lim > 96) lo = top_groups_bound<AM>(top, gn, q.a, lo, r);
   lo = fminf(lo, hi);
+  const float cut = raw_cut(q.a, live, lo);
 
-  // ---------------------------------------------- 2. candidate lists at tau_lb
-  uint2* mylist = A.cand + list_entry<kCandCap>(q.bh, A.nqb, q.qb, q.wave, q.lane);
+  // A lane whose last place is above the cut may have lost groups that count.  Where there are few of them in the block all their
+  // keys are looked at (scan_lanes()); where there are more, a second sweep over the scores of the block finds their keys, in which
+  // the other lanes look for nothing (but in a wave most of whose lanes are lost, all of them do).
+  int first = 0;
+  if constexpr (C::BIAS) first = q.kt_first_wave * C::NSB;
+  const int seen = (((q.wave_lim_max + 31) >> 5) - first) * GroupNumbers<G>::kPerBlock;
+  int ne = live ? top.above(cut, gn) : 0;
+  bool lost = ne >= places && seen > places;
+  const unsigned long long lost_lanes = __ballot(lost);
+  ScanLds* sl = reinterpret_cast<ScanLds*>(ovf + kListHeaderBytes / 4);
+  int items = 0;  // at most 64 kTopGroups
+#pragma unroll
+  for (int k = 0; k < 4; ++k) items += (int)__popcll(__ballot(!lost && ((ne >> k) & 1) != 0)) << k;
+  if (q.lane == 0) sl->lost_of_wave[q.wave] = (int)__popcll(lost_lanes) | items << 16;
+  __syncthreads();  // (also: the tile buffers are free)
+  int lost_before = 0, nlost = 0, most = 0;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    const int n = sl->lost_of_wave[w];
+    if (w < q.wave) lost_before += n & 0xffff;
+    nlost += n & 0xffff;
+    most = max(most, n >> 16);
+  }
+  nlost = __builtin_amdgcn_readfirstlane(nlost);
+  most = __builtin_amdgcn_readfirstlane(most);
+  // Rescoring goes by the wave with the most groups, the second sweep by the keys: in short rows that keep many keys the sweep is cheaper.
+  using Again = SweepAgain<T, D>;
+  const bool all_again = most > Again::kStart + ((q.block_lim - first * 32) >> 7) * Again::kPerTile;
+  if (all_again) nlost = kThreads;
+  if (lost && nlost <= kScanLanes) {
+    const int x = lost_before + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(lost_lanes >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)lost_lanes, 0u));
+    sl->lane[x] = q.tid;
+    sl->cut[x] = cut;
+    sl->negated[x] = q.c < 0.f ? 1 : 0;
+    if constexpr (C::BIAS) sl->w[x] = q.w; else sl->w[x] = 0.f;
+  }
+  if (all_again || (nlost > kScanLanes && __popcll(lost_lanes) >= 32)) lost = live;
+  if (lost) ne = 0;
+  uint2* wave_list = A.cand + list_entry<kCandCap>(q.bh, A.nqb, q.qb, q.wave, 0);
   int cnt = 0;
-  mark_blocks(q, top, bn, raw_cut(q.a, live, lo), words, min((((q.block_lim + 31) >> 5) + 31) >> 5, Cfg::kMarkWords));
-  const bool fits = collect_sweep<C, T, D, kCandCap, Cfg::kLdsCells>(q, g, A.K, tiles, ovf, lds_cells, live, lo, A.cells, mylist, cnt,
-                                                                     n_qk2, n_cand_tiles, words, strip_no);
+  unsigned n_qk2 = 0, n_cand_tiles = 0;
+  if (A.stats) n_cand_tiles = distinct_blocks<G>(top, gn, lost && nlost <= kScanLanes ? places : ne, q.lane);
+  if (!rescore_groups<C, T, D, G>(q, g, A.Q, A.K, top, gn, cut, ne, reinterpret_cast<int*>(smem) + q.wave * kRescoreWords, wave_list, cnt))
+    ovf[2] = 1;
+  if (nlost > 0) {
+    __syncthreads();
+    if (ovf[2] == 0 && nlost <= kScanLanes) {
+      const int found = scan_lanes<C, T, D, G>(A, q, nlost, first * GroupNumbers<G>::kPerBlock, sl, reinterpret_cast<uint2*>(smem));
+      if (found >= 0) {
+        if (found > kCandCap) ovf[2] = 1;
+        cnt = min(found, kCandCap);
+        if (A.stats) atomicAdd(&A.stats[ENTMAX_STAT_FWD_CAND_TILES], (unsigned long long)max(cnt - places, 0));  // (at most)
+      }
+    }
+  }
+  bool fits;
+  if (nlost > kScanLanes && ovf[2] == 0) {  // (not written since the barrier)
+    C qs;  // (made again: kept through what comes before, the query fragments and offsets would be spilled)
+    qs.init(g, A.Q, q.bh, q.qb);
+    qs.init_window(g);
+    fits = collect_sweep<C, T, D, kCandCap, LS, RING>(qs, g, A.K, smem, ovf, lds_cells, lost ? cut : kInf, A.cells, wave_list + q.lane, cnt,
+                                                n_qk2, n_cand_tiles, __ballot(lost) != 0ull, strip_no);
+  } else {
+    pool_want(ovf + 3, cnt, q.lane);
+    __syncthreads();
+    fits = ovf[2] == 0;
+  }
   if (!fits) {
-    // the tiled kernel takes the block, and with it what the first sweep found out about every row
+    // the tiled kernel takes the block, and with it what the sweep found out about every row
     if (q.tid == 0) A.dense_flag[flag_idx] = kFlagWithBounds;
     if (q.valid && q.hh == 0) A.bounds[row_idx] = make_float2(lo, y1);
   } else {
@@ -519,7 +809,7 @@ __device__ __forceinline__ void fwd_lists_block(const FwdSparseArgs& A, int bh_,
   if (A.stats && q.lane == 0) {
     const unsigned n_win = q.window_skipped_blocks();
     atomicAdd(&A.stats[ENTMAX_STAT_FWD_TILES_VISIBLE], (unsigned long long)(n_vis + n_win));
-    if (BIAS) atomicAdd(&A.stats[ENTMAX_STAT_FWD_WINDOW_SKIPPED], (unsigned long long)n_win);
+    if (C::BIAS) atomicAdd(&A.stats[ENTMAX_STAT_FWD_WINDOW_SKIPPED], (unsigned long long)n_win);
     atomicAdd(&A.stats[ENTMAX_STAT_FWD_LIST_QK], (unsigned long long)(n_vis + n_qk2));
     if (fits) {
       atomicAdd(&A.stats[ENTMAX_STAT_FWD_CAND_TILES], (unsigned long long)n_cand_tiles);
@@ -528,8 +818,253 @@ __device__ __forceinline__ void fwd_lists_block(const FwdSparseArgs& A, int bh_,
   }
 }
 
+// The sweep over the scores and what follows it, for R adjacent query blocks from block blk on: every wave holds its 32-row
+// group of each of them, so that with two a K fragment read from LDS feeds two matrix instructions and a K tile staged
+// through LDS serves 256 rows.
+// One sweep and rescored groups instead of two sweeps (kernel time, causal, alpha 1.5): B 8, H 12, n 1024, D 64 47 -> 41 us; B 4, H 12,
+// n 4096 136 -> 94; B 2, H 16, n 8192, D 128 530 -> 357; B 1, H 12, n 32768 (two blocks a workgroup) 1275 -> 880; B 2, H 16, n 5003,
+// D 128, alpha 2 245 -> 150.  Of the 94 us the sweep is 57 (its matrix instructions alone would take 21, its vector instructions 25: a
+// SIMD's three waves share one issue slot, and alone on its CU a workgroup needs 0.7 us a tile), the rescoring 21.  What was in the way before: the second sweep's branches around every block with a candidate (82 us).
+// Sixteen keys a group instead of eight: the sweep 6 us less, the rescoring's reads doubled, 94 -> 104 us.
+template <typename T, int D, int AM, bool BIAS, int R>
+__device__ __forceinline__ void fwd_lists_blocks(const FwdSparseArgs& A, int bh_, int blk, char* smem, int strip_no) {
+  using C = QCtx<T, D, ListCfg<T, D>::kTile, BIAS>;
+  using Cfg = ListCfg<T, D>;
+  using KTile = typename C::KTile;
+  constexpr int KT = C::KT, NSB = C::NSB, NC = C::NC;
+  const Geom& g = A.g;
+  int* ovf = reinterpret_cast<int*>(smem + Cfg::kFwdTiles);  // sticky overflow flags: [0], [1] by tile parity, [2] list; [3] pool_want()
+  int* votes = ovf + 4;                                      // the waves' votes (see below)
+  const int tid = threadIdx.x;
+  if (tid < kListHeaderBytes / 4) ovf[tid] = 0;  // (first barrier: init_window's or the sweep's)
+
+  C q[R];
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    q[k].init(g, A.Q, bh_, blk + k);
+    q[k].init_window(g);
+  }
+  if (q[R - 1].block_lim == 0) {  // no row of any block sees any key: the finish kernel writes the zeros
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      const long long row_idx = (long long)q[k].bh * g.Nq + (q[k].valid ? q[k].i : 0);
+      if (q[k].valid) {
+        A.lcnt[row_idx * 2 + q[k].hh] = 0;
+        if (q[k].hh == 0) A.bounds[row_idx] = make_float2(0.f, 0.f);
+      }
+      if (tid == 0) A.dense_flag[q[k].bh * A.nqb + q[k].qb] = 0;
+    }
+    return;
+  }
+  // tiles first .. ntiles - 1, those before whole_end wholly visible to every row
+  const int ntiles = q[R - 1].ntiles;  // a later block sees at least the keys of the earlier one
+  const int whole_end = __builtin_amdgcn_readfirstlane(row_limit(g, q[0].qb * kBlockRows) / KT);
+  int first = 0;
+  bool biased = false;  // (of the head: the same for all waves)
+  if constexpr (BIAS) {
+    first = q[0].kt_first;
+#pragma unroll
+    for (int k = 1; k < R; ++k) first = min(first, q[k].kt_first);
+#pragma unroll
+    for (int k = 0; k < R; ++k) q[k].kt_first = q[k].kt_first_wave = first;  // (the waves go through the tiles together)
+    biased = g.slopes[q[0].h] != 0.f;
+  }
+  Slot slots[1];
+  slots[0].base = reinterpret_cast<const char*>(reinterpret_cast<const T*>(A.K) + (long long)q[0].b * g.kv_sb +
+                                                (long long)q[0].h * g.kv_sh);
+  slots[0].row_bytes = g.kv_sn * (long long)sizeof(T);
+
+  const GroupNumbers<Cfg::kGroup> gn(g.Nk);
+  using Top = TopGroups<Cfg::kGroup>;
+  Top top[R];
+  float m1[R];
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    top[k].init();
+    m1[k] = -kInf;
+  }
+
+  // Dense rows are found out on the first tile: where, for three quarters of a wave's rows, half of the keys of
+  // the tile's first block come within the bracket's width of the block's largest score, the lists would overflow anyway (a row of
+  // the paper's sparse setting has a handful of such keys).  Blocks all of whose waves vote so are handed to the
+  // tiled kernel after that one block of scores (fp32: two tiles) instead of after a full sweep (a matter of time only: the tiled
+  // kernel handles any row).
+  auto vote = [&](const C& qk, const f32x16_t& acc, float lm) -> bool {
+    // the bracket's width in raw units, a little wider than needed (rounding)
+    const float reach = (qk.valid && qk.lim > 0) ? (qk.a > 0.f ? 1.0001f / qk.a : 3.0e38f) : -kInf;
+    int near = 0;  // of the lane's 16 keys of the tile's first block
+#pragma unroll
+    for (int e = 0; e < 16; ++e) near += (acc[e] + reach > lm) ? 1 : 0;
+    return __popcll(__ballot(near >= 8)) >= 48;
+  };
+  auto all_dense = [&]() { return (votes[0] & votes[1] & votes[2] & votes[3]) != 0; };
+  auto vote_on = [&](int kt, const char* tl) {
+    bool dense = true;
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      const f32x16_t acc = q[k].scores(tl, 0, kt);
+      dense = vote(q[k], acc, max16(acc)) && dense;
+    }
+    if (dense && q[0].lane == 0) votes[q[0].wave] = 1;
+  };
+  // any tile, one 32-key block after the other
+  auto general = [&](int kt, const char* tl) {
+    if (!Cfg::kRing && kt == first && kt < whole_end) vote_on(kt, tl);
+#pragma unroll 1
+    for (int sb = 0; sb < NSB; ++sb) {
+      const int j0 = kt * KT + sb * 32;
+#pragma unroll
+      for (int k = 0; k < R; ++k) {
+        if (j0 >= q[k].wave_lim_max) continue;
+        f32x16_t acc = q[k].scores(tl, sb, kt);
+        if (j0 + 32 > q[k].wave_lim_min) mask_block(q[k], acc, j0);
+        m1[k] = fmaxf(m1[k], top[k].take(acc, gn, kt * NSB + sb));
+      }
+    }
+  };
+  int places = kTopGroups;
+  if constexpr (!Cfg::kRing) {
+    sweep_tiles<C, T, D, 1, 0, Cfg::kDepth>(
+        smem, slots, ntiles, g.Nk, tid, [&](int kt) { return kt >= first; }, general,
+        // (the votes of a tile are final before the barrier that ends it)
+        [&](int kt) { return kt == first + 1 && all_dense(); });
+  } else {
+    TileRing<C, T, D> ring;
+    ring.start(smem, slots[0], first, ntiles, g.Nk);
+    // Tiles all of whose keys every row sees.  The matrix instructions of a block run beside the vector work on the scores of
+    // the one before it (with two query blocks: of the other query block), which needs two accumulators; the last one waits
+    // over the barrier for the next tile.  A K fragment is requested when the one before it in its place has been used.
+    auto whole_tiles = [&](auto biased_, auto places_) {
+      constexpr int K = decltype(places_)::value;
+      f32x16_t late;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) late[e] = -kInf;
+      int late_jb = 0;
+      float late_floor = Top::kNothing;  // (nothing waits)
+      auto pipelined = [&](int kt, const char* tl) {
+        constexpr int F = 4;  // fragments in registers
+        Frag<T> kf[F];
+#pragma unroll
+        for (int cc = 0; cc < F; ++cc) kf[cc] = q[0].koff[cc].load(tl, 0);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int sb = 0; sb < NSB; ++sb) {
+#pragma unroll
+          for (int k = 0; k < R; ++k) {
+            const int kl = k == 0 ? R - 1 : k - 1;  // the query block whose scores wait
+            const int j0 = kt * KT + sb * 32;
+            float m[Top::Numbers::kPerBlock], x[Top::Numbers::kPerBlock];
+            f32x16_t acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            if constexpr (decltype(biased_)::value) q[k].bias_before(acc, j0);
+#pragma unroll
+            for (int cc = 0; cc < NC; ++cc) {
+              acc = Elem<T>::mma(kf[cc % F], q[k].qf[cc], acc);
+              // what this place holds next: a later fragment of the block, its first ones again, or the next block's
+              const int nx = cc + F;
+              if (nx < NC)
+                kf[cc % F] = q[0].koff[nx].load(tl, sb * 32 * KTile::kRowBytes);
+              else if (k + 1 < R) {
+                if (NC > F) kf[cc % F] = q[0].koff[nx - NC].load(tl, sb * 32 * KTile::kRowBytes);
+              } else if (sb + 1 < NSB)
+                kf[cc % F] = q[0].koff[nx - NC].load(tl, (sb + 1) * 32 * KTile::kRowBytes);
+              __builtin_amdgcn_sched_barrier(0);  // (the order is the point: left to itself the compiler issues all products first)
+              if (cc == 0) top[kl].template take_part<0, K>(late, gn, late_jb, late_floor, m, x, m1[kl]);
+              if (cc == NC / 4) top[kl].template take_part<1, K>(late, gn, late_jb, late_floor, m, x, m1[kl]);
+              if (cc == 2 * NC / 4) top[kl].template take_part<2, K>(late, gn, late_jb, late_floor, m, x, m1[kl]);
+              if (cc == 3 * NC / 4) top[kl].template take_part<3, K>(late, gn, late_jb, late_floor, m, x, m1[kl]);
+              __builtin_amdgcn_sched_barrier(0);
+            }
+            late = acc;
+            late_jb = j0 >> 5;
+            late_floor = Top::kFloor;
+          }
+        }
+#pragma unroll
+        for (int k = 0; k < R; ++k) {  // (all of it happens here: the compiler moves what it can behind the next branch)
+#pragma unroll
+          for (int e = 0; e < K; ++e) asm volatile("" : "+v"(top[k].t[e]));
+          asm volatile("" : "+v"(m1[k]));
+        }
+      };
+#pragma unroll 1
+      while (ring.kt < whole_end) {
+        ring.step([&](const char* tl) { pipelined(ring.kt, tl); });
+      }
+      m1[R - 1] = fmaxf(m1[R - 1], top[R - 1].take(late, gn, late_jb, late_floor));
+    };
+    bool weak = false;
+#pragma unroll
+    for (int k = 0; k < R; ++k)
+      weak = weak || (q[k].valid && q[k].lim > 0 && !(q[k].a * sqrtf((float)D) >= kFewPlacesScale));
+    if (__ballot(weak) == 0ull) places = kFewPlaces;
+    auto both = [&](auto biased_) {
+      if (places == kFewPlaces)
+        whole_tiles(biased_, std::integral_constant<int, kFewPlaces>());
+      else
+        whole_tiles(biased_, std::integral_constant<int, kTopGroups>());
+    };
+    if (first < whole_end) {
+      vote_on(first, smem);
+      __syncthreads();
+    }
+    if (all_dense()) {
+      ring.abandon();
+    } else {
+      if (!BIAS || !biased) {
+        both(std::false_type());
+      } else if constexpr (BIAS) {
+        if (g.causal) both(std::true_type());  // (every key of such a tile lies at or before every row's position)
+      }
+      while (ring.kt < ntiles) ring.step([&](const char* tl) { general(ring.kt, tl); });
+    }
+  }
+  // blocks the waves have computed
+  unsigned n_vis[R];
+#pragma unroll
+  for (int k = 0; k < R; ++k) n_vis[k] = (unsigned)max(((q[k].wave_lim_max + 31) >> 5) - first * NSB, 0);
+  if (all_dense()) {  // (the sweep ended on a barrier)
+    __syncthreads();  // every thread has read the votes before the next block's zeroes them
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      if (tid == 0) A.dense_flag[q[k].bh * A.nqb + q[k].qb] = kFlagDense;
+      if (A.stats && q[k].lane == 0)
+        atomicAdd(&A.stats[ENTMAX_STAT_FWD_LIST_QK], (unsigned long long)Cfg::kRing ? 1ull : (unsigned long long)min(n_vis[k], 2u * NSB));
+    }
+    return;
+  }
+  if constexpr (R == 1) {
+    make_lists<C, T, D, AM, Cfg::kGroup, Cfg::kFwdCells, Cfg::kRing>(A, q[0], top[0], m1[0], smem, strip_no, n_vis[0], places);
+  } else {
+    // What is left is done for one block after the other; what the sweep found out about the second waits in LDS, in the third
+    // tile buffer (which nothing else uses now), so that only one block's rows are in registers.
+    static_assert(Cfg::kRing && R == 2 && kTopGroups * kThreads * 4 <= C::kTileBytes, "a tile buffer holds a block's entries");
+    float* stash = reinterpret_cast<float*>(smem + 2 * C::kTileBytes) + tid;  // [kTopGroups][kThreads]
+    Top tk = top[0];
+#pragma unroll
+    for (int e = 0; e < kTopGroups; ++e) stash[e * kThreads] = top[1].t[e];
+    const float m_first = m1[0], m_last = m1[R - 1];
+    const unsigned n_first = n_vis[0], n_last = n_vis[R - 1];
+#pragma unroll 1
+    for (int k = 0; k < R; ++k) {
+      if (k) {
+        __syncthreads();  // (every thread is done with the first block's words)
+        if (tid < kListHeaderBytes / 4) ovf[tid] = 0;
+        __syncthreads();
+      }
+      C qk;
+      qk.init(g, A.Q, bh_, blk + k);
+      if constexpr (BIAS) qk.kt_first = qk.kt_first_wave = first;
+      if (k) {
+#pragma unroll
+        for (int e = 0; e < kTopGroups; ++e) tk.t[e] = stash[e * kThreads];
+      }
+      make_lists<C, T, D, AM, Cfg::kGroup, Cfg::kFwdCells, false>(A, qk, tk, k ? m_last : m_first, smem, strip_no + k, k ? n_last : n_first, places);
+    }
+  }
+}
+
 template <typename T, int D, int AM, bool BIAS>
-__global__ __launch_bounds__(kThreads, (ListCfg<T, D>::kOcc)) void fwd_lists_kernel(FwdSparseArgs A) {
+__global__ __launch_bounds__(kThreads, (ListCfg<T, D>::kFwdOcc)) void fwd_lists_kernel(FwdSparseArgs A) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   PairItem it;
   if (A.unpaired) {  // a head's blocks on one XCD, the longest first
@@ -556,245 +1091,14 @@ __global__ __launch_bounds__(kThreads, (ListCfg<T, D>::kOcc)) void fwd_lists_ker
     const int blk = part ? it.second : it.first;
     if (blk < 0) break;
     if (part) __syncthreads();
-    fwd_lists_block<T, D, AM, BIAS>(A, it.bh, blk, smem);
+    fwd_lists_blocks<T, D, AM, BIAS, 1>(A, it.bh, blk, smem, (int)blockIdx.x);
   }
 }
 
 // ------------------------------------------------- long sequences: two query blocks per workgroup
-// The same two sweeps as fwd_lists_block for the adjacent blocks 2 sblk and 2 sblk + 1 at once:
-// every wave holds its 32-row group of both blocks (64 query rows), so that a K fragment read from LDS feeds two
-// matrix instructions and a K tile staged through LDS serves 256 rows.  Each block keeps its own lists, flags, bounds and
-// block bits.  Two block memories (TopBlocks) do not fit the registers beside that (184 spills: 4.3 ms at n 32768), so the bound
-// is the two-key one and the first sweep sets a block's bit where some lane's largest score of it comes within the
-// bracket's width of that lane's running maximum (half of the blocks at n 32768).  Used where the launch still fills the
-// chip with half as many workgroups (Nk >= ListCfg::kPairMinKeys).
-template <typename T, int D>
-struct PairCfg {
-  using Cfg = ListCfg<T, D>;
-  static constexpr int kLdsCells = 1;   // cells per thread and block kept in LDS
-  static constexpr int kFlagWords = 64; // block bits per wave and block: 65536 keys
-  static constexpr size_t kLdsBytes = 2 * (size_t)Cfg::kTile * D * sizeof(T) + 32 + 2 * (size_t)kLdsCells * kThreads * 20 +
-                                      2 * (size_t)kWaves * kFlagWords * 4;
-};
-
+// Used where the launch still fills the chip with half as many workgroups (Nk >= ListCfg::kPairMinKeys).
 template <typename T, int D, int AM, bool BIAS>
-__device__ __forceinline__ void fwd_lists_pair(const FwdSparseArgs& A, int bh_, int sblk, char* smem) {
-  using C = QCtx<T, D, ListCfg<T, D>::kTile, BIAS>;
-  using P = PairCfg<T, D>;
-  using KTile = typename C::KTile;
-  constexpr int KT = C::KT, NSB = C::NSB, NC = C::NC, TB = C::kTileBytes, LS = P::kLdsCells, W = P::kFlagWords;
-  constexpr uint32_t kAll = (1u << NSB) - 1u;
-  const Geom& g = A.g;
-  char* tiles = smem;
-  int* ovf = reinterpret_cast<int*>(smem + 2 * TB);  // [2 blocks][3], see collect_sweep; [6], [7]: the blocks' pool_want()
-  char* lds_cells = smem + 2 * TB + 32;
-  uint32_t* allbits = reinterpret_cast<uint32_t*>(lds_cells + 2 * (size_t)LS * kThreads * 20);  // [2][kWaves][W]
-  for (int w = threadIdx.x; w < 2 * kWaves * W; w += kThreads) allbits[w] = 0u;
-  if (threadIdx.x < 8) ovf[threadIdx.x] = 0;  // (first barrier: init_window's or the first sweep's)
-
-  C q[2];
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    q[k].init(g, A.Q, bh_, 2 * sblk + k);
-    q[k].init_window(g);
-  }
-  const int tid = q[0].tid, wave = q[0].wave, lane = q[0].lane;
-  uint32_t* mybits[2] = {allbits + wave * W, allbits + (kWaves + wave) * W};
-  const int ntiles = q[1].ntiles;  // the later block sees at least the keys of the earlier one
-  bool live[2];
-  long long row_idx[2];
-  int flag_idx[2];
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    live[k] = q[k].valid && q[k].lim > 0;
-    row_idx[k] = (long long)q[k].bh * g.Nq + (q[k].valid ? q[k].i : 0);
-    flag_idx[k] = q[k].bh * A.nqb + q[k].qb;
-  }
-  if (q[1].block_lim == 0) {  // no row of either block sees any key: the finish kernel writes the zeros
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      if (q[k].valid) {
-        A.lcnt[row_idx[k] * 2 + q[k].hh] = 0;
-        if (q[k].hh == 0) A.bounds[row_idx[k]] = make_float2(0.f, 0.f);
-      }
-      if (tid == 0) A.dense_flag[flag_idx[k]] = 0;
-    }
-    return;
-  }
-  Slot slots[1];
-  slots[0].base = reinterpret_cast<const char*>(reinterpret_cast<const T*>(A.K) + (long long)q[0].b * g.kv_sb +
-                                                (long long)q[0].h * g.kv_sh);
-  slots[0].row_bytes = g.kv_sn * (long long)sizeof(T);
-  auto needed = [&](int kt) { return q[0].tile_in_window(kt) || q[1].tile_in_window(kt); };
-  // 32-key blocks of tile kt some row of the wave's group of block k sees
-  auto visible = [&](int k, int kt) -> uint32_t { return q[k].tile_in_wave_window(kt) ? q[k].visible_bits(kt) : 0u; };
-  // the K fragments of a 32-key block, shared by both groups
-  auto load_k = [&](const char* tl, int sb, Frag<T> (&kf)[NC]) {
-#pragma unroll
-    for (int cc = 0; cc < NC; ++cc) kf[cc] = q[0].koff[cc].load(tl, sb * 32 * KTile::kRowBytes);
-  };
-  auto product = [&](int k, const Frag<T> (&kf)[NC], int j0) -> f32x16_t {
-    f32x16_t acc = q[k].block_start(j0);
-#pragma unroll
-    for (int cc = 0; cc < NC; ++cc) acc = Elem<T>::mma(kf[cc], q[k].qf[cc], acc);
-    return acc;
-  };
-  unsigned n_vis[2] = {0u, 0u}, n_qk2[2] = {0u, 0u}, n_cand_tiles[2] = {0u, 0u};
-
-  // ---------------------------------------------- 1. row maxima, runners-up and the block bits
-  float m1[2] = {-kInf, -kInf}, m2[2] = {-kInf, -kInf}, reach[2];
-#pragma unroll
-  for (int k = 0; k < 2; ++k) reach[k] = live[k] ? (q[k].a > 0.f ? 1.0001f / q[k].a : 3.0e38f) : -kInf;
-  sweep_tiles<C, T, D, 1, 0, ListCfg<T, D>::kDepth>(tiles, slots, ntiles, g.Nk, tid, needed, [&](int kt, const char* tl) {
-    uint32_t act[2] = {visible(0, kt), visible(1, kt)};
-    if ((act[0] | act[1]) == 0u) return;
-    uint32_t bits[2] = {0u, 0u};
-    auto take = [&](int k, f32x16_t& acc, int sb) {
-      const int j0 = kt * KT + sb * 32;
-      ++n_vis[k];
-      if (j0 + 32 > q[k].wave_lim_min) mask_block(q[k], acc, j0);
-      const float lm = max16(acc);
-      m2[k] = fmaxf(m2[k], fminf(m1[k], lm));
-      m1[k] = fmaxf(m1[k], lm);
-      if (__ballot(lm + reach[k] > m1[k]) != 0ull) bits[k] |= 1u << sb;
-    };
-    if (act[0] == kAll && act[1] == kAll) {
-      // every block for both groups: the fragments of block sb + 1 are requested before the products of block sb
-      Frag<T> kf[2][NC];
-      load_k(tl, 0, kf[0]);
-#pragma unroll
-      for (int sb = 0; sb < NSB; ++sb) {
-        if (sb + 1 < NSB) load_k(tl, sb + 1, kf[(sb + 1) & 1]);
-        const int j0 = kt * KT + sb * 32;
-        f32x16_t a0 = q[0].block_start(j0), a1 = q[1].block_start(j0);
-#pragma unroll
-        for (int cc = 0; cc < NC; ++cc) {
-          a0 = Elem<T>::mma(kf[sb & 1][cc], q[0].qf[cc], a0);
-          a1 = Elem<T>::mma(kf[sb & 1][cc], q[1].qf[cc], a1);
-        }
-        take(0, a0, sb);
-        take(1, a1, sb);
-      }
-    } else {
-#pragma unroll
-      for (int sb = 0; sb < NSB; ++sb) {
-        if (((act[0] | act[1]) & (1u << sb)) == 0u) continue;
-        Frag<T> kf[NC];
-        load_k(tl, sb, kf);
-        f32x16_t acc[2];  // (both products before the vector work on either)
-#pragma unroll
-        for (int k = 0; k < 2; ++k)
-          if ((act[k] & (1u << sb)) != 0u) acc[k] = product(k, kf, kt * KT + sb * 32);
-#pragma unroll
-        for (int k = 0; k < 2; ++k)
-          if ((act[k] & (1u << sb)) != 0u) take(k, acc[k], sb);
-      }
-    }
-    if ((kt + 1) * NSB <= W * 32 && lane == 0) {  // (each wave writes only its own words)
-#pragma unroll
-      for (int k = 0; k < 2; ++k)
-        if (bits[k] != 0u) mybits[k][(kt * NSB) >> 5] |= bits[k] << ((kt * NSB) & 31);
-    }
-  });
-  float lo[2], hi[2];
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const float p1 = __shfl_xor(m1[k], 32), p2 = __shfl_xor(m2[k], 32);
-    const float top = fmaxf(m1[k], p1);
-    m2[k] = fmaxf(fminf(m1[k], p1), fmaxf(m2[k], p2));
-    m1[k] = top;
-    const float y1 = live[k] ? q[k].a * m1[k] : 0.f;
-    lo[k] = y1 - 1.0f;  // App. A eq. (bounds), left end
-    hi[k] = live[k] ? y1 - __builtin_amdgcn_exp2f(-(g.alpha - 1.0f) * __builtin_amdgcn_logf((float)q[k].lim)) : 0.f;
-    if (live[k] && m2[k] > -kInf) lo[k] = two_key_bound<AM>(y1, q[k].a * m2[k], 1.0f / (g.alpha - 1.0f));
-    lo[k] = fminf(lo[k], hi[k]);
-  }
-
-  // ---------------------------------------------- 2. candidate lists at tau_lb (see collect_sweep)
-  float cut[2];
-  CellBuf<kCandCap, LS> cb[2];
-  int ncell[2] = {0, 0};
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    cut[k] = raw_cut(q[k].a, live[k], lo[k]);
-    cb[k].init(A.cells, lds_cells + k * CellBuf<kCandCap, LS>::kLdsBytes, tid, 2 * (int)blockIdx.x + k);
-  }
-  sweep_tiles<C, T, D, 1, 0, ListCfg<T, D>::kDepth>(
-      tiles, slots, ntiles, g.Nk, tid, needed,
-      [&](int kt, const char* tl) {
-        uint32_t act[2] = {visible(0, kt), visible(1, kt)};
-        if ((kt + 1) * NSB <= W * 32) {
-          const int jb = kt * NSB;
-#pragma unroll
-          for (int k = 0; k < 2; ++k) act[k] &= __builtin_amdgcn_readfirstlane(mybits[k][jb >> 5]) >> (jb & 31);
-        }
-        // a block whose strip overflowed is lost to the tiled kernel anyway (flags of the previous tile's parity
-        // were final before the barrier that ended that tile)
-#pragma unroll
-        for (int k = 0; k < 2; ++k)
-          if (kt > 0 && ovf[3 * k + ((kt - 1) & 1)] != 0) act[k] = 0u;
-        if ((act[0] | act[1]) == 0u) return;
-#pragma unroll
-        for (int sb = 0; sb < NSB; ++sb) {
-          if (((act[0] | act[1]) & (1u << sb)) == 0u) continue;
-          Frag<T> kf[NC];
-          load_k(tl, sb, kf);
-          const int j0 = kt * KT + sb * 32;
-          f32x16_t accs[2];  // (both products before the vector work on either)
-#pragma unroll
-          for (int k = 0; k < 2; ++k)
-            if ((act[k] & (1u << sb)) != 0u) accs[k] = product(k, kf, j0);
-#pragma unroll
-          for (int k = 0; k < 2; ++k) {
-            if ((act[k] & (1u << sb)) == 0u) continue;
-            f32x16_t& acc = accs[k];
-            ++n_qk2[k];
-            if (j0 + 32 > q[k].wave_lim_min) mask_block(q[k], acc, j0);
-            append_cells(q[k], acc, j0, cut[k], cb[k], ncell[k], n_cand_tiles[k]);
-          }
-        }
-#pragma unroll
-        for (int k = 0; k < 2; ++k)
-          if (__ballot(ncell[k] > kCandCap) != 0ull && lane == 0) ovf[3 * k + (kt & 1)] = 1;
-      },
-      [&](int kt) { return kt > 0 && ovf[(kt - 1) & 1] != 0 && ovf[3 + ((kt - 1) & 1)] != 0; });
-  // the sweep ended on a barrier: the strips' flags are final
-  int cnt[2] = {0, 0};
-  bool fits[2];
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    fits[k] = (ovf[3 * k] | ovf[3 * k + 1]) == 0;
-    if (fits[k]) {
-      uint2* mylist = A.cand + list_entry<kCandCap>(q[k].bh, A.nqb, q[k].qb, wave, lane);
-      const int total = cells_to_list<kCandCap>(cb[k], ncell[k], cut[k], mylist, cnt[k]);
-      if (total > kCandCap) ovf[3 * k + 2] = 1;
-      pool_want(ovf + 6 + k, cnt[k], lane);
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    fits[k] = fits[k] && ovf[3 * k + 2] == 0;
-    if (tid == 0) A.dense_flag[flag_idx[k]] = fits[k] ? -ovf[6 + k] : kFlagDense;
-    if (fits[k] && q[k].valid) {
-      A.lcnt[row_idx[k] * 2 + q[k].hh] = cnt[k];
-      if (q[k].hh == 0) A.bounds[row_idx[k]] = make_float2(lo[k], hi[k]);
-    }
-    if (A.stats && lane == 0) {
-      const unsigned n_win = q[k].window_skipped_blocks();
-      atomicAdd(&A.stats[ENTMAX_STAT_FWD_TILES_VISIBLE], (unsigned long long)(n_vis[k] + n_win));
-      if (BIAS) atomicAdd(&A.stats[ENTMAX_STAT_FWD_WINDOW_SKIPPED], (unsigned long long)n_win);
-      atomicAdd(&A.stats[ENTMAX_STAT_FWD_LIST_QK], (unsigned long long)(n_vis[k] + n_qk2[k]));
-      if (fits[k]) {
-        atomicAdd(&A.stats[ENTMAX_STAT_FWD_CAND_TILES], (unsigned long long)n_cand_tiles[k]);
-        if (wave == 0) atomicAdd(&A.stats[ENTMAX_STAT_FWD_SPARSE_BLOCKS], 1ull);
-      }
-    }
-  }
-}
-
-template <typename T, int D, int AM, bool BIAS>
-__global__ __launch_bounds__(kThreads, (ListCfg<T, D>::kOcc)) void fwd_lists_pair_kernel(FwdSparseArgs A) {
+__global__ __launch_bounds__(kThreads, (ListCfg<T, D>::kFwdOcc)) void fwd_lists_pair_kernel(FwdSparseArgs A) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int nsb = (A.nqb + 1) >> 1;  // pairs of adjacent blocks per head
   const PairItem it = pair_item(nsb);
@@ -813,9 +1117,9 @@ __global__ __launch_bounds__(kThreads, (ListCfg<T, D>::kOcc)) void fwd_lists_pai
     if (sblk < 0) break;
     if (part) __syncthreads();
     if (2 * sblk + 1 < A.nqb)
-      fwd_lists_pair<T, D, AM, BIAS>(A, it.bh, sblk, smem);
+      fwd_lists_blocks<T, D, AM, BIAS, 2>(A, it.bh, 2 * sblk, smem, 2 * (int)blockIdx.x);
     else  // a head's odd last block
-      fwd_lists_block<T, D, AM, BIAS>(A, it.bh, 2 * sblk, smem, 2 * (int)blockIdx.x);
+      fwd_lists_blocks<T, D, AM, BIAS, 1>(A, it.bh, 2 * sblk, smem, 2 * (int)blockIdx.x);
   }
 }
 

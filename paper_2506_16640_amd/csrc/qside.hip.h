@@ -75,6 +75,16 @@ struct QCtx {
     ntiles = uni((block_lim + KT - 1) / KT);
     wave_lim_min = uni(q0 < g.Nq ? row_limit(g, q0) : 0);
     wave_lim_max = uni(q0 < g.Nq ? row_limit(g, min(g.Nq, q0 + 32) - 1) : 0);
+    init_row(g, Q);
+    if constexpr (BIAS) {
+      wave_pos_min = uni(q0 + (g.Nk - g.Nq));
+      wave_bias = __ballot(w != 0.f) != 0ull;
+      kt_first = kt_first_wave = 0;
+    }
+  }
+
+  // what follows from the lane's row (i, valid, lim are set)
+  __device__ __forceinline__ void init_row(const Geom& g, const void* Q) {
     float scale = valid ? row_scale(g, b, h, i, lim, nullptr, nullptr, nullptr) : 0.f;
     float inv_sqrt_d = 1.0f / sqrtf((float)D);
     c = scale * inv_sqrt_d;
@@ -89,9 +99,6 @@ struct QCtx {
     if constexpr (BIAS) {
       w = valid ? bias_w<D>(g, h, c, a) : 0.f;
       pos = i + (g.Nk - g.Nq);
-      wave_pos_min = uni(q0 + (g.Nk - g.Nq));
-      wave_bias = __ballot(w != 0.f) != 0ull;
-      kt_first = kt_first_wave = 0;
     }
   }
 
@@ -154,13 +161,18 @@ struct QCtx {
     const int rel = pos - j0;
     if (j0 + 31 <= wave_pos_min) {
       // every key of the block is at or before every row's position: dist = rel - key_of(e) > = 0
-      const float base = w * (float)(rel - 4 * hh);
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[e] = fmaf(-w, (float)(8 * (e >> 2) + (e & 3)), base);
+      bias_before(acc, j0);
     } else {
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[e] = w * (float)max(rel - key_of(e), 0);
     }
+  }
+
+  // the first case alone: w dist for a block whose keys are all at or before every row's position
+  __device__ __forceinline__ void bias_before(f32x16_t& acc, int j0) const {
+    const float base = w * (float)(pos - j0 - 4 * hh);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = fmaf(-w, (float)(8 * (e >> 2) + (e & 3)), base);
   }
 
   // S^T block: rows = 32 keys of sub-block sb of the K tile, cols = the wave's 32 queries.
@@ -378,6 +390,91 @@ __device__ __forceinline__ void sweep_tiles(char* smem, const Slot* slots, int n
     }
   }
 }
+
+// 16 bytes per lane from sbase + voff (global memory) to LDS, at lds (wave-uniform LDS byte address) + 16 lane, without a
+// register in between.  The compiler does not count these loads: before the bytes are read, every wave waits for its
+// own (lds_loads_wait) and the workgroup meets at a barrier.
+__device__ __forceinline__ void load_to_lds(const char* sbase, uint32_t voff, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(sbase) : "memory", "m0");
+}
+// until at most N of the wave's loads are under way (they end in order)
+template <int N>
+__device__ __forceinline__ void lds_loads_wait() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+// The key tiles first .. ntiles - 1 of one natural-layout tensor, straight to LDS, two of them under way while one is worked on: a
+// ring of three buffers at smem.  start(), then step() as long as kt < ntiles, then finish(); all threads of the
+// workgroup together.  No registers hold tiles and no wave writes them to LDS, which is what sweep_tiles() spends on each tile.
+template <typename C, typename T, int D>
+struct TileRing {
+  using Tile = typename C::KTile;
+  static constexpr int KT = C::KT, TB = C::kTileBytes;
+  static constexpr int L = Tile::kChunks / kThreads;  // loads of a wave per tile
+  static constexpr int RS = kThreads / Tile::kCpr;    // rows between a thread's chunks
+  static_assert(Tile::kChunks % kThreads == 0 && RS % 16 == 0, "a thread's chunks sit at the same place of their rows' swizzle");
+  char* smem;
+  const char* base;
+  long long row_bytes;
+  int ntiles, Nk, kt, cur;
+  uint32_t voff, lds0;
+  __device__ __forceinline__ void issue(int t, int buf) const {
+    const char* src = base + (long long)t * KT * row_bytes;
+    const int rows_left = Nk - t * KT;
+    const uint32_t dst = lds0 + (uint32_t)buf * TB;
+    if (rows_left >= KT) {
+#pragma unroll
+      for (int it = 0; it < L; ++it) load_to_lds(src + (long long)(it * RS) * row_bytes, voff, dst + it * kThreads * 16);
+    } else {  // ragged last tile: rows beyond the tensor repeat its last one (see Stage::fetch)
+      const int row0 = (int)threadIdx.x / Tile::kCpr;
+      const uint32_t chunk = (uint32_t)((((int)threadIdx.x % Tile::kCpr) ^ Tile::swz(row0)) * 16);
+#pragma unroll
+      for (int it = 0; it < L; ++it)
+        load_to_lds(src, (uint32_t)min(row0 + it * RS, rows_left - 1) * (uint32_t)row_bytes + chunk, dst + it * kThreads * 16);
+    }
+  }
+  __device__ __forceinline__ void start(char* smem_, const Slot& slot, int first, int ntiles_, int Nk_) {
+    smem = smem_;
+    base = slot.base;
+    row_bytes = slot.row_bytes;
+    ntiles = ntiles_;
+    Nk = Nk_;
+    kt = first;
+    cur = 0;
+    const int tid = threadIdx.x, row0 = tid / Tile::kCpr;
+    // which 16 bytes of its row go to this thread's place
+    voff = (uint32_t)row0 * (uint32_t)row_bytes + (uint32_t)(((tid % Tile::kCpr) ^ Tile::swz(row0)) * 16);
+    lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem + (uint32_t)(tid & ~63) * 16u);
+    if (kt < ntiles) issue(kt, 0);
+    if (kt + 1 < ntiles) {
+      issue(kt + 1, 1);
+      lds_loads_wait<L>();
+    } else {
+      lds_loads_wait<0>();
+    }
+    __syncthreads();
+  }
+  // body(tile) on tile kt
+  template <class Body>
+  __device__ __forceinline__ void step(Body body) {
+    const int buf2 = cur == 0 ? 2 : cur - 1;  // that of the tile before, which every wave has left
+    const bool more = kt + 2 < ntiles;
+    if (more) issue(kt + 2, buf2);
+    body(smem + cur * TB);
+    if (more)
+      lds_loads_wait<L>();  // tile kt + 1 is there, kt + 2 is under way
+    else
+      lds_loads_wait<0>();
+    __syncthreads();
+    cur = cur == 2 ? 0 : cur + 1;
+    ++kt;
+  }
+  // before the buffers are used for something else when not all tiles have been worked on
+  __device__ __forceinline__ void abandon() const {
+    lds_loads_wait<0>();
+    __syncthreads();
+  }
+};
 
 // Per-wave bit sets over the 32-key blocks of a head, kept in LDS: bit jb of
 // wave w says the block can hold a non-zero probability for some row of the wave.

@@ -32,7 +32,7 @@ bool launch_fwd_am(const FwdArgs& a, int am, int nblocks, hipStream_t st) {
 
 template <typename T, int D, int AM, bool BIAS>
 bool launch_fwd_sparse(const FwdSparseArgs& a, int nblocks, hipStream_t st, void* const* ev) {
-  size_t smem = ListCfg<T, D>::kLdsBytes;
+  size_t smem = ListCfg<T, D>::kFwdLdsBytes;
   const int nsb = (a.nqb + 1) / 2;
   const long long pair_grid = (long long)a.g.B * a.g.H * ((nsb + 1) / 2);
   const bool long_seq = a.g.Nk >= ListCfg<T, D>::kPairMinKeys;
@@ -42,8 +42,7 @@ bool launch_fwd_sparse(const FwdSparseArgs& a, int nblocks, hipStream_t st, void
     // long sequences: the second sweep skips blocks the first cleared, and a workgroup takes two adjacent blocks
     // where that still leaves three workgroups for every CU (measured at B 4, H 12, n 4096, where it leaves 1.5:
     // 221 us against 139 us with one block per workgroup)
-    const size_t smem2 = PairCfg<T, D>::kLdsBytes > smem ? PairCfg<T, D>::kLdsBytes : smem;
-    hipLaunchKernelGGL((fwd_lists_pair_kernel<T, D, AM, BIAS>), dim3((unsigned)pair_grid), dim3(kThreads), smem2, st, a);
+    hipLaunchKernelGGL((fwd_lists_pair_kernel<T, D, AM, BIAS>), dim3((unsigned)pair_grid), dim3(kThreads), smem, st, a);
     launched = true;
     }
   }

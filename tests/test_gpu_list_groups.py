@@ -1,0 +1,74 @@
+"""GPU parity of the forward's list kernels where their memory of a row's largest key groups ends: rows whose large scores lie
+in fewer, as many and more groups than a lane keeps (8 for strong scales, 12 else), in so few lanes of a query block that their keys are looked at
+one by one and in more, in short rows that are swept a second time at once; one and two query blocks per workgroup, with and
+without distance bias.  The backward gets the forward's lists.  The bars are the parity tests' (bf16 inputs, sums in fp32)."""
+import numpy as np
+import pytest
+
+from paper_2506_16640_amd import synth
+from tests.parity_util import compare, gpu_run, oracle_run
+
+pytestmark = pytest.mark.gpu
+
+
+def _data(n, d, dtype, scale, groups, rows, half, seed):
+    """`groups` keys, each in a group of its own (8 keys of one lane half), point along a common direction that `rows` late queries carry."""
+    data = synth.make_inputs(B=1, H=2, n=n, nk=n, d=d, dtype=dtype, scale="head", seed=seed)
+    rng = np.random.default_rng(seed)
+    data["beta"][:], data["gamma"][:], data["delta"] = (scale - 1.0) / np.log(n), 1.0, 1.0
+    u = np.ones(d, dtype=np.float32)
+    at = n - 140 - rng.choice(rows * 3, size=rows, replace=False)
+    data["Q"][:, :, at] = data["Q"][:, :, at] * 0.125 + np.float32(16.0 / d) * u
+    pick = rng.choice((n - 140 - rows * 3) // 16, size=groups, replace=False)  # 16 keys: a group of either half
+    keys = 16 * pick + 8 * rng.integers(0, 2, size=groups) + 4 * half + rng.integers(0, 4, size=groups)
+    data["K"][:, :, keys] = (2.0 + 0.0625 * rng.integers(0, 3, size=groups)).astype(np.float32)[:, None] * u
+    if dtype == "bf16":  # both sides see the same bf16 values
+        data["Q"][:] = synth.bf16_round(data["Q"])
+    return data
+
+
+def _check(data, alpha, dtype, label, **kw):
+    g = gpu_run(data, alpha, dtype, use_saved=True, stats=True, **kw)
+    kw.pop("path", None)
+    r = oracle_run(data, alpha, **kw)
+    print(label, compare(g, r, label=label), {k: v for k, v in g["stats"].items() if v})
+
+
+@pytest.mark.parametrize("d,dtype", [(64, "bf16"), (128, "bf16"), (64, "fp32"), (128, "fp32")])
+@pytest.mark.parametrize("scale", [7.0, 4.0])
+@pytest.mark.parametrize("groups", [7, 8, 9, 11, 12, 13, 20])
+def test_groups_and_lanes(groups, scale, d, dtype):
+    for rows in (1, 8, 9, 60):
+        data = _data(704, d, dtype, scale, groups, rows, half=groups & 1, seed=groups + rows)
+        _check(data, 1.5, dtype, "groups %d rows %d scale %g d%d %s" % (groups, rows, scale, d, dtype))
+
+
+@pytest.mark.parametrize("alpha", [1.25, 1.7, 2.0])
+def test_other_alphas(alpha):
+    for groups, rows in ((8, 8), (13, 5), (20, 40)):
+        _check(_data(704, 64, "bf16", 7.0, groups, rows, 0, seed=3), alpha, "bf16", "alpha %g groups %d rows %d" % (alpha, groups, rows))
+
+
+@pytest.mark.parametrize("n", [620, 769, 1100])
+def test_two_blocks_per_workgroup(n):
+    for groups, rows, scale in ((8, 4, 7.0), (9, 4, 7.0), (12, 40, 4.0), (14, 3, 4.0), (20, 40, 7.0)):
+        _check(_data(n, 64, "bf16", scale, groups, rows, 1, seed=n + groups), 1.5, "bf16", "two blocks n%d groups %d rows %d" % (n, groups, rows), path=2)
+
+
+@pytest.mark.parametrize("bias_mode,causal", [(0, True), (1, True), (0, False)])
+@pytest.mark.parametrize("path", [0, 2])
+def test_with_distance_bias(bias_mode, causal, path):
+    slopes = np.array([0.0, 1.0 / 512], dtype=np.float32)
+    for groups, rows in ((8, 3), (13, 6), (20, 40)):
+        data = _data(900, 64, "bf16", 7.0, groups, rows, 0, seed=groups)
+        _check(data, 1.5, "bf16", "bias m%d groups %d rows %d" % (bias_mode, groups, rows), slopes=slopes, bias_mode=bias_mode, causal=causal, path=path)
+
+
+def test_negative_scales_and_weak_short_rows():
+    data = _data(704, 64, "bf16", 7.0, 13, 6, 0, seed=1)
+    data["K"][:] = -data["K"]
+    data["beta"][:], data["delta"] = -data["beta"], -1.0
+    _check(data, 1.5, "bf16", "negative scale")
+    for n in (97, 130, 260):  # short rows that keep a good part of their keys
+        data = synth.make_inputs(B=2, H=2, n=n, nk=n, d=64, dtype="bf16", scale="none", seed=n)
+        _check(data, 1.5, "bf16", "short rows n%d" % n)
