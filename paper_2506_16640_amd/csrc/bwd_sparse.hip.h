@@ -233,7 +233,11 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_rows_kernel(BwdSparseArgs A) 
     // are linear in mu,
     //   dQ_i = c (sum_j g dP k_j - mu sum_j g k_j),   dscale_i = sum_j g dP d_j - mu sum_j g d_j,
     // the K rows are gathered in the same pass as the V rows: one memory round trip for both.
+    // The sums of dscale take the scores relative to one of the row's own (sum_j dS_ij = 0, so that the difference is only in rounding: at scores
+    // of some tens the products they would otherwise be formed from are ten times as large as what is left of them).
     float dpv[NE];  // dP of the lane's own entries
+    const float d_first = (cnt > 0) ? dv[0] : -kInf, d_other = __shfl_xor(d_first, 32);
+    const float d_ref = fmaxf(fmaxf(d_first, d_other), -3.0e38f);
     float Z = 0.f, N = 0.f, sd1 = 0.f, sd0 = 0.f;
     float qa[DH], qb[DH];  // this lane's half of sum g dP k and of sum g k
 #pragma unroll
@@ -280,7 +284,7 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_rows_kernel(BwdSparseArgs A) 
           float gdp = gg * dp;
           Z += gg;
           N += gdp;
-          const float dz = (w_out != 0.f) ? fmaf(-w_out, (float)bias_dist(pos, (int)j), d) : d;
+          const float dz = ((w_out != 0.f) ? fmaf(-w_out, (float)bias_dist(pos, (int)j), d) : d) - d_ref;
           sd1 = fmaf(gdp, dz, sd1);
           sd0 = fmaf(gg, dz, sd0);
 #pragma unroll
