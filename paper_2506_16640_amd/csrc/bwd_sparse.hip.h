@@ -112,93 +112,82 @@ __global__ __launch_bounds__(kThreads, (ListCfg<T, D>::kOcc)) void bwd_lists_ker
   }
 }
 
-// Everything row-wise from the lists: D / 32 lanes per row, each with 32 of the features (a lane pair per row at
-// D = 64; at D = 128 two lanes per list half, which both read that half's entries -- with 64 features per lane the
-// kernel needed 388 registers and ran one wave per SIMD: 234 against 174 us at B 2, H 16, n 8192).
-// Measured and not kept: 16 features per lane (twice the waves at 146 registers: same time at both head
-// dimensions), eight consecutive lanes per row so that a gathered row is one load instruction (D = 64: 78 -> 82 us),
-// all gathers of a short row requested before the first is used (-> 101 us), a head's keys on its rows' XCD in the
-// key kernel (no change).
-template <int D>
+// Everything row-wise from the lists.  A wave owns 32 rows, as in the sweeps; what belongs to a row alone (its scale, its list words) a lane pair
+// brings, and the gathers are done by eight lanes (an octet) per row, eight rows at a time, each lane an eighth of the features in 16-byte words: a
+// gathered row is then one line per load instruction, and an entry costs its eight lanes some 45 vector instructions, where a lane pair per row
+// spent 200 for every entry of the longest of 32 rows (two to a SIMD at 226 registers).  Lane k of the octet holds entries k, k + 8, ... of the row
+// (both halves' lists one after the other).  B 4, H 12, n 4096, D 64: 51 -> 32 us (alpha 1.25: 73 -> 60); B 2, H 16, n 8192, D 128: 147 -> 94.
+// Two entries of a row under way at a time (D 64; one at D 128) and four workgroups per CU; four entries 33.6 us; five workgroups spill (44 to 72).
+// The same division of the gathers in the forward's finish kernel, whose lane pairs hold little beside the value row, was slower (44 -> 52 to 57 us).
+template <typename T, int D>
 struct RowsCfg {
-  static constexpr int kFH = D / 64;  // lanes per list half
+  static constexpr int W = D * (int)sizeof(T) / 128;          // 16-byte words of a row per lane
+  static constexpr int kPer = 16 / (int)sizeof(T);            // elements of a word
+  static constexpr int kAhead = W == 1 ? 2 : 1;               // entries of a row whose V and K rows are requested together
 };
+__device__ __forceinline__ float octet_sum(float v) {
+  v += dpp_move<0xb1>(v);   // lane ^ 1
+  v += dpp_move<0x4e>(v);   // lane ^ 2
+  return v + dpp_move<0x141>(v);  // lane 7 - k of the octet: the other four
+}
 template <typename T, int D, int AM>
-__global__ __launch_bounds__(kThreads, 2) void bwd_rows_kernel(BwdSparseArgs A) {
+__global__ __launch_bounds__(kThreads, (sizeof(T) == 2 ? 4 : 2)) void bwd_rows_kernel(BwdSparseArgs A) {
   const Geom& g = A.g;
-  constexpr int FH = RowsCfg<D>::kFH;
-  if ((int)blockIdx.x >= g.B * g.H * A.nqb * FH) {  // riders behind the row workgroups
-    transpose_ride<T, D>(A.ride, (int)blockIdx.x - g.B * g.H * A.nqb * FH);
+  if ((int)blockIdx.x >= g.B * g.H * A.nqb) {  // riders behind the row workgroups
+    transpose_ride<T, D>(A.ride, (int)blockIdx.x - g.B * g.H * A.nqb);
     return;
   }
+  using Cfg = RowsCfg<T, D>;
+  constexpr int W = Cfg::W, PER = Cfg::kPer, U = Cfg::kAhead;
   RowLane rl;
-  rl.init<FH>(g, A.nqb);
-  constexpr int DH = 32;  // features per lane
-  const int feat0 = (rl.hh * FH + rl.f) * DH;  // the lane's first feature
-  const bool owner_lane = rl.f == 0;           // the lane of its list half that places the entries and writes the row scalars
+  rl.init(g, A.nqb);
+  const int lane = threadIdx.x & 63, oct = lane >> 3, k = lane & 7;
   const float r = 1.0f / (g.alpha - 1.0f);
   const long long row_idx = (long long)rl.bh * g.Nq + (rl.valid ? rl.i : 0);
   const int lim = rl.valid ? row_limit(g, rl.i) : 0;
   const bool live = rl.valid && lim > 0;
-  const float scale = rl.valid ? row_scale(g, rl.b, rl.h, rl.i, lim, nullptr, nullptr, nullptr) : 0.f;
-  const float inv_sqrt_d = 1.0f / sqrtf((float)D);
-  const float c = scale * inv_sqrt_d;
-  const float a = (g.alpha - 1.0f) * fabsf(c);  // same arithmetic as the sweep that made the lists
-  const float sgn = (c < 0.f) ? -1.f : 1.f;
-  // distance bias outside the scale: dscale_i = sum_j dS_ij z_ij needs the listed scores without their bias term
-  const float w_out = (g.slopes && g.bias_mode == 1) ? bias_w<D>(g, rl.h, c, a) : 0.f;
-  const int pos = rl.i + (g.Nk - g.Nq);
   // every load that does not depend on another is issued before the first wait (the head's flags included)
-  const int head_dense = (A.head_flag[rl.bh] == kHeadTiled || A.block_flag[rl.bh * A.nqb + rl.qb] != 0) ? 1 : 0;
+  const int hflag = A.head_flag[rl.bh], bflag = A.block_flag[rl.bh * A.nqb + rl.qb];
   const float tau_raw = A.tau[row_idx];
   const int cnt_raw = A.lcnt[row_idx * 2 + rl.hh];
-  const float tau = live ? tau_raw : 0.f;
+  const float scale = rl.valid ? row_scale(g, rl.b, rl.h, rl.i, lim, nullptr, nullptr, nullptr) : 0.f;
+  const float inv_sqrt_d = 1.0f / sqrtf((float)D);
+  const float c_own = scale * inv_sqrt_d;
+  const float a_own = (g.alpha - 1.0f) * fabsf(c_own);  // same arithmetic as the sweep that made the lists
+  // distance bias outside the scale: dscale_i = sum_j dS_ij z_ij needs the listed scores without their bias term
+  const float w_own = (g.slopes && g.bias_mode == 1) ? bias_w<D>(g, rl.h, c_own, a_own) : 0.f;
+  const float tau_own = live ? tau_raw : 0.f;
+  // where this half row's entries are and how many; entries of a workspace list are kListStride apart
+  unsigned place_own = 0u;
+  int cnt_own = cnt_raw;
+  const uint2* lists = A.list;
+  if (A.packed) {
+    place_own = (unsigned)cnt_raw >> 5;
+    cnt_own = cnt_raw & 31;
+    if ((long long)place_own + cnt_own > A.pool_cap) {  // not a place the forward wrote (a flagged block's words hold anything)
+      place_own = 0u;
+      cnt_own = 0;
+    }
+  } else {
+    lists += list_entry<kBwdCap>(rl.bh, A.nqb, rl.qb, rl.w32, 0);
+    place_own = (unsigned)lane;
+  }
+  const int lstride = A.packed ? 1 : kListStride;
+  cnt_own = live ? min(max(cnt_own, 0), kBwdCap) : 0;
   const long long q_base = (long long)rl.b * g.q_sb + (long long)rl.h * g.q_sh;
   const long long kv_base = (long long)rl.b * g.kv_sb + (long long)rl.h * g.kv_sh;
-  // where this half row's entries are, and how far apart
-  const uint2* rdlist;
-  int cnt_list, lstride;
-  if (A.packed) {
-    long long off = (long long)((unsigned)cnt_raw >> 5);
-    cnt_list = cnt_raw & 31;
-    if (off + cnt_list > A.pool_cap) {  // not a place the forward wrote (a flagged block's words hold anything)
-      off = 0;
-      cnt_list = 0;
-    }
-    rdlist = A.list + off;
-    lstride = 1;
-  } else {
-    rdlist = A.list + list_entry<kBwdCap>(rl.bh, A.nqb, rl.qb, rl.w32, rl.hh * 32 + rl.li);
-    cnt_list = cnt_raw;
-    lstride = kListStride;
-  }
-  const int cnt = live ? min(cnt_list, kBwdCap) : 0;
-  const T* Kbh = reinterpret_cast<const T*>(A.K) + kv_base;
-  const T* Vbh = reinterpret_cast<const T*>(A.V) + kv_base;
-
-  // the row's dO, this lane's half of the features, widened to fp32
-  float dov[DH];
-  if (rl.valid) {
-    load_row_f32<T>(reinterpret_cast<const T*>(A.dO) + q_base + (long long)rl.i * g.q_sn + feat0, DH, dov);
-  } else {
-#pragma unroll
-    for (int t = 0; t < DH; ++t) dov[t] = 0.f;
-  }
-  unsigned n_entries = 0;
-  // the first entries are requested whatever the list length is (the slots exist whatever they hold; the
-  // pool ends on kSavedPoolPad spare entries)
-  constexpr int kEarly = 4;
-  uint2 early[kEarly];
-#pragma unroll
-  for (int e = 0; e < kEarly; ++e) early[e] = rdlist[e * lstride];
-  if (head_dense != 0) {  // the tiled kernels own this block
+  const char* Kbh = reinterpret_cast<const char*>(reinterpret_cast<const T*>(A.K) + kv_base) + 16 * k;
+  const char* Vbh = reinterpret_cast<const char*>(reinterpret_cast<const T*>(A.V) + kv_base) + 16 * k;
+  const uint32_t kv_bytes = (uint32_t)(g.kv_sn * (long long)sizeof(T));
+  const long long q_bytes = g.q_sn * (long long)sizeof(T);
+  const long long cap = (long long)g.Nq * 2 * kBwdCap;  // entries a head can hold
+  if (hflag == kHeadTiled || bflag != 0) {  // the tiled kernels own this block
     // The forward numbered this block's entries among their keys' entries before it knew that the block would
     // not take the list path: in a head whose other blocks do, those places must not stay undefined.  They get
     // records that add nothing.
-    if (A.packed && owner_lane && A.block_flag[rl.bh * A.nqb + rl.qb] == kBlockListsUnused && A.head_flag[rl.bh] == kHeadMixed) {
-      const long long cap = (long long)g.Nq * 2 * kBwdCap;
-      for (int e = 0; e < cnt; ++e) {
-        const uint2 en = rdlist[e];
+    if (A.packed && bflag == kBlockListsUnused && hflag == kHeadMixed) {
+      for (int e = 0; e < cnt_own; ++e) {
+        const uint2 en = lists[place_own + e];
         const unsigned key = min(en.x & ((1u << kSavedKeyBits) - 1u), (unsigned)(g.Nk - 1)), rank = en.x >> kSavedKeyBits;
         const long long kidx = (long long)rl.bh * g.Nk + key;
         const int slot = A.koffs[kidx] + (rank < kSavedRankMost ? (int)rank : (int)kSavedRankMost + atomicAdd(&A.kcursor[kidx], 1));
@@ -210,120 +199,163 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_rows_kernel(BwdSparseArgs A) 
     }
     return;
   }
+  unsigned n_entries = 0;
+  const int i0 = rl.qb * kBlockRows + rl.w32 * 32;  // the wave's first row
 
-  auto finish = [&](auto ne_tag) {
-    constexpr int NE = decltype(ne_tag)::value;
-    unsigned jv[NE], rkv[NE];
-    float dv[NE];  // raw dot products (sign-folded), -inf for empty slots
+  // the octet's row of step s: 8 s + oct of the wave's 32
+  struct Group {
+    int n0, n;              // entries of the first half's list, of both
+    unsigned place0, place1;
+    uint2 first;            // the lane's first entry
+  };
+  auto bring = [&](int s) {
+    Group gr;
+    const int row = 8 * s + oct;
+    gr.n0 = __shfl(cnt_own, row);
+    gr.n = gr.n0 + __shfl(cnt_own, row + 32);
+    gr.place0 = (unsigned)__shfl((int)place_own, row);
+    gr.place1 = (unsigned)__shfl((int)place_own, row + 32);
+    gr.first = make_uint2(0u, 0u);
+    if (k < gr.n) gr.first = lists[k < gr.n0 ? gr.place0 + (unsigned)(k * lstride) : gr.place1 + (unsigned)((k - gr.n0) * lstride)];
+    return gr;
+  };
+
+  // R: rounds of eight entries
+  auto finish = [&](const Group& gr, int s, auto rounds_) {
+    constexpr int R = decltype(rounds_)::value;
+    const int row = 8 * s + oct, i = i0 + row;
+    const bool valid = i < g.Nq;
+    const float a = __shfl(a_own, row), c = __shfl(c_own, row), tau = __shfl(tau_own, row);
+    const float w_out = (g.slopes && g.bias_mode == 1) ? __shfl(w_own, row) : 0.f;
+    const int pos = i + (g.Nk - g.Nq);
+    u32x4_t dow[W];
+    const char* dorow = reinterpret_cast<const char*>(reinterpret_cast<const T*>(A.dO) + q_base) + (long long)min(i, g.Nq - 1) * q_bytes + 16 * k;
 #pragma unroll
-    for (int e = 0; e < NE; ++e) {
-      uint2 en = make_uint2(0u, 0u);
-      if (e < kEarly)
-        en = early[e];
-      else if (e < cnt)
-        en = rdlist[e * lstride];
+    for (int w = 0; w < W; ++w) dow[w] = *reinterpret_cast<const u32x4_t*>(dorow + 128 * w);
+    unsigned jv[R];
+    float xv[R], dv[R], dpv[R];
+    int slotv[R];  // place in the key-major arrays of the lane's entries; -1: not part of the support
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      const int e = 8 * q + k;
+      uint2 en = gr.first;
+      if (q > 0) {
+        en = make_uint2(0u, 0u);
+        if (e < gr.n) en = lists[e < gr.n0 ? gr.place0 + (unsigned)(e * lstride) : gr.place1 + (unsigned)((e - gr.n0) * lstride)];
+      }
       // the forward's entries carry their arrival number among their key's entries above the key index
-      rkv[e] = A.packed ? en.x >> kSavedKeyBits : kSavedRankMost;
+      const unsigned rank = A.packed ? en.x >> kSavedKeyBits : kSavedRankMost;
       if (A.packed) en.x &= (1u << kSavedKeyBits) - 1u;
       // (a key index is never followed outside the tensors, whatever a stale or foreign `saved` buffer holds)
-      jv[e] = (e < cnt) ? min(en.x, (unsigned)(g.Nk - 1)) : 0u;
-      dv[e] = (e < cnt) ? __uint_as_float(en.y) : -kInf;
+      jv[q] = min(en.x, (unsigned)(g.Nk - 1));
+      dv[q] = __uint_as_float(en.y);
+      xv[q] = e < gr.n ? fmaxf(fmaf(dv[q], a, -tau), 0.f) : 0.f;
+      dpv[q] = 0.f;
+      slotv[q] = -1;
+      // the entry's arrival number among the key's entries is its place in the key's segment: the forward's, or (lists made here,
+      // and a key's entries beyond the numbers the forward can write) from the key's cursor
+      if (xv[q] > 0.f) {
+        const long long kidx = (long long)rl.bh * g.Nk + jv[q];
+        slotv[q] = A.koffs[kidx] +
+                   (rank < kSavedRankMost ? (int)rank : (A.packed ? (int)kSavedRankMost : 0) + atomicAdd(&A.kcursor[kidx], 1));
+        ++n_entries;
+      }
     }
-    // One gather pass over the entries of the row (both halves): dP = <dO, v_j> and, because dQ and dscale
-    // are linear in mu,
+    // One gather pass over the entries of the row: dP = <dO, v_j> and, because dQ and dscale are linear in mu,
     //   dQ_i = c (sum_j g dP k_j - mu sum_j g k_j),   dscale_i = sum_j g dP d_j - mu sum_j g d_j,
     // the K rows are gathered in the same pass as the V rows: one memory round trip for both.
     // The sums of dscale take the scores relative to one of the row's own (sum_j dS_ij = 0, so that the difference is only in rounding: at scores
     // of some tens the products they would otherwise be formed from are ten times as large as what is left of them).
-    float dpv[NE];  // dP of the lane's own entries
-    const float d_first = (cnt > 0) ? dv[0] : -kInf, d_other = __shfl_xor(d_first, 32);
-    const float d_ref = fmaxf(fmaxf(d_first, d_other), -3.0e38f);
+    const float d_ref = __shfl(dv[0], lane & ~7);
     float Z = 0.f, N = 0.f, sd1 = 0.f, sd0 = 0.f;
-    float qa[DH], qb[DH];  // this lane's half of sum g dP k and of sum g k
+    float qa[W][PER], qb[W][PER];  // this lane's features of sum g dP k and of sum g k
 #pragma unroll
-    for (int t = 0; t < DH; ++t) qa[t] = qb[t] = 0.f;
-    int slotv[NE];  // place in the key-major arrays of the lane's own entries; -1: not part of the support
+    for (int w = 0; w < W; ++w)
 #pragma unroll
-    for (int e = 0; e < NE; ++e) {
-      slotv[e] = -1;
-      dpv[e] = 0.f;
-    }
+      for (int t = 0; t < PER; ++t) qa[w][t] = qb[w][t] = 0.f;
 #pragma unroll
-    for (int e = 0; e < NE; ++e) {
-      unsigned pj = (unsigned)__shfl_xor((int)jv[e], 32);
-      float pd = __shfl_xor(dv[e], 32);
+    for (int q = 0; q < R; ++q) {
 #pragma unroll
-      for (int src = 0; src < 2; ++src) {
-        // both lanes of the pair look at the same entry: entry e of the lane whose half index is src
-        unsigned j = (rl.hh == src) ? jv[e] : pj;
-        float d = (rl.hh == src) ? dv[e] : pd;
-        float x = (d > -kInf) ? fmaxf(fmaf(d, a, -tau), 0.f) : 0.f;
-        if (__ballot(x > 0.f) == 0ull) continue;
-        float part = 0.f;
-        RawRow<T, DH> kk;
-        if (x > 0.f) {
-          RawRow<T, DH> vv;
-          vv.load(Vbh + (long long)j * g.kv_sn + feat0);
-          kk.load(Kbh + (long long)j * g.kv_sn + feat0);
-          // the entry's owner takes its arrival number among the key's entries: its place in the key's segment
-          if (rl.hh == src && owner_lane) {
-            const long long kidx = (long long)rl.bh * g.Nk + j;
-            // its arrival number: the forward's, or (lists made here, and a key's entries beyond the numbers
-            // the forward can write) from the key's cursor
-            slotv[e] = A.koffs[kidx] +
-                       (rkv[e] < kSavedRankMost ? (int)rkv[e] : (A.packed ? (int)kSavedRankMost : 0) + atomicAdd(&A.kcursor[kidx], 1));
-            ++n_entries;
+      for (int e0 = 0; e0 < 8; e0 += U) {
+        if (__ballot(8 * q + e0 < gr.n) == 0ull) break;
+        float x[U], d[U];
+        unsigned j[U];
+        u32x4_t vw[U][W], kw[U][W];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int from = (lane & ~7) + e0 + u;
+          x[u] = __shfl(xv[q], from);
+          j[u] = (unsigned)__shfl((int)jv[q], from);
+          d[u] = __shfl(dv[q], from);
+          if (x[u] > 0.f) {
+            const unsigned long long at = (unsigned long long)j[u] * kv_bytes;
+#pragma unroll
+            for (int w = 0; w < W; ++w) vw[u][w] = *reinterpret_cast<const u32x4_t*>(Vbh + at + 128 * w);
+#pragma unroll
+            for (int w = 0; w < W; ++w) kw[u][w] = *reinterpret_cast<const u32x4_t*>(Kbh + at + 128 * w);
           }
-#pragma unroll
-          for (int t = 0; t < DH; ++t) part = fmaf(dov[t], vv.get(t), part);
         }
-        if (FH == 2) part += __shfl_xor(part, 16);
-        float dp = part + __shfl_xor(part, 32);
-        if (x > 0.f) {
-          float gg = pow_rm1<AM>(x, r);
-          float gdp = gg * dp;
-          Z += gg;
-          N += gdp;
-          const float dz = ((w_out != 0.f) ? fmaf(-w_out, (float)bias_dist(pos, (int)j), d) : d) - d_ref;
-          sd1 = fmaf(gdp, dz, sd1);
-          sd0 = fmaf(gg, dz, sd0);
 #pragma unroll
-          for (int t = 0; t < DH; ++t) {
-            const float kt = kk.get(t);
-            qa[t] = fmaf(gdp, kt, qa[t]);
-            qb[t] = fmaf(gg, kt, qb[t]);
+        for (int u = 0; u < U; ++u) {
+          if (x[u] > 0.f) {  // (the same for all lanes of an octet)
+            float part = 0.f;
+#pragma unroll
+            for (int w = 0; w < W; ++w)
+#pragma unroll
+              for (int t = 0; t < PER; ++t) part = fmaf(word_elem<T>(dow[w], t), word_elem<T>(vw[u][w], t), part);
+            const float dp = octet_sum(part);
+            const float gg = pow_rm1<AM>(x[u], r), gdp = gg * dp;
+            Z += gg;
+            N += gdp;
+            const float dz = ((w_out != 0.f) ? fmaf(-w_out, (float)bias_dist(pos, (int)j[u]), d[u]) : d[u]) - d_ref;
+            sd1 = fmaf(gdp, dz, sd1);
+            sd0 = fmaf(gg, dz, sd0);
+#pragma unroll
+            for (int w = 0; w < W; ++w)
+#pragma unroll
+              for (int t = 0; t < PER; ++t) {
+                const float kt = word_elem<T>(kw[u][w], t);
+                qa[w][t] = fmaf(gdp, kt, qa[w][t]);
+                qb[w][t] = fmaf(gg, kt, qb[w][t]);
+              }
+            if (k == e0 + u) dpv[q] = dp;
           }
-          if (rl.hh == src) dpv[e] = dp;
         }
       }
     }
     const float mu = (Z > 0.f) ? N / Z : 0.f;
-    float dq[DH];
+    if (valid) {
+      char* dqrow = reinterpret_cast<char*>(reinterpret_cast<T*>(A.dQ) + q_base) + (long long)i * q_bytes + 16 * k;
 #pragma unroll
-    for (int t = 0; t < DH; ++t) dq[t] = c * fmaf(-mu, qb[t], qa[t]);
-    const float dsc = fmaf(-mu, sd0, sd1);
+      for (int w = 0; w < W; ++w) {
+        float dq[PER];
+#pragma unroll
+        for (int t = 0; t < PER; ++t) dq[t] = c * fmaf(-mu, qb[w][t], qa[w][t]);
+        store_row<T>(reinterpret_cast<T*>(dqrow + 128 * w), PER, dq);
+      }
+      // the scores were formed with q negated when scale_i < 0: undo the sign for z_ij
+      if (k == 0) A.dscale[(long long)rl.bh * g.Nq + i] = (c < 0.f ? -1.f : 1.f) * fmaf(-mu, sd0, sd1) * inv_sqrt_d;
+    }
     // the per-entry records (query, p, c dS) go straight to their place in the key-major arrays
     // (a listed key whose probability rounds to zero here has no place and is dropped)
-    const long long cap = (long long)g.Nq * 2 * kBwdCap;  // entries a head can hold
 #pragma unroll
-    for (int e = 0; e < NE; ++e) {
-      if (slotv[e] >= 0 && slotv[e] < cap) {  // (key_offsets_kernel flags heads whose segments would not fit)
-        float x = fmaxf(fmaf(dv[e], a, -tau), 0.f);
-        float ds = pow_rm1<AM>(x, r) * (dpv[e] - mu);
-        A.csc_i[rl.bh * cap + slotv[e]] = rl.i;
-        A.csc_pw[rl.bh * cap + slotv[e]] = make_float2(pow_r<AM>(x, r), c * ds);
+    for (int q = 0; q < R; ++q) {
+      if (slotv[q] >= 0 && slotv[q] < cap) {  // (key_offsets_kernel flags heads whose segments would not fit)
+        A.csc_i[rl.bh * cap + slotv[q]] = i;
+        A.csc_pw[rl.bh * cap + slotv[q]] = make_float2(pow_r<AM>(xv[q], r), c * pow_rm1<AM>(xv[q], r) * (dpv[q] - mu));
       }
     }
-    if (rl.valid) {
-      store_row<T>(reinterpret_cast<T*>(A.dQ) + q_base + (long long)rl.i * g.q_sn + feat0, DH, dq);
-      // the scores were formed with q negated when scale_i < 0: undo the sign for z_ij
-      if (rl.hh == 0 && owner_lane) A.dscale[row_idx] = sgn * dsc * inv_sqrt_d;
-    }
   };
-  if (__ballot(cnt > 4) == 0ull)
-    finish(std::integral_constant<int, 4>());
-  else
-    finish(std::integral_constant<int, kBwdCap>());
+  Group next = bring(0);
+#pragma unroll 1
+  for (int s = 0; s < 4; ++s) {
+    const Group now = next;
+    if (s < 3) next = bring(s + 1);
+    if (__ballot(now.n > 8) == 0ull)
+      finish(now, s, std::integral_constant<int, 1>());
+    else
+      finish(now, s, std::integral_constant<int, 2 * kBwdCap / 8>());
+  }
 
   if (A.stats) {
     unsigned ent = n_entries;

@@ -1166,6 +1166,15 @@ struct RawRow {
   }
 };
 
+// element t of a 16-byte word of a row, widened
+template <typename T>
+__device__ __forceinline__ float word_elem(const u32x4_t& w, int t) {
+  if constexpr (sizeof(T) == 2)
+    return __uint_as_float((t & 1) ? (w[t >> 1] & 0xffff0000u) : (w[t >> 1] << 16));
+  else
+    return __uint_as_float(w[t]);
+}
+
 template <typename T>
 __device__ __forceinline__ void store_row(T* row, int n, const float* v) {
   if constexpr (sizeof(T) == 2) {

@@ -72,3 +72,35 @@ def test_negative_scales_and_weak_short_rows():
     for n in (97, 130, 260):  # short rows that keep a good part of their keys
         data = synth.make_inputs(B=2, H=2, n=n, nk=n, d=64, dtype="bf16", scale="none", seed=n)
         _check(data, 1.5, "bf16", "short rows n%d" % n)
+
+
+@pytest.mark.parametrize("d,dtype", [(64, "bf16"), (128, "bf16"), (64, "fp32"), (128, "fp32")])
+@pytest.mark.parametrize("use_saved", [False, True])
+def test_supports_of_every_length(use_saved, d, dtype):
+    """The backward's row kernel takes eight entries of a row at a time: rows of 1 to 32 entries (16 per half row at most), uneven between
+    the halves, next to each other; the last 128-row block is ragged."""
+    n = 300
+    data = synth.make_inputs(B=1, H=2, n=n, nk=n, d=d, dtype=dtype, scale="none", seed=d)
+    # features 0 .. 31: every query in a class of its own feature, with as many keys of one and the same score far above
+    # the rest (features 32 .. 47) as the class has; features 48 .. are the keys' alone, so that dQ is not zero
+    data["Q"][..., :32] = data["Q"][..., 48:] = 0.0
+    data["K"][..., :32] = 0.0
+    free, lengths = list(range(n)), []
+    while True:
+        length = len(lengths) + 1
+        first = min(length, 16) if length % 3 else length // 2  # of the first half row
+        keys = [j for j in free if (j // 4) % 2 == 0][:first] + [j for j in free if (j // 4) % 2 == 1][:length - first]
+        if len(keys) < length or length > 24:
+            break
+        free = [j for j in free if j not in keys]
+        data["K"][:, :, keys, :48] = 0.0
+        data["K"][:, :, keys, len(lengths)] = 5.0
+        lengths.append(length)
+    assert len(lengths) >= 18
+    data["Q"][:, :, np.arange(n), np.arange(n) % len(lengths)] = 8.0
+    data["delta"] = np.sqrt(d)  # (alpha-1) s = 20 against a spread of 2
+    g = gpu_run(data, 1.5, dtype, causal=False, use_saved=use_saved, saved_factor=8, stats=True)
+    r = oracle_run(data, 1.5, causal=False)
+    counts = np.bincount(r["support"].astype(int).ravel(), minlength=len(lengths) + 1)
+    print(counts, compare(g, r, label="lengths %s d%d %s" % (use_saved, d, dtype)), {k: v for k, v in g["stats"].items() if v})
+    assert (counts[1:len(lengths) + 1] > 0).all() and g["stats"]["bwd_support"] == r["support"].sum()
