@@ -89,16 +89,19 @@ struct QCtx {
     float inv_sqrt_d = 1.0f / sqrtf((float)D);
     c = scale * inv_sqrt_d;
     a = (g.alpha - 1.0f) * fabsf(c);
+    load_fragments(g, Q);
+    if constexpr (BIAS) {
+      w = valid ? bias_w<D>(g, h, c, a) : 0.f;
+      pos = i + (g.Nk - g.Nq);
+    }
+  }
+  __device__ __forceinline__ void load_fragments(const Geom& g, const void* Q) {
     const T* qrow = reinterpret_cast<const T*>(Q) + (long long)b * g.q_sb + (long long)h * g.q_sh + (long long)i * g.q_sn;
 #pragma unroll
     for (int cc = 0; cc < NC; ++cc) {
       Frag<T> f = valid ? Elem<T>::load(qrow + 16 * cc + 8 * hh) : Elem<T>::zero();
       qf[cc] = (c < 0.f) ? Elem<T>::negate(f) : f;
       koff[cc] = FragOff<T>::template make<KTile>(li, 2 * cc + hh);
-    }
-    if constexpr (BIAS) {
-      w = valid ? bias_w<D>(g, h, c, a) : 0.f;
-      pos = i + (g.Nk - g.Nq);
     }
   }
 
