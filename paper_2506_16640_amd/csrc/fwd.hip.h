@@ -253,7 +253,7 @@ struct ListCfg {
   static constexpr int kGroup = 8;
   // sequences of at least this length: two query blocks per workgroup (fwd_lists_pair_kernel)
   static constexpr int kPairMinKeys = 16384;
-  // The forward's list kernels bring their tiles straight to LDS (sweep_ring(): three buffers), and its rare second sweep keeps all its cells in
+  // The forward's list kernels bring their tiles straight to LDS (TileRing: three buffers), and its rare second sweep keeps all its cells in
   // scratch memory; fp32 (whose rows are too long for that swizzle at D = 128) stays with two buffers and registers.
   static constexpr bool kRing = sizeof(T) == 2;
   static constexpr int kFwdCells = kRing ? 0 : kLdsCells;

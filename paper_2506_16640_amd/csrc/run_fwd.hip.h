@@ -39,8 +39,7 @@ bool launch_fwd_sparse(const FwdSparseArgs& a, int nblocks, hipStream_t st, void
   bool launched = false;
   if constexpr (sizeof(T) == 2 && D == 64) {  // (the only combination the two-block kernel is built for)
     if (a.force_long || (long_seq && pair_grid >= kPairMinWorkgroups)) {
-    // long sequences: the second sweep skips blocks the first cleared, and a workgroup takes two adjacent blocks
-    // where that still leaves three workgroups for every CU (measured at B 4, H 12, n 4096, where it leaves 1.5:
+    // long sequences: a workgroup takes two adjacent blocks where that still leaves three workgroups for every CU (measured at B 4, H 12, n 4096, where it leaves 1.5:
     // 221 us against 139 us with one block per workgroup)
     hipLaunchKernelGGL((fwd_lists_pair_kernel<T, D, AM, BIAS>), dim3((unsigned)pair_grid), dim3(kThreads), smem, st, a);
     launched = true;
