@@ -396,9 +396,11 @@ __device__ __forceinline__ void sweep_tiles(char* smem, const Slot* slots, int n
 
 // 16 bytes per lane from sbase + voff (global memory) to LDS, at lds (wave-uniform LDS byte address) + 16 lane, without a
 // register in between.  The compiler does not count these loads: before the bytes are read, every wave waits for its
-// own (lds_loads_wait) and the workgroup meets at a barrier.
+// own (lds_loads_wait) and the workgroup meets at a barrier.  Nor does it look for hazards inside the block, so the wait states
+// stand here: one from a scalar write of m0 to the load that takes its LDS address from it, five from a vector write of a scalar register
+// (sbase may come from one) to a load that reads it -- the scalar move is the first of them.
 __device__ __forceinline__ void load_to_lds(const char* sbase, uint32_t voff, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(sbase) : "memory", "m0");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(sbase) : "memory", "m0");
 }
 // until at most N of the wave's loads are under way (they end in order)
 template <int N>
