@@ -265,8 +265,11 @@ __global__ __launch_bounds__(kThreads, (sizeof(T) == 2 ? 4 : 2)) void bwd_rows_k
     //   dQ_i = c (sum_j g dP k_j - mu sum_j g k_j),   dscale_i = sum_j g dP d_j - mu sum_j g d_j,
     // the K rows are gathered in the same pass as the V rows: one memory round trip for both.
     // The sums of dscale take the scores relative to one of the row's own (sum_j dS_ij = 0, so that the difference is only in rounding: at scores
-    // of some tens the products they would otherwise be formed from are ten times as large as what is left of them).
-    const float d_ref = __shfl(dv[0], lane & ~7);
+    // of some tens the products they would otherwise be formed from are ten times as large as what is left of them).  Like the others that one
+    // is without its bias term, which at small scales is many times the scores.
+    float d_first = dv[0];
+    if (w_out != 0.f) d_first = fmaf(-w_out, (float)bias_dist(pos, (int)jv[0]), d_first);
+    const float d_ref = __shfl(xv[0] > 0.f ? d_first : 0.f, lane & ~7);
     float Z = 0.f, N = 0.f, sd1 = 0.f, sd0 = 0.f;
     float qa[W][PER], qb[W][PER];  // this lane's features of sum g dP k and of sum g k
 #pragma unroll
