@@ -773,6 +773,15 @@ __device__ __forceinline__ void make_lists(const FwdSparseArgs& A, const C& q, T
   if (!all_again && !rescore_groups<C, T, D, G>(q, g, A.Q, A.K, top, gn, cut, ne, reinterpret_cast<int*>(smem) + q.wave * kRescoreWords,
                                                 wave_list, cnt))
     ovf[2] = 1;
+  // The cutoff comes from the matrix cores' scores, and what is compared with it from sums in another order.  Where the products are some 1e5
+  // times the bracket's width the two may differ by as much, and none of a row's keys pass: the block is the tiled kernel's, whose scores are
+  // the sweep's.  (A list that is not empty holds the row's largest score.  Rows of infinite or NaN scores have no list.)
+  auto none_passed = [&](bool looked_at) {
+    const bool finite = m1 > -2.9e38f && fabsf(lo) < 3.0e38f;
+    return __ballot(looked_at && live && finite && cnt + __shfl_xor(cnt, 32) == 0) != 0ull;
+  };
+  const unsigned long long swept_rows = __ballot(lost);
+  if (none_passed((((swept_rows | swept_rows >> 32 | swept_rows << 32) >> q.lane) & 1ull) == 0ull)) ovf[2] = 1;
   if (nlost > 0) {
     __syncthreads();
     if (ovf[2] == 0 && nlost <= kScanLanes) {
@@ -782,6 +791,7 @@ __device__ __forceinline__ void make_lists(const FwdSparseArgs& A, const C& q, T
         cnt = min(found, kCandCap);
         if (A.stats) atomicAdd(&A.stats[ENTMAX_STAT_FWD_CAND_TILES], (unsigned long long)max(cnt - places, 0));  // (at most)
       }
+      if (none_passed(true)) ovf[2] = 1;
     }
   }
   bool fits;
@@ -1335,14 +1345,30 @@ __global__ __launch_bounds__(kThreads) void fwd_finish_kernel(FwdSparseArgs A) {
     const bool has_tail = __ballot(cnt > NE) != 0ull;
     bool done = !live;
     int iter = 0;
+    float y_most = -kInf;
+#pragma unroll
+    for (int e = 0; e < NE; ++e) y_most = fmaxf(y_most, yv[e]);
     while (__ballot(!done) != 0ull && iter < kMaxSolveIters) {
       RowSums sums;
       sums.clear();
 #pragma unroll
       for (int e = 0; e < NE; ++e) accumulate<AM>(sums, yv[e] - tau, r);
       if (has_tail)
-        for (int e = NE; e < cnt; ++e) accumulate<AM>(sums, a * __uint_as_float(mylist[e * kListStride].y) - tau, r);
+        for (int e = NE; e < cnt; ++e) {
+          const float y = a * __uint_as_float(mylist[e * kListStride].y);
+          y_most = fmaxf(y_most, y);
+          accumulate<AM>(sums, y - tau, r);
+        }
       sums.combine_halves();
+      if (iter == 0) {
+        // The bracket is that of the list's scores.  Those of the sweep, which the bounds came from, are the same sums in another
+        // order: with them a row of one key had p = 1 - 2 (a d_sweep - a d_list) (alpha 1.5) where it is 1.
+        y_most = fmaxf(y_most, __shfl_xor(y_most, 32));
+        if (y_most > -kInf) {
+          lo = y_most - 1.0f;
+          hi = y_most - __builtin_amdgcn_exp2f(-(g.alpha - 1.0f) * __builtin_amdgcn_logf((float)lim));
+        }
+      }
       if (!done) done = solve_step<AM>(sums, r, tau, lo, hi);
       ++iter;
     }

@@ -1,5 +1,5 @@
-"""GPU checks of what rounding leaves of the list path's results where terms cancel: the gradient of the scale with a bias many times
-the scores."""
+"""GPU checks of what rounding leaves of the list path's results: the gradient of the scale with a bias many times the scores, rows of one
+key, and rows whose scores' rounding is as wide as the threshold's bracket."""
 import numpy as np
 import pytest
 
@@ -26,3 +26,41 @@ def test_scale_gradient_beside_a_large_bias(d, dtype, use_saved):
     errs = {n: rel_err(g[n], r[n]) for n in ("dbeta", "dQ", "dV")}
     print(d, dtype, errs, g["dbeta"], r["dbeta"])
     assert errs["dbeta"] <= 2e-3, errs
+
+
+@pytest.mark.parametrize("alpha", [1.5, 2.0, 1.25, 1.7])
+@pytest.mark.parametrize("d", [64, 128])
+def test_rows_of_one_key(d, alpha):
+    """A row of one key has p = 1 whatever order its score was summed in: y = a d and tau = y - 1 are rounded to fp32, half a unit in the last
+    place of y each, and p = (a d - tau)^r is off by r times that (and a few roundings of values near 1)."""
+    n, r = 400, 1.0 / (alpha - 1.0)
+    data = synth.make_inputs(B=2, H=2, n=n, nk=n, d=d, dtype="fp32", scale="head", seed=9)
+    data["beta"][:], data["gamma"][:], data["delta"] = 1.0, 0.0, 11.0  # scale 12
+    g = gpu_run(data, alpha, "fp32", bwd=False)
+    y = 12.0 * (alpha - 1.0) / np.sqrt(d) * np.matmul(data["Q"].astype(np.float64), data["K"].transpose(0, 1, 3, 2).astype(np.float64))
+    y = np.where(np.tril(np.ones((n, n), dtype=bool)), y, -np.inf)
+    two = np.sort(y, axis=-1)[..., -2:]
+    one = two[..., 1] - two[..., 0] > 1.01
+    value = np.take_along_axis(data["V"], y.argmax(-1)[..., None], axis=2).astype(np.float64)
+    p = (g["O"] * value).sum(-1) / (value * value).sum(-1)
+    bar = r * np.spacing(np.abs(two[..., 1]).astype(np.float32)) + 4 * 2.0 ** -24
+    print(d, alpha, "rows", int(one.sum()), "p off by", np.abs(p - 1.0)[one].max(), "of the bar", (np.abs(p - 1.0) / bar)[one].max())
+    assert one.sum() > 500 and (np.abs(p - 1.0) <= bar)[one].all()
+
+
+@pytest.mark.parametrize("size", [1024.0, 2048.0, 4096.0, 8192.0])
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("d,dtype", [(64, "bf16"), (128, "bf16"), (64, "fp32")])
+def test_scores_that_round_by_the_width_of_the_bracket(d, dtype, causal, size):
+    """Half of the products are +- size^2 and cancel: the sums round by a hundredth of the bracket's width to several times it, another way in
+    every order of summation.  Which keys a row has is then a matter of rounding, but its probabilities add up to one."""
+    data = synth.make_inputs(B=2, H=3, n=500, nk=500, d=d, dtype=dtype, scale="none", seed=4)
+    sign = np.where(np.arange(d // 2) % 2 == 0, 1.0, -1.0)
+    data["Q"][..., : d // 2] = size * np.random.default_rng(8).permuted(np.broadcast_to(sign, data["Q"].shape[:3] + (d // 2,)), axis=-1)
+    data["K"][..., : d // 2] = size
+    data["Q"][..., d // 2:] *= 16.0
+    data["V"][:] = 1.0
+    g = gpu_run(data, 1.5, dtype, causal=causal, bwd=False, stats=True)
+    off = np.abs(g["O"] - 1.0).max(-1)
+    print(d, dtype, causal, size, "largest deviation", off.max(), {k: v for k, v in g["stats"].items() if v and k.startswith("fwd")})
+    assert off.max() <= 1e-2  # (O is rounded to bf16: 4e-3)
