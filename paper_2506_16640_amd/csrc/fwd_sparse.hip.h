@@ -479,6 +479,9 @@ struct OctetScores {
 };
 
 constexpr int kRescoreWords = 64 * (kTopGroups + 1);  // of LDS, per wave, for rescore_groups()
+// A word of rescore_groups(): the lane (6 bits), the group's number (Nk <= 2^22: at most 18 bits), and which of the seven words before it,
+// as far as they are in its own eight, are the same lane's (bit o: word o of the eight).
+constexpr int kNumberBits = 18, kBeforeShift = 6 + kNumberBits;
 
 // The keys of the groups that the lanes' first `ne` entries name: their scores, and those above the row's cut go on the
 // lists.  The octets of the wave take the groups in turn, two at a time (D 64, bf16) so that sixteen groups are under way.
@@ -498,23 +501,31 @@ __device__ __forceinline__ bool rescore_groups(const C& q, const Geom& g, const 
     return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
   };
   counts[q.lane] = 0;
-  int n = 0;
+  int n = 0, last = -8;
+  uint32_t earlier = 0u;
 #pragma unroll
   for (int k = 0; k < kTopGroups; ++k) {
     const unsigned long long takers = __ballot(k < ne);
-    if (k < ne) slots[n + lanes_below(takers)] = (int)((__float_as_uint(top.t[k]) & ~gn.keep) << 6) | q.lane;
+    if (k < ne) {
+      const int at = n + lanes_below(takers);
+      earlier = (at >> 3) == (last >> 3) ? earlier | 1u << (last & 7) : 0u;
+      last = at;
+      slots[at] = (int)(earlier << kBeforeShift | (__float_as_uint(top.t[k]) & ~gn.keep) << 6) | q.lane;
+    }
     n += (int)__popcll(takers);
   }
   __builtin_amdgcn_wave_barrier();
 #pragma unroll 1
   for (int s0 = 0; s0 < n; s0 += 8 * N) {
     int id[N], j0[N];
+    uint32_t same[N];  // the octets before this one that have a group of its lane
     typename O::Row row[N];
 #pragma unroll
     for (int u = 0; u < N; ++u) {
       const uint32_t slot = (uint32_t)slots[min(s0 + 8 * u + oct, n - 1)];
       id[u] = (int)(slot & 63u);
-      j0[u] = O::first_key((int)(slot >> 6), id[u] >> 5);
+      j0[u] = O::first_key((int)((slot >> 6) & ((1u << kNumberBits) - 1u)), id[u] >> 5);
+      same[u] = slot >> kBeforeShift;
       row[u] = o.row(q, cut, id[u]);
       if (s0 + 8 * u + oct >= n) row[u].lim = 0;
     }
@@ -526,11 +537,18 @@ __device__ __forceinline__ bool rescore_groups(const C& q, const Geom& g, const 
       for (int u = 0; u < N; ++u) {
         const int j = o.key(j0[u], r0);
         const bool pass = j < row[u].lim && d[u] > row[u].cut;
-        const unsigned mine = (unsigned)(__ballot(pass) >> (8 * oct)) & 0xffu;
-        // (an octet's place in its list: the hardware adds for the lanes of one instruction in their order)
-        int before = 0;
-        if (c == 0) before = atomicAdd(counts + id[u], (int)__popc(mine));
-        const int at = __shfl(before, q.lane & ~7) + (int)__popc(mine & ((1u << c) - 1u));
+        const unsigned long long all = __ballot(pass);
+        const unsigned mine = (unsigned)(all >> (8 * oct)) & 0xffu;
+        // The octet's place in its list: behind what came in earlier turns and in this one from octets before it.  (The order in which the
+        // hardware adds for the lanes of one instruction is not relied on.)
+        int at = counts[id[u]] + (int)__popc(mine & ((1u << c) - 1u));
+        __builtin_amdgcn_wave_barrier();
+        if (c == 0) atomicAdd(counts + id[u], (int)__popc(mine));
+        __builtin_amdgcn_wave_barrier();
+        if (__ballot(same[u] != 0u) != 0ull) {
+#pragma unroll
+          for (int k = 0; k < 7; ++k) at += ((same[u] >> k) & 1u) != 0u ? (int)__popc((unsigned)(all >> (8 * k)) & 0xffu) : 0;
+        }
         if (pass && at < kCandCap) wave_list[at * kListStride + id[u]] = make_uint2((unsigned)j, __float_as_uint(d[u]));
       }
     }
