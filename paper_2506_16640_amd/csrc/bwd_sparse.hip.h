@@ -13,7 +13,7 @@
 //                      of these counts (every key gets a segment that can hold all its entries), and
 //                      the list of keys with long segments;
 //   bwd_rows_kernel    everything row-wise (mu, dscale, dQ) from the lists, by
-//                      gathering the few K and V rows (one lane pair per row).
+//                      gathering the few K and V rows (eight lanes per row).
 //                      Each entry's (query, p, c dS) goes straight into its key's segment, at the
 //                      place a returning atomic on the key's cursor hands out;
 //   bwd_keys_kernel    eight lanes per key (one wave per key for long segments): dV_j and dK_j as
@@ -116,8 +116,12 @@ __global__ __launch_bounds__(kThreads, (ListCfg<T, D>::kOcc)) void bwd_lists_ker
 // brings, and the gathers are done by eight lanes (an octet) per row, eight rows at a time, each lane an eighth of the features in 16-byte words: a
 // gathered row is then one line per load instruction, and an entry costs its eight lanes some 45 vector instructions, where a lane pair per row
 // spent 200 for every entry of the longest of 32 rows (two to a SIMD at 226 registers).  Lane k of the octet holds entries k, k + 8, ... of the row
-// (both halves' lists one after the other).  B 4, H 12, n 4096, D 64: 51 -> 32 us (alpha 1.25: 73 -> 60); B 2, H 16, n 8192, D 128: 147 -> 94.
-// Two entries of a row under way at a time (D 64; one at D 128) and four workgroups per CU; four entries 33.6 us; five workgroups spill (44 to 72).
+// (both halves' lists one after the other).  B 4, H 12, n 4096, D 64: 60 -> 41 us; B 2, H 16, n 8192, D 128: 151 -> 104.
+// The four steps of eight rows are chains of dependent reads one after the other, 16 of them a step where a row has more than eight entries: a
+// launch that does not fill the chip, or whose rows are long, is faster with one step a wave (SPREAD, see rows_spread()): alpha 1.25, n 4096
+// 75 (lane pairs) / 78 / 67 us; 16 heads, n 437 28 / 32 / 13.
+// Two entries of a row under way at a time (D 64; one at D 128) and four workgroups per CU; four entries 46 us, or only for long rows 84 where it
+// is 78; five workgroups spill.
 // The same division of the gathers in the forward's finish kernel, whose lane pairs hold little beside the value row, was slower (44 -> 52 to 57 us).
 template <typename T, int D>
 struct RowsCfg {
@@ -130,17 +134,19 @@ __device__ __forceinline__ float octet_sum(float v) {
   v += dpp_move<0x4e>(v);   // lane ^ 2
   return v + dpp_move<0x141>(v);  // lane 7 - k of the octet: the other four
 }
-template <typename T, int D, int AM>
+template <typename T, int D, int AM, bool SPREAD>
 __global__ __launch_bounds__(kThreads, (sizeof(T) == 2 ? 4 : 2)) void bwd_rows_kernel(BwdSparseArgs A) {
   const Geom& g = A.g;
-  if ((int)blockIdx.x >= g.B * g.H * A.nqb) {  // riders behind the row workgroups
-    transpose_ride<T, D>(A.ride, (int)blockIdx.x - g.B * g.H * A.nqb);
+  const int row_workgroups = g.B * g.H * A.nqb * (SPREAD ? kWaves : 1);
+  if ((int)blockIdx.x >= row_workgroups) {  // riders behind the row workgroups
+    transpose_ride<T, D>(A.ride, (int)blockIdx.x - row_workgroups);
     return;
   }
   using Cfg = RowsCfg<T, D>;
   constexpr int W = Cfg::W, PER = Cfg::kPer, U = Cfg::kAhead;
   RowLane rl;
-  rl.init(g, A.nqb);
+  rl.init(g, A.nqb, SPREAD);
+  const int only_step = (int)threadIdx.x >> 6;  // SPREAD: of the four steps of eight rows each, the wave's
   const int lane = threadIdx.x & 63, oct = lane >> 3, k = lane & 7;
   const float r = 1.0f / (g.alpha - 1.0f);
   const long long row_idx = (long long)rl.bh * g.Nq + (rl.valid ? rl.i : 0);
@@ -186,14 +192,27 @@ __global__ __launch_bounds__(kThreads, (sizeof(T) == 2 ? 4 : 2)) void bwd_rows_k
     // not take the list path: in a head whose other blocks do, those places must not stay undefined.  They get
     // records that add nothing.
     if (A.packed && bflag == kBlockListsUnused && hflag == kHeadMixed) {
-      for (int e = 0; e < cnt_own; ++e) {
-        const uint2 en = lists[place_own + e];
-        const unsigned key = min(en.x & ((1u << kSavedKeyBits) - 1u), (unsigned)(g.Nk - 1)), rank = en.x >> kSavedKeyBits;
-        const long long kidx = (long long)rl.bh * g.Nk + key;
-        const int slot = A.koffs[kidx] + (rank < kSavedRankMost ? (int)rank : (int)kSavedRankMost + atomicAdd(&A.kcursor[kidx], 1));
-        if (slot >= 0 && slot < cap) {
-          A.csc_i[rl.bh * cap + slot] = min(rl.i, g.Nq - 1);
-          A.csc_pw[rl.bh * cap + slot] = make_float2(0.f, 0.f);
+      const int mine = !SPREAD || (rl.li >> 3) == only_step ? cnt_own : 0;
+      constexpr int P = 4;  // entries under way at a time
+      for (int e0 = 0; __ballot(e0 < mine) != 0ull; e0 += P) {
+        uint2 en[P];
+        int slot[P];
+#pragma unroll
+        for (int e = 0; e < P; ++e)
+          if (e0 + e < mine) en[e] = lists[place_own + e0 + e];
+#pragma unroll
+        for (int e = 0; e < P; ++e) {
+          if (e0 + e >= mine) continue;
+          const unsigned key = min(en[e].x & ((1u << kSavedKeyBits) - 1u), (unsigned)(g.Nk - 1)), rank = en[e].x >> kSavedKeyBits;
+          const long long kidx = (long long)rl.bh * g.Nk + key;
+          slot[e] = A.koffs[kidx] + (rank < kSavedRankMost ? (int)rank : (int)kSavedRankMost + atomicAdd(&A.kcursor[kidx], 1));
+        }
+#pragma unroll
+        for (int e = 0; e < P; ++e) {
+          if (e0 + e < mine && slot[e] >= 0 && slot[e] < cap) {
+            A.csc_i[rl.bh * cap + slot[e]] = min(rl.i, g.Nq - 1);
+            A.csc_pw[rl.bh * cap + slot[e]] = make_float2(0.f, 0.f);
+          }
         }
       }
     }
@@ -349,15 +368,22 @@ __global__ __launch_bounds__(kThreads, (sizeof(T) == 2 ? 4 : 2)) void bwd_rows_k
       }
     }
   };
-  Group next = bring(0);
-#pragma unroll 1
-  for (int s = 0; s < 4; ++s) {
-    const Group now = next;
-    if (s < 3) next = bring(s + 1);
-    if (__ballot(now.n > 8) == 0ull)
-      finish(now, s, std::integral_constant<int, 1>());
+  auto row_step = [&](const Group& gr, int step) {
+    if (__ballot(gr.n > 8) == 0ull)
+      finish(gr, step, std::integral_constant<int, 1>());
     else
-      finish(now, s, std::integral_constant<int, 2 * kBwdCap / 8>());
+      finish(gr, step, std::integral_constant<int, 2 * kBwdCap / 8>());
+  };
+  Group next = bring(SPREAD ? only_step : 0);
+  if constexpr (SPREAD) {
+    row_step(next, only_step);
+  } else {
+#pragma unroll 1
+    for (int s = 0; s < 4; ++s) {
+      const Group now = next;
+      if (s < 3) next = bring(s + 1);
+      row_step(now, s);
+    }
   }
 
   if (A.stats) {

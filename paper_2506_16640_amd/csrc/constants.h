@@ -22,6 +22,16 @@ inline bool fwd_lists_unpaired(long long heads, int nqb) {
   return nqb >= 2 && (nqb == 2 || pairs >= kUnpairedFromWorkgroups) && pairs < kUnpairedBelowWorkgroups;
 }
 
+// The backward's row kernel takes a 32-row group per workgroup, eight rows a wave in one step, instead of a block and four steps one after the
+// other, while that fills the chip better (up to five blocks per CU), and where rows are long (alpha below 1.5, per-query scales: rows of weak
+// scales), whose steps are chains of dependent reads.  Before -> so: 16 heads, n 437, alpha 1.25 32 -> 13 us; 3 x 12 heads, n 4096 42 -> 34;
+// 4 x 16 heads, n 2500, D 128 (1280 blocks) 52 -> 48; 4 x 12, n 4096 (1536 blocks) alpha 1.25 78 -> 67, per-query scales (8 x 12, n 1999)
+// 82 -> 66, but alpha 1.5 with per-head scales 41 -> 46: what a wave reads for its rows' scalars is then shared by four times as few.
+constexpr int kRowsSpreadBelow = 1408;
+inline bool rows_spread(long long blocks, float alpha, bool query_scales) {
+  return blocks < kRowsSpreadBelow || (blocks < (1 << 20) && (alpha < 1.45f || query_scales));  // (a launch has less than 2^32 threads)
+}
+
 constexpr int kCandCap = 32;     // candidate entries per lane = per half row (forward lists)
 constexpr int kBwdCap = 16;      // support entries per lane = per half row (the lists the backward works from)
 constexpr int kListStride = 64;  // lists are stored slot-major per wave: entry s of the 64 lanes together

@@ -1216,34 +1216,28 @@ __device__ __forceinline__ void store_row(T* row, int n, const float* v) {
   }
 }
 
-// Row coordinates of a lane in the list kernels.  FH = 1: wave w of block qb owns rows qb*128 + 32 w .. + 31,
-// lane l row (l % 32), list half hh = l / 32 -- the same assignment as in the sweeps that wrote the lists; a
-// workgroup is one 128-row block.  FH = 2: two lanes per list half, each with half of that half's features
-// (f = 0, 1): a wave owns 16 rows, lane l = 32 hh + 16 f + r, and two consecutive workgroups share a block.
+// Row coordinates of a lane in the list kernels: wave w of block qb owns rows qb*128 + 32 w .. + 31, lane l row (l % 32), list half
+// hh = l / 32 -- the same assignment as in the sweeps that wrote the lists; a workgroup is one 128-row block.  With `groups`
+// it is one of the block's four 32-row groups, which all four waves then have.
 // (li, w32): the row's lane and 32-row group in the sweeps' numbering, as list_entry() wants them.
 // Where the heads divide evenly over the eight XCDs the workgroups are renumbered so that a head's rows all run on
 // one XCD, the one whose L2 saw the head's keys and lists in the sweeps (finish kernel, measured on one box:
 // B 4, H 12, n 4096: 54 -> 50 us; with 12 heads at n 32768, one and a half heads per XCD, it was 60 -> 73 us).
 struct RowLane {
-  int bh, b, h, qb, i, li, hh, f, w32;
+  int bh, b, h, qb, i, li, hh, w32;
   bool valid;
-  template <int FH = 1>
-  __device__ __forceinline__ void init(const Geom& g, int nqb) {
-    static_assert(FH == 1 || FH == 2, "one or two lanes per list half");
-    constexpr int R = 32 / FH;  // rows per wave
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int vb = (g.B * g.H) % 8 == 0 ? xcd_remap(blockIdx.x, g.B * g.H * nqb * FH) : (int)blockIdx.x;
-    const int blk = vb / FH, sub = vb % FH;
+  __device__ __forceinline__ void init(const Geom& g, int nqb, bool groups = false) {
+    const int tid = threadIdx.x, lane = tid & 63, per_block = groups ? kWaves : 1;
+    const int vb = (g.B * g.H) % 8 == 0 ? xcd_remap(blockIdx.x, g.B * g.H * nqb * per_block) : (int)blockIdx.x;
+    const int blk = vb / per_block;
     bh = blk / nqb;
     qb = blk % nqb;
     b = bh / g.H;
     h = bh % g.H;
     hh = lane >> 5;
-    f = (lane & 31) / R;
-    const int row_in_block = (sub * kWaves + wave) * R + (lane & (R - 1));
-    li = row_in_block & 31;
-    w32 = row_in_block >> 5;
-    i = qb * kBlockRows + row_in_block;
+    li = lane & 31;
+    w32 = groups ? vb % per_block : tid >> 6;
+    i = qb * kBlockRows + w32 * 32 + li;
     valid = i < g.Nq;
   }
 };

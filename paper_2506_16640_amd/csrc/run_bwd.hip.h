@@ -33,7 +33,6 @@ bool launch_bwd_kernels(const BwdArgs& a_in, const Layout& L, int B, int H, hipS
 
 template <typename T, int D, int AM, bool BIAS>
 bool launch_bwd_rows(const BwdSparseArgs& a, int nblocks, hipStream_t st, void* const* ev, bool from_saved) {
-  const dim3 row_grid((unsigned)(a.g.B * a.g.H * a.nqb + a.ride.workgroups()));
   if (!from_saved) {
     // no lists from the forward: one Q K^T sweep at tau rebuilds the supports
     size_t smem = ListCfg<T, D>::kLdsBytes;
@@ -51,7 +50,11 @@ bool launch_bwd_rows(const BwdSparseArgs& a, int nblocks, hipStream_t st, void* 
                        use_lds ? 1 : 0);
     if (!launch_ok()) return false;
   }
-  hipLaunchKernelGGL((bwd_rows_kernel<T, D, AM>), row_grid, dim3(kThreads), 0, st, a);
+  const long long blocks = (long long)a.g.B * a.g.H * a.nqb;
+  if (rows_spread(blocks, a.g.alpha, a.g.scale_layout == 2))
+    hipLaunchKernelGGL((bwd_rows_kernel<T, D, AM, true>), dim3((unsigned)(blocks * kWaves + a.ride.workgroups())), dim3(kThreads), 0, st, a);
+  else
+    hipLaunchKernelGGL((bwd_rows_kernel<T, D, AM, false>), dim3((unsigned)(blocks + a.ride.workgroups())), dim3(kThreads), 0, st, a);
   return launch_ok();
 }
 
