@@ -253,9 +253,13 @@ struct ListCfg {
   static constexpr int kGroup = 8;
   // sequences of at least this length: two query blocks per workgroup (fwd_lists_pair_kernel)
   static constexpr int kPairMinKeys = 16384;
-  // The forward's list kernels bring their tiles straight to LDS (TileRing: three buffers), and its rare second sweep keeps all its cells in
-  // scratch memory; fp32 (whose rows are too long for that swizzle at D = 128) stays with two buffers and registers.
+  // The forward's list kernels bring their tiles straight to LDS (TileRing: three buffers), and its second sweep, which weak scales take often,
+  // keeps its cells in scratch memory; only where it has at most two tiles, the first three of a thread in the third buffer (D = 64, forward:
+  // B 8, H 12, no scale, n 64 37.5 -> 35.5 us, n 128 50.6 -> 48, n 256 84 -> 80; D = 128, n 1100 80 -> 82, so not there).  fp32 (whose
+  // rows are too long for that swizzle at D = 128) stays with two buffers and registers.
   static constexpr bool kRing = sizeof(T) == 2;
+  static constexpr int kThirdBufferCells = kRing && D == 64 ? 3 : 0;
+  static_assert(kThirdBufferCells * kThreads * 20 <= kTile * D * (int)sizeof(T), "the cells fit the buffer");
   static constexpr int kFwdCells = kRing ? 0 : kLdsCells;
   static constexpr size_t kFwdTiles = (kRing ? 3 : 2) * (size_t)kTile * D * sizeof(T);
   static constexpr size_t kFwdLdsBytes = kFwdTiles + kListHeaderBytes + kScanBytes + (size_t)kFwdCells * kThreads * 20;

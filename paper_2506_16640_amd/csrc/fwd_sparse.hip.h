@@ -89,17 +89,19 @@ struct CellBuf {
   char* lds;
   char* strip;  // workgroup-uniform
   int tid;
+  int in_lds;  // cells of a thread that go to LDS (LS, or 0)
   static constexpr size_t kBytesPerWorkgroup = cell_bytes_per_workgroup(CAP);
   static constexpr int kLdsBytes = LS * kThreads * 20;
   __device__ __forceinline__ void init(void* base, char* lds_, int tid_, int strip_no = blockIdx.x) {
     strip = reinterpret_cast<char*>(base) + (size_t)strip_no * kBytesPerWorkgroup;
     lds = lds_;
     tid = tid_;
+    in_lds = LS;
   }
   // n: cells this thread stored before.  A strip that is full keeps overwriting its last cell (the caller
   // then discards the lists).
   __device__ __forceinline__ void store(int n, const f32x4_t& v, int key) {
-    if (LS > 0 && n < LS) {
+    if (LS > 0 && n < in_lds) {
       const int e = n * kThreads + tid;
       *reinterpret_cast<f32x4_t*>(lds + e * 16) = v;
       *reinterpret_cast<int*>(lds + LS * kThreads * 16 + e * 4) = key;
@@ -110,7 +112,7 @@ struct CellBuf {
     }
   }
   __device__ __forceinline__ void load(int n, f32x4_t& v, int& key) const {
-    if (LS > 0 && n < LS) {
+    if (LS > 0 && n < in_lds) {
       const int e = n * kThreads + tid;
       v = *reinterpret_cast<const f32x4_t*>(lds + e * 16);
       key = *reinterpret_cast<const int*>(lds + LS * kThreads * 16 + e * 4);
@@ -153,21 +155,30 @@ __device__ __forceinline__ void mask_block(const C& q, f32x16_t& acc, int j0) {
 
 // A cell holds at most four candidates, so there are at least as many candidates as cells.  One pass: the scores
 // above the cutoff go to the list.  Returns how many there are; more than CAP: the block's lists are discarded.
+// Four cells are read at a time: one after the other they are a chain of memory round trips (forward, 12 heads: B 4, n 4096, alpha 1.25
+// 406 -> 399 us, no scale 660 -> 645; 8 heads, n 1100, alpha 1.7, no scale 79.6 -> 77.6).
 template <int CAP, typename CB>
 __device__ __forceinline__ int cells_to_list(const CB& cb, int ncell, float cut, uint2* mylist, int& cnt) {
   int total = 0;
-  for (int k = 0; k < ncell; ++k) {
-    f32x4_t dv;
-    int jc;
-    cb.load(k, dv, jc);
+  constexpr int P = 4;  // cells under way at a time
+  for (int k = 0; k < ncell; k += P) {
+    f32x4_t dv[P];
+    int jc[P];
 #pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-      if (dv[rr] > cut) {
-        if (cnt < CAP) {
-          mylist[cnt * kListStride] = make_uint2((unsigned)(jc + rr), __float_as_uint(dv[rr]));
-          ++cnt;
+    for (int u = 0; u < P; ++u)
+      if (k + u < ncell) cb.load(k + u, dv[u], jc[u]);
+#pragma unroll
+    for (int u = 0; u < P; ++u) {
+      if (k + u >= ncell) break;
+#pragma unroll
+      for (int rr = 0; rr < 4; ++rr) {
+        if (dv[u][rr] > cut) {
+          if (cnt < CAP) {
+            mylist[cnt * kListStride] = make_uint2((unsigned)(jc[u] + rr), __float_as_uint(dv[u][rr]));
+            ++cnt;
+          }
+          ++total;
         }
-        ++total;
       }
     }
   }
@@ -209,6 +220,11 @@ __device__ __forceinline__ bool collect_sweep(const C& q, const Geom& g, const v
   if (q.tid < 3) ovf[q.tid] = 0;
   CellBuf<CAP, LS> cb;
   cb.init(cells, lds_cells, q.tid, strip_no < 0 ? (int)blockIdx.x : strip_no);  // (which of the scratch strips is this workgroup's)
+  if constexpr (RING && LS > 0) {  // (the cells' LDS is the ring's third buffer)
+    int first = 0;
+    if constexpr (C::BIAS) first = q.kt_first;
+    if (q.ntiles - first > 2) cb.in_lds = 0;
+  }
   int ncell = 0;
   Slot slots[1];
   slots[0].base = reinterpret_cast<const char*>(reinterpret_cast<const T*>(K) + (long long)q.b * g.kv_sb +
@@ -725,7 +741,8 @@ __device__ __forceinline__ void make_lists(const FwdSparseArgs& A, const C& q, T
                                            unsigned n_vis, int places) {
   const Geom& g = A.g;
   int* ovf = reinterpret_cast<int*>(smem + ListCfg<T, D>::kFwdTiles);
-  char* lds_cells = smem + ListCfg<T, D>::kFwdTiles + kListHeaderBytes + sizeof(ScanLds);
+  // (with the ring: in its third buffer, which sweeps of at most two tiles leave alone)
+  char* lds_cells = ListCfg<T, D>::kRing ? smem + 2 * C::kTileBytes : smem + ListCfg<T, D>::kFwdTiles + kListHeaderBytes + sizeof(ScanLds);
   const GroupNumbers<G> gn(g.Nk);
   const int flag_idx = q.bh * A.nqb + q.qb;
   const long long row_idx = (long long)q.bh * g.Nq + (q.valid ? q.i : 0);
@@ -1065,7 +1082,7 @@ __device__ __forceinline__ void fwd_lists_blocks(const FwdSparseArgs& A, int bh_
     return;
   }
   if constexpr (R == 1) {
-    make_lists<C, T, D, AM, Cfg::kGroup, Cfg::kFwdCells, Cfg::kRing>(A, q[0], top[0], m1[0], smem, strip_no, n_vis[0], places);
+    make_lists<C, T, D, AM, Cfg::kGroup, Cfg::kRing ? Cfg::kThirdBufferCells : Cfg::kFwdCells, Cfg::kRing>(A, q[0], top[0], m1[0], smem, strip_no, n_vis[0], places);
   } else {
     // What is left is done for one block after the other; what the sweep found out about the second waits in LDS, in the third
     // tile buffer (which nothing else uses now), so that only one block's rows are in registers.
