@@ -725,13 +725,19 @@ __device__ __forceinline__ int scan_lanes(const FwdSparseArgs& A, const C& q, in
   return cnt;
 }
 
-// Groups to rescore in a wave from which on the second sweep is taken instead: kStart, and kPerTile for every 128 keys of the block.
-// Measured (kernel, never / 160 + 6 / 48 + 24 / 24 + 12): B 4, H 12, n 4096, alpha 1.25 220 / 195 / 221 / 196 us; per-query scales, B 3, n 1999, bias
-// 128 / 109 / 128 / 108; B 8, n 1024, alpha 1.5 41 / 41 / 41 / 54; n 4096 93 / 94 / 93 / 98.  fp32, one head of 256, scale 1: 45 us without, 40 with 24 + 24.
-template <typename T, int D>
+// Groups to rescore in a wave up to which the second sweep is not taken: kStart and kPerTile for every 128 keys of the block, for short
+// blocks kShort and 48 for every 128 keys (a sweep of few tiles is over before sixteen groups at a time are).  Measured, bf16 (list kernel, before the short
+// blocks' line; never / 160 + 6 / 48 + 24 / 24 + 12): B 4, H 12, n 4096, alpha 1.25 220 / 195 / 221 / 196 us; per-query scales, B 3, n 1999, bias
+// 128 / 109 / 128 / 108; B 8, n 1024, alpha 1.5 41 / 41 / 41 / 54; n 4096 93 / 94 / 93 / 98.  Forward, 160 + 6 t with 48 + 48 t / without / with
+// 24 + 24 t: B 8, H 12, n 64 24.4 / 26.2 / 24.6, n 200 31.2 / 33.1 / 31.6, n 500 43.0 / 43.8 / 46.5; H 12, n 1024 53.8 / 54.2 / 60.3.  fp32 (forward,
+// 96 + 48 t / 48 + 24 t / 24 + 12 t / always swept): B 2, H 12, n 300 60 / 70 / 70 / 70; B 8, n 600 85 / 103 / 111 / 111; n 4096 320 / 315 / 321 / 599;
+// D 128, H 16, B 2, n 200 64 / 75 / 77 / 77; alpha 1.25, B 2, n 2000 676 / 672 / 700 / 704 (160 + 6 t 690).
+template <typename T>
 struct SweepAgain {
-  static constexpr int kStart = sizeof(T) == 2 ? 160 : 48;
+  static constexpr int kStart = 160;
   static constexpr int kPerTile = sizeof(T) == 2 ? 6 : 24;
+  static constexpr int kShort = sizeof(T) == 2 ? 48 : 96;
+  static __device__ __forceinline__ int most_groups(int keys) { return min(kStart + (keys >> 7) * kPerTile, kShort + (keys >> 7) * 48); }
 };
 
 // What follows the sweep over the scores of a block: the rows' bounds, the scores of the keys that can matter, the lists.
@@ -755,17 +761,18 @@ __device__ __forceinline__ void make_lists(const FwdSparseArgs& A, const C& q, T
   float hi = live ? y1 - __builtin_amdgcn_exp2f(-(g.alpha - 1.0f) * __builtin_amdgcn_logf((float)q.lim)) : 0.f;
   // two-element sub-problem {y1, y2}: its threshold is a lower bound of the row's
   if (live && m2 > -2.9e38f) lo = two_key_bound<AM>(y1, q.a * m2, r);
-  // Rows of at most three blocks keep the two-key bound.  Not for speed: short rows that keep most of their keys then reach
-  // the tiled kernel, whose smallest cases the tests are made of.  Training steps with the limit at 96, without one and
-  // at 192: B 8, H 12, n 96 124, 106 and 123 us; n 160 152, 147, 187; B 1, H 1, n 256, fp32 151, 150, 256; rows of
-  // constant logit range (n 256 to 4096) the same with any.
+  // Rows of at most three blocks keep the two-key bound: in a dense head the tighter one keeps some first blocks, whose rows are that short, on
+  // long lists, and the launch then waits for the finish kernel's long tail and for the tiled kernel, which the head's other blocks
+  // need anyway.  Training steps with the limit / without: B 2, H 12, dense rows, n 256 93 / 142 us, n 300 108 / 154, n 500 135 / 182; B 8, n 128
+  // 134 / 157.  Rows without a scale, which all fit the lists, pay for it: n 96 112 / 100, n 128 124 / 113, forward n 64 40 / 36.
   if (live && q.lim > 96) lo = top_groups_bound<AM>(top, gn, q.a, lo, r);
   lo = fminf(lo, hi);
   const float cut = raw_cut(q.a, live, lo);
 
   // A lane whose last place is above the cut may have lost groups that count.  Where there are few of them in the block all their
-  // keys are looked at (scan_lanes()); where there are more, a second sweep over the scores of the block finds their keys, in which
-  // the other lanes look for nothing (but in a wave most of whose lanes are lost, all of them do).
+  // keys are looked at (scan_lanes()); where there are more, a second sweep over the scores of the block finds the keys of all its rows.  (With
+  // the other lanes' groups rescored all the same, and only the lost ones looked for in the sweep, the longest workgroups had both in turn: forward, 12 heads,
+  // alpha 1.25, B 2, n 1999 236 -> 221 us, with distance bias 257 -> 242, B 4, n 4096 402 -> 391.)
   int first = 0;
   if constexpr (C::BIAS) first = q.kt_first_wave * C::NSB;
   const int seen = (((q.wave_lim_max + 31) >> 5) - first) * GroupNumbers<G>::kPerBlock;
@@ -789,25 +796,18 @@ __device__ __forceinline__ void make_lists(const FwdSparseArgs& A, const C& q, T
   nlost = __builtin_amdgcn_readfirstlane(nlost);
   most = __builtin_amdgcn_readfirstlane(most);
   // Rescoring goes by the wave with the most groups, the second sweep by the keys: in short rows that keep many keys the sweep is cheaper.
-  using Again = SweepAgain<T, D>;
-  const bool all_again = most > Again::kStart + ((q.block_lim - first * 32) >> 7) * Again::kPerTile;
-  if (all_again) nlost = kThreads;
-  if (lost && nlost <= kScanLanes) {
+  const bool again = nlost > kScanLanes || most > SweepAgain<T>::most_groups(q.block_lim - first * 32);
+  if (lost && !again) {
     const int x = lost_before + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(lost_lanes >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)lost_lanes, 0u));
     sl->lane[x] = q.tid;
     sl->cut[x] = cut;
     sl->negated[x] = q.c < 0.f ? 1 : 0;
     if constexpr (C::BIAS) sl->w[x] = q.w; else sl->w[x] = 0.f;
   }
-  if (all_again || (nlost > kScanLanes && __popcll(lost_lanes) >= 32)) lost = live;
   if (lost) ne = 0;
   uint2* wave_list = A.cand + list_entry<kCandCap>(q.bh, A.nqb, q.qb, q.wave, 0);
   int cnt = 0;
   unsigned n_qk2 = 0, n_cand_tiles = 0;
-  if (A.stats) n_cand_tiles = distinct_blocks<G>(top, gn, lost && nlost <= kScanLanes ? places : ne, q.lane);
-  if (!all_again && !rescore_groups<C, T, D, G>(q, g, A.Q, A.K, top, gn, cut, ne, reinterpret_cast<int*>(smem) + q.wave * kRescoreWords,
-                                                wave_list, cnt))
-    ovf[2] = 1;
   // The cutoff comes from the matrix cores' scores, and what is compared with it from sums in another order.  Where the products are some 1e5
   // times the bracket's width the two may differ by as much, and none of a row's keys pass: the block is the tiled kernel's, whose scores are
   // the sweep's.  (A list that is not empty holds the row's largest score.  Rows of infinite or NaN scores have no list.)
@@ -815,28 +815,30 @@ __device__ __forceinline__ void make_lists(const FwdSparseArgs& A, const C& q, T
     const bool finite = m1 > -2.9e38f && fabsf(lo) < 3.0e38f;
     return __ballot(looked_at && live && finite && cnt + __shfl_xor(cnt, 32) == 0) != 0ull;
   };
-  const unsigned long long swept_rows = __ballot(lost);
-  if (none_passed((((swept_rows | swept_rows >> 32 | swept_rows << 32) >> q.lane) & 1ull) == 0ull)) ovf[2] = 1;
-  if (nlost > 0) {
-    __syncthreads();
-    if (ovf[2] == 0 && nlost <= kScanLanes) {
-      const int found = scan_lanes<C, T, D, G>(A, q, nlost, first * GroupNumbers<G>::kPerBlock, sl, reinterpret_cast<uint2*>(smem));
-      if (found >= 0) {
-        if (found > kCandCap) ovf[2] = 1;
-        cnt = min(found, kCandCap);
-        if (A.stats) atomicAdd(&A.stats[ENTMAX_STAT_FWD_CAND_TILES], (unsigned long long)max(cnt - places, 0));  // (at most)
-      }
-      if (none_passed(true)) ovf[2] = 1;
-    }
-  }
   bool fits;
-  if (nlost > kScanLanes && ovf[2] == 0) {  // (not written since the barrier)
+  if (again) {
     C qs = q;  // (its fragments and offsets are loaded again: kept through what comes before they would be spilled; scale and window
                // are kept: with them made again too the kernel of B 4, H 12, n 4096, alpha 1.25 took 190 us instead of 185)
     qs.load_fragments(g, A.Q);
-    fits = collect_sweep<C, T, D, kCandCap, LS, RING>(qs, g, A.K, smem, ovf, lds_cells, lost ? cut : kInf, A.cells, wave_list + q.lane, cnt,
-                                                n_qk2, n_cand_tiles, __ballot(lost) != 0ull, strip_no);
+    fits = collect_sweep<C, T, D, kCandCap, LS, RING>(qs, g, A.K, smem, ovf, lds_cells, cut, A.cells, wave_list + q.lane, cnt, n_qk2, n_cand_tiles,
+                                                __ballot(live) != 0ull, strip_no);
   } else {
+    if (A.stats) n_cand_tiles = distinct_blocks<G>(top, gn, lost ? places : ne, q.lane);
+    if (!rescore_groups<C, T, D, G>(q, g, A.Q, A.K, top, gn, cut, ne, reinterpret_cast<int*>(smem) + q.wave * kRescoreWords, wave_list, cnt))
+      ovf[2] = 1;
+    if (none_passed((((lost_lanes | lost_lanes >> 32 | lost_lanes << 32) >> q.lane) & 1ull) == 0ull)) ovf[2] = 1;
+    if (nlost > 0) {
+      __syncthreads();
+      if (ovf[2] == 0) {
+        const int found = scan_lanes<C, T, D, G>(A, q, nlost, first * GroupNumbers<G>::kPerBlock, sl, reinterpret_cast<uint2*>(smem));
+        if (found >= 0) {
+          if (found > kCandCap) ovf[2] = 1;
+          cnt = min(found, kCandCap);
+          if (A.stats) atomicAdd(&A.stats[ENTMAX_STAT_FWD_CAND_TILES], (unsigned long long)max(cnt - places, 0));  // (at most)
+        }
+        if (none_passed(true)) ovf[2] = 1;
+      }
+    }
     pool_want(ovf + 3, cnt, q.lane);
     __syncthreads();
     fits = ovf[2] == 0;
