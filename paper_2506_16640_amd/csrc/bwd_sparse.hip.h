@@ -29,7 +29,7 @@
 namespace entmax {
 
 constexpr int kHeadMixed = 1, kHeadTiled = 2;  // values of a head's flag, see BwdSparseArgs::head_flag
-constexpr int kSortedKeyEntries = 8;        // a key with at most this many entries is summed by one lane pair
+constexpr int kSortedKeyEntries = 8;        // a key with at most this many entries is summed by eight lanes
 
 struct BwdSparseArgs {
   Geom g;

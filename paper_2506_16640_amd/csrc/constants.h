@@ -37,7 +37,8 @@ constexpr int kBwdCap = 16;      // support entries per lane = per half row (the
 constexpr int kListStride = 64;  // lists are stored slot-major per wave: entry s of the 64 lanes together
 // The `saved` buffer packs the rows' support lists into a pool: the size the library asks for holds this many
 // entries per row on average (a larger buffer gives a larger pool), at least kSavedPoolFloor (one block's worst
-// case), plus kSavedPoolPad entries behind the end that speculative reads may touch.
+// case), plus kSavedPoolPad entries behind the end.  (No kernel touches those: they are part of the size that callers have been given, and
+// places are handed out the same with them.)
 // A packed entry's first word is the key index (22 bits: Nk <= 2^22) with, above it, the entry's arrival number
 // among its key's entries, so that the backward knows its place in the key's segment without asking; the largest
 // value stands for "later than that" (those entries take their place from a cursor in the backward).

@@ -12,7 +12,7 @@
 //     2. the scores of the keys of the groups above tau_lb once more, from memory: every key with (alpha-1) s_ij > tau_lb goes on the
 //        row's candidate list (key index + raw score).  Every key of the
 //        support is on that list; nothing else of the row can matter.  Rows with more such groups than were kept are
-//        looked through on their own, or swept a second time.
+//        looked through on their own; where a block has many of them, or many groups, it is swept a second time instead.
 //   fwd_finish_kernel (no matrix work, one lane pair per row)
 //     3. the threshold by the same safeguarded steps as the tiled kernel
 //        (closed-form local-model root for alpha 1.5 / 2, Halley / Newton

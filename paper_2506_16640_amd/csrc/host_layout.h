@@ -180,8 +180,8 @@ inline Layout make_layout(const entmax_attn_params* p) {
   return L;
 }
 
-// Entries the pool of a `saved` buffer of `bytes` bytes holds (beyond them: kSavedPoolPad entries that may be read
-// but never hold anything).  Places are packed into 27 bits next to the 5-bit length.
+// Entries the pool of a `saved` buffer of `bytes` bytes holds (beyond them: kSavedPoolPad entries that
+// are not used).  Places are packed into 27 bits next to the 5-bit length.
 inline long long saved_pool_entries(const Layout& L, size_t bytes) {
   if (bytes < L.sv_pool + (size_t)kSavedPoolPad * 8) return 0;
   const unsigned long long n = (bytes - L.sv_pool) / 8 - kSavedPoolPad;

@@ -409,7 +409,7 @@ __device__ __forceinline__ void lds_loads_wait() {
 }
 
 // The key tiles first .. ntiles - 1 of one natural-layout tensor, straight to LDS, two of them under way while one is worked on: a
-// ring of three buffers at smem.  start(), then step() as long as kt < ntiles, then finish(); all threads of the
+// ring of three buffers at smem.  start(), then step() as long as kt < ntiles (abandon() where that ends early); all threads of the
 // workgroup together.  No registers hold tiles and no wave writes them to LDS, which is what sweep_tiles() spends on each tile.
 template <typename C, typename T, int D>
 struct TileRing {

@@ -1,6 +1,6 @@
-"""GPU parity of the list kernel's block marks at their edges: rows whose large scores lie in fewer, as many and more
-32-key blocks than a lane remembers, all-equal rows, and sequences longer than the marks reach.  The bars are the parity
-tests' (2e-2 on O, 1e-3 on tau: bf16 inputs, sums in fp32)."""
+"""GPU parity of the list kernel's memory of large scores at its edges: rows whose large scores lie in fewer, as many and more
+32-key blocks than a lane has places, all-equal rows, and sequences whose group numbers take many bits of the remembered
+scores.  The bars are the parity tests' (2e-2 on O, 1e-3 on tau: bf16 inputs, sums in fp32)."""
 import numpy as np
 import pytest
 
@@ -35,7 +35,7 @@ def test_large_scores_in_so_many_blocks(blocks, d, dtype):
 
 @pytest.mark.parametrize("n", [31, 170, 200, 1000])
 def test_rows_of_equal_scores(n):
-    """Zero queries: every score is exactly zero, and its bits next to a block's number are a denormal."""
+    """Zero queries: every score is exactly zero, and its bits next to a group's number are a denormal."""
     data = _data(n, n, 64, seed=3)
     data["Q"][:, :, ::3] = 0.0
     for alpha in (1.5, 2.0):
