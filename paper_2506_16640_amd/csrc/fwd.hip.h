@@ -238,12 +238,14 @@ constexpr int kScanBytes = 272;       // ... of the forward's: ScanLds
 // Keys per LDS tile and workgroups per CU of the list sweeps (fwd_sparse.hip.h, bwd_sparse.hip.h), as measured:
 // at D = 64 four 32-key blocks per tile and three workgroups per CU; at D = 128 the query fragments take twice
 // the registers, and two blocks per tile with four workgroups per CU run the backward's sweep a quarter faster; the forward's,
-// which works on two blocks of scores at a time, takes three there too (B 2, H 16, n 8192: 357 us; 577 with four, 128 registers).
+// which works on two blocks of scores at a time, takes three there too (B 2, H 16, n 8192: 357 us; 577 with four, 128 registers).  In fp32 at
+// D = 128 the query fragments alone are 64 registers, and with three the forward's list kernel spilled 57 to 160: two (forward, 16 heads, B 4: n 350 94 -> 80 us,
+// with distance bias and no scale 183 -> 133, n 2500 761 -> 706, with bias 693 -> 580).
 template <typename T, int D>
 struct ListCfg {
   static constexpr int kTile = sizeof(T) == 2 ? (D == 64 ? 128 : 64) : 32;
   static constexpr int kOcc = (sizeof(T) == 2 && D == 128) ? 4 : 3;
-  static constexpr int kFwdOcc = 3;
+  static constexpr int kFwdOcc = (sizeof(T) == 4 && D == 128) ? 2 : 3;
   // key tiles in flight (sweep_tiles).  Measured at B 4, H 12, n 4096, D 64: two in flight cost registers
   // (spills at three workgroups per CU: 145 us against 139; no spills at two per CU: 188 us)
   static constexpr int kDepth = 1;
